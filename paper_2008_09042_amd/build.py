@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libmaxwell.so")
-SOURCES = ["api.hip", "plan.hip", "gemm.hip", "fft.hip", "elementwise.hip", "nufft.hip", "tucker_fused.hip", "core_contract.hip",
+SOURCES = ["api.hip", "plan.hip", "gemm.hip", "fft_tr16.hip", "fft_tr32.hip", "fft.hip", "elementwise.hip", "nufft.hip", "tucker_fused.hip", "core_contract.hip",
            "mode3.hip", "solver.hip", "admm.hip", "compress.hip", "skinny.hip", "diag.hip", "tune.hip"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -56,6 +56,11 @@ hipError_t split_bf16_launch(const float2* src, int64_t count, uint16_t* hi, uin
 hipError_t bf16_split_diag_launch(const float* x, int64_t n, int variant, uint16_t* hi, uint16_t* lo,
                                   hipStream_t st);
 
+// A divisor of x < 2^31 as a multiply-high, an add and a shift (built by fast_div, fft_device.h).
+struct FastDiv {
+  uint32_t d, m, l;
+};
+
 // ---------------------------------------------------------------- FFT
 // Transform along one axis of data laid out [outer][n][inner] (complex elements).
 // centred unitary DFT; dir = -1 forward (exp(-2 pi i ...)), +1 inverse.
@@ -81,6 +86,11 @@ struct FftAxisArgs {
   int64_t coil_elems, nsamples;  // N, M
   uint32_t coil_magic, coil_shift;  // multiply-high division by N (set by fft_axis_launch)
   int lines;              // lines per workgroup (set by fft_axis_launch)
+  // two-radix kernel (set by fft_axis_launch): lines visited per [outer] and [inner], log2 of
+  // `lines`, the radices n = r0 r1
+  uint32_t tr_outer, tr_inner;
+  int tr_lshift;
+  FastDiv tr_r0, tr_r1, tr_chunks, tr_coil;  // ..., tiles per outer index, lines per coil
   // optional gridding window (the NUFFT's zero-pad and crop with deapodisation, 2D grids of
   // g0 x g1 with the centred wn0 x wn1 window at (woff0, woff1)); grid rows and columns
   // outside the window that no later pass reads are neither computed nor written:
@@ -103,6 +113,8 @@ struct FftLaunch {
   FftAxisArgs a;
   int smp;
   bool twl;
+  bool tr, big;  // two-radix kernel (fft_tr.h); with radices above 16
+  int variant, threads;
   int64_t blocks;
   size_t lds;
 };
@@ -119,6 +131,11 @@ struct FftMulti {
 void fft_collect(std::vector<FftLaunch>* sink);
 // Launches prepared passes of independent arrays, several per launch.
 hipError_t fft_multi_launch(const std::vector<FftLaunch>& ls, hipStream_t st);
+// The two-radix kernel's launches, radices up to 16 and up to 32.
+hipError_t fft_tr16_launch(const FftLaunch& l, hipStream_t st);
+hipError_t fft_tr32_launch(const FftLaunch& l, hipStream_t st);
+hipError_t fft_tr16_multi(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st);
+hipError_t fft_tr32_multi(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st);
 int fft_factorise(int64_t n, int* radix);  // returns number of passes, 0 if unsupported
 
 // ---------------------------------------------------------------- elementwise / sampling

@@ -24,7 +24,9 @@ namespace mx {
 
 namespace {
 
+// ---------------------------------------------------------------- pass by pass in LDS
 constexpr int NT = 256;
+constexpr int TR_NT = 256;          // most threads of a two-radix workgroup
 constexpr int TILE = 4096;          // complex elements per LDS tile at most (before padding):
                                     // with the twiddles, about 40 KB, four workgroups per CU
 constexpr int TW_LDS_MAX = 1024;    // twiddle tables up to this length are staged in LDS
@@ -278,10 +280,80 @@ int fft_factorise(int64_t n, int* radix) {
   return np;
 }
 
+namespace {
+
+// n = r0 r1 with the smallest larger radix, both among the two-radix kernel's cases; r0 >= r1.
+bool tr_radices(int n, int& r0, int& r1) {
+  static const int set[] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32};
+  auto has = [](int v) {
+    for (int s : set)
+      if (s == v) return true;
+    return false;
+  };
+  for (int s : set)
+    if (n % s == 0 && n / s <= s && has(n / s)) {
+      r0 = s;
+      r1 = n / s;
+      return true;
+    }
+  return false;
+}
+
+// Division by any d < 2^31, the magic number in integer arithmetic (fast_div's holds d < 2^20).
+FastDiv wide_div(uint32_t d) {
+  uint32_t l = 0;
+  while ((1ull << l) < d) ++l;
+  return {d, (uint32_t)((((1ull << l) - d) << 32) / d + 1), l};
+}
+
+// Tiles of the two-radix kernel: one butterfly per thread in the pass with more of them
+// (256 / r0 lines), at least 8 adjacent strided lines (64-byte runs per load), and fewer lines
+// where that leaves less than about 1024 workgroups, down to one wave per workgroup.
+hipError_t tr_prepare(FftAxisArgs a, int smp, int r0, int r1, FftLaunch& out) {
+  const bool contiguous = a.inner == 1;
+  a.tr_outer = a.outer;
+  a.tr_inner = a.inner;
+  if (smp && a.win == WIN_PAD) a.tr_outer = a.outer / a.outer_per_coil * a.wn0;
+  if (a.crop_out) a.tr_inner = a.wn1;
+  int T = 1, lshift = 0;
+  const int nb = r0 > r1 ? r0 : r1;
+  while (2 * T * nb <= TR_NT) T *= 2;
+  if (!contiguous && T < 8) T = 8;
+  const int Tmin = contiguous ? 1 : 8;
+  auto blocks = [&](int64_t t) {
+    return contiguous ? (a.tr_outer + t - 1) / t : a.tr_outer * ((a.tr_inner + t - 1) / t);
+  };
+  while (T > Tmin && T * nb > 64 && blocks(T) < 1024) T /= 2;
+  while ((1 << lshift) < T) ++lshift;
+  a.lines = T;
+  a.tr_lshift = lshift;
+  a.tr_r0 = fast_div((uint32_t)r0);
+  a.tr_r1 = fast_div((uint32_t)r1);
+  a.tr_chunks = wide_div((uint32_t)((a.tr_inner + T - 1) / T));
+  a.tr_coil = wide_div((uint32_t)(a.win == WIN_PAD ? a.wn0 : a.outer_per_coil));
+  int threads = (T * nb + 63) / 64 * 64;
+  if (threads > TR_NT) threads = TR_NT;
+  out.a = a;
+  out.tr = true;
+  out.smp = smp;
+  out.big = nb > 16;
+  out.twl = false;
+  // the kernel variants of TR_VARIANTS; the fused reads and writes fix the direction
+  static const int var[8] = {0, 2, 3, -1, 4, 5, 6, 7};
+  out.variant = smp == 0 && a.dir > 0 ? 1 : var[smp];
+  out.threads = threads;
+  out.blocks = blocks(T);
+  out.lds = (size_t)((contiguous ? T * r0 * (r1 | 1) : T * r0 * r1) + a.n) * sizeof(float2);
+  return hipSuccess;
+}
+
+}  // namespace
+
 // Lines per workgroup: enough workgroups to spread a small transform over the whole
 // chip (about 1024), at most 64 lines or TILE elements per tile (small tiles keep
 // several workgroups resident per CU), and for strided lines at least 8 adjacent ones
-// (64-byte runs per load) where the tile allows.
+// (64-byte runs per load) where the tile allows.  Sizes that split into two radices (nearly
+// all up to 1024) take the two-radix kernel instead.
 hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
   FftAxisArgs a = args;
   const int n = (int)a.n;
@@ -317,6 +389,14 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
     if (a.crop_out && (contiguous || !a.iphi || a.outer_per_coil != 1)) return hipErrorInvalidValue;
     smp = a.crop_out ? 5 : a.win == WIN_PAD ? 4 : a.win == WIN_ROWS_IN ? 6 : 7;
   }
+  out.tr = false;
+  if (smp <= 2 || (a.win || a.crop_out)) {
+    int r0, r1;
+    const bool inv = smp == 1 || smp == 5 || smp == 7;  // the direction that the pass belongs to
+    if ((!a.premul || contiguous) && (smp == 0 || (a.dir > 0) == inv) && a.outer * a.inner <= 0x7fffffffLL &&
+        tr_radices(n, r0, r1))
+      return tr_prepare(a, smp, r0, r1, out);
+  }
   // the reading pass places whole lines' samples directly when every tile holds lines of
   // one coil only
   if (smp == 1 && contiguous && a.in_mask && a.in_lptr && a.outer_per_coil % T == 0) smp = 3;
@@ -334,6 +414,8 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
   }
   out.a = a;
   out.smp = smp;
+  out.big = false;
+  out.threads = NT;
   out.twl = twl;
   out.blocks = blocks;
   out.lds = lds;
@@ -356,6 +438,7 @@ hipError_t fft_axis_launch(const FftAxisArgs& args, hipStream_t st) {
     g_fft_collect->push_back(l);
     return hipSuccess;
   }
+  if (l.tr) return l.big ? fft_tr32_launch(l, st) : fft_tr16_launch(l, st);
   const dim3 gr((unsigned)l.blocks), bl(NT);
   const FftAxisArgs& a = l.a;
   switch (l.smp * 2 + (l.twl ? 1 : 0)) {
@@ -381,6 +464,32 @@ hipError_t fft_axis_launch(const FftAxisArgs& args, hipStream_t st) {
 
 // Prepared passes of several slices, grouped by kernel variant, FFT_MULTI per launch.
 hipError_t fft_multi_launch(const std::vector<FftLaunch>& ls, hipStream_t st) {
+  // groups of the two-radix kernel: one variant and workgroup size each
+  std::vector<const FftLaunch*> tr;
+  for (const FftLaunch& l : ls)
+    if (l.tr && l.blocks > 0) tr.push_back(&l);
+  while (!tr.empty()) {
+    const FftLaunch& k = *tr[0];
+    FftMulti m;
+    std::memset(&m, 0, sizeof(m));
+    size_t lds = 0;
+    std::vector<const FftLaunch*> rest;
+    for (const FftLaunch* l : tr) {
+      if (l->variant != k.variant || l->big != k.big || l->threads != k.threads || m.n == FFT_MULTI ||
+          (int64_t)m.start[m.n] + l->blocks > 0x7fffffff) {
+        rest.push_back(l);
+        continue;
+      }
+      m.d[m.n] = l->a;
+      m.start[m.n + 1] = m.start[m.n] + (int)l->blocks;
+      ++m.n;
+      if (l->lds > lds) lds = l->lds;
+    }
+    const hipError_t e = k.big ? fft_tr32_multi(k.variant, k.threads, lds, m, st)
+                               : fft_tr16_multi(k.variant, k.threads, lds, m, st);
+    if (e != hipSuccess) return e;
+    tr.swap(rest);
+  }
   for (int variant = 0; variant < 16; ++variant) {
     FftMulti m;
     std::memset(&m, 0, sizeof(m));
@@ -412,7 +521,7 @@ hipError_t fft_multi_launch(const std::vector<FftLaunch>& ls, hipStream_t st) {
       return e;
     };
     for (const FftLaunch& l : ls) {
-      if (l.smp * 2 + (l.twl ? 1 : 0) != variant || l.blocks <= 0) continue;
+      if (l.tr || l.smp * 2 + (l.twl ? 1 : 0) != variant || l.blocks <= 0) continue;
       if (m.n == FFT_MULTI || (int64_t)m.start[m.n] + l.blocks > 0x7fffffff) {
         hipError_t e = flush();
         if (e != hipSuccess) return e;

@@ -128,9 +128,6 @@ __device__ __forceinline__ void dft_small<5>(float2 (&v)[5], int dir) {
 // m = floor(2^32 (2^l - d) / d) + 1, x / d = (umulhi(x, m) + x) >> l.  The quotient
 // for m is taken in FP64, exact here: the numerator is below 2^53 and a fractional
 // part, at least 1/d, stays clear of the rounding error.
-struct FastDiv {
-  uint32_t d, m, l;
-};
 __host__ __device__ inline FastDiv fast_div(uint32_t d) {
   const uint32_t l = d > 1 ? 32u - (uint32_t)__builtin_clz(d - 1) : 0u;
   const double q = 4294967296.0 * (double)((1ull << l) - d) / (double)d;

@@ -1,0 +1,448 @@
+// Two-radix form of the batched centred DFT along one axis (the operator F of fft.hip, whose
+// data layout, fused sampling and gridding window it shares): the kernel and its launches,
+// instantiated for radices up to 16 (fft_tr16.hip) and up to 32 (fft_tr32.hip).
+#pragma once
+
+#include <cstring>
+
+#include "fft_device.h"
+
+namespace mx {
+
+namespace {
+
+// ---------------------------------------------------------------- two-radix transforms
+// n = R0 R1 with both radices compile-time cases (2 .. 32): a thread loads the R0 inputs of a
+// butterfly straight from memory into registers, transforms them, exchanges them with the
+// other threads of its line through LDS once, transforms R1 of them and stores the outputs
+// straight to memory.  An element crosses LDS once (a store and a load) and the workgroup
+// meets one barrier, where the pass-by-pass form below crosses it once per radix and once
+// more on the way in and out, with two barriers per radix.
+//
+// The chessboard signs of the centred transform are index shifts here: the plain DFT of the
+// input taken from index i + n/2 (mod n), written to index k + n/2 (mod n), so they cost
+// nothing (for an even radix the shift permutes a thread's own registers).
+//
+// Index maps: pass 0 butterfly j < R1 holds inputs i = j + r R1; its output r goes to LDS
+// at (r, j); pass 1 butterfly j' < R0 reads (j', r') for r' < R1, multiplies by
+// exp(-+2 pi i j' r' / n) and gives outputs k = j' + r' R0.  The LDS pitch along r is odd for
+// contiguous lines (a quarter wave writes 16 consecutive j and reads 16 consecutive j', both
+// conflict-free) and the tile's lines are innermost for strided ones.
+//
+// What bounds a pass: its bytes (16 B an element).  A 256 x 256 pass of 32 coils (33.5 MB, in
+// the last-level cache) takes 9.2-10.8 us against 16-19 us pass by pass, one of 512 x 512 and
+// 128 coils (537 MB) 115-133 against 148-192 us (4.0-4.7 TB/s; a copy reaches 5.0), the three
+// of 120 x 100 x 90 and 8 coils (138 MB each) 19-34 against 49-67 us, a gridding pass at
+// 512 x 512 and 16 coils 11-16 against 19-27 us.
+constexpr int TR_NT = 256;
+
+constexpr double tr_cos(double x) {  // Taylor series about 0 for |x| <= pi
+  double t = 1.0, s = 1.0;
+  for (int k = 1; k < 20; ++k) {
+    t *= -x * x / ((2.0 * k - 1.0) * (2.0 * k));
+    s += t;
+  }
+  return s;
+}
+constexpr double tr_sin(double x) {
+  double t = x, s = x;
+  for (int k = 1; k < 20; ++k) {
+    t *= -x * x / ((2.0 * k) * (2.0 * k + 1.0));
+    s += t;
+  }
+  return s;
+}
+template <int N>
+struct TrTab {  // cos and sin of 2 pi m / N
+  float c[N], s[N];
+  constexpr TrTab() : c(), s() {
+    for (int m = 0; m < N; ++m) {
+      const int q = 2 * m > N ? m - N : m;
+      const double x = 6.283185307179586476925286766559 * q / N;
+      c[m] = (float)tr_cos(x);
+      s[m] = (float)tr_sin(x);
+    }
+  }
+};
+
+template <int R, int DIR>
+__device__ __forceinline__ void tr_dft(float2 (&v)[R]);
+
+// R = A B: input index B a + b, DFTs over a, the products w_R^(b k1), DFTs over b; output
+// k1 + A k2.
+template <int A, int B, int DIR>
+__device__ __forceinline__ void tr_comp(float2 (&v)[A * B]) {
+  constexpr int R = A * B;
+  constexpr TrTab<R> tab;
+  float2 t[B][A];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+#pragma unroll
+    for (int q = 0; q < A; ++q) t[b][q] = v[B * q + b];
+    tr_dft<A, DIR>(t[b]);
+#pragma unroll
+    for (int k = 1; k < A; ++k) {
+      const int m = b * k;
+      if (m == 0) continue;
+      if (4 * m == R) t[b][k] = mul_mi(t[b][k], DIR);
+      else if (2 * m == R) t[b][k] = make_float2(-t[b][k].x, -t[b][k].y);
+      else if (4 * m == 3 * R) t[b][k] = mul_mi(t[b][k], -DIR);
+      else t[b][k] = cmul(t[b][k], make_float2(tab.c[m], DIR < 0 ? -tab.s[m] : tab.s[m]));
+    }
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < A; ++k1) {
+    float2 u[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) u[b] = t[b][k1];
+    tr_dft<B, DIR>(u);
+#pragma unroll
+    for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = u[k2];
+  }
+}
+
+template <int R, int DIR>
+__device__ __forceinline__ void tr_dft(float2 (&v)[R]) {
+  if constexpr (R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 16) dft_small<R>(v, DIR);
+  else if constexpr (R == 6) tr_comp<2, 3, DIR>(v);
+  else if constexpr (R == 9) tr_comp<3, 3, DIR>(v);
+  else if constexpr (R == 10) tr_comp<2, 5, DIR>(v);
+  else if constexpr (R == 12) tr_comp<4, 3, DIR>(v);
+  else if constexpr (R == 15) tr_comp<3, 5, DIR>(v);
+  else if constexpr (R == 18) tr_comp<2, 9, DIR>(v);
+  else if constexpr (R == 20) tr_comp<4, 5, DIR>(v);
+  else if constexpr (R == 24) tr_comp<8, 3, DIR>(v);
+  else if constexpr (R == 25) tr_comp<5, 5, DIR>(v);
+  else if constexpr (R == 27) tr_comp<3, 9, DIR>(v);
+  else if constexpr (R == 30) tr_comp<2, 15, DIR>(v);
+  else {
+    static_assert(R == 32, "radix");
+    tr_comp<4, 8, DIR>(v);
+  }
+}
+
+// Where one line of a tile comes from and goes to.  SMP as in fft_axis_body, with the
+// gridding window's passes visiting only the lines that carry work: the pad pass (4) takes
+// its lines from the J wn0 window rows, the crop pass (5) from the wn1 window columns.
+template <int SMP>
+struct TrLine {
+  const FftAxisArgs& a;
+  bool valid;
+  int64_t in, out;    // element offsets of index 0 of the line
+  int64_t pm;         // premultiply offset (0, 4), index within a coil (1, 2)
+  int64_t smp;        // sample offset of the coil (1, 2)
+  int64_t st;         // stride of the line's index
+  float w0;           // 1 / Phi of the line's own axis (4, 5)
+
+  __device__ __forceinline__ TrLine(const FftAxisArgs& args, uint32_t o0, uint32_t t0, int l) : a(args) {
+    st = a.inner;
+    uint32_t o = o0, t = 0;
+    if (a.inner == 1) {
+      o = o0 + l;
+      valid = o < a.tr_outer;
+      if (!valid) o = o0;
+    } else {
+      t = t0 + l;
+      valid = t < a.tr_inner;
+      if (!valid) t = t0;
+    }
+    pm = smp = 0;
+    w0 = 1.f;
+    if constexpr (SMP == 4) {
+      const uint32_t j = fdiv(o, a.tr_coil), r0 = o - j * (uint32_t)a.wn0;
+      pm = (int64_t)r0 * a.wn1 - a.woff1;
+      in = (int64_t)o * a.wn1 - a.woff1;
+      out = (j * a.outer_per_coil + a.woff0 + r0) * a.n;
+      w0 = a.iphi[r0];
+    } else if constexpr (SMP == 5) {
+      in = o * a.n * a.inner + a.woff1 + t;
+      out = ((int64_t)o * a.wn0 - a.woff0) * a.wn1 + t;
+      w0 = a.iphi[a.wn0 + t];
+    } else {
+      in = out = o * a.n * a.inner + t;
+      if (SMP == 0 && a.premul) pm = (o - fdiv(o, a.tr_coil) * a.tr_coil.d) * a.n;
+      if constexpr (SMP == 1 || SMP == 2) {
+        const int64_t j = fdiv(o, a.tr_coil);
+        pm = in - j * a.coil_elems;
+        smp = j * a.nsamples;
+      }
+    }
+  }
+
+  // v[r] = input of the centred index idx(r), off(r) = idx(r) times the line's index stride
+  template <int R, class Idx, class Off>
+  __device__ __forceinline__ void load(float2 (&v)[R], Idx idx, Off off) const {
+    if constexpr (SMP == 1) {
+      int m[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) m[r] = a.in_inv[pm + off(r)];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        v[r] = a.in_samples[smp + max(m[r], 0)];
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (m[r] < 0) v[r] = make_float2(0.f, 0.f);
+    } else if constexpr (SMP == 4) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = a.src[in + min(max(idx(r), a.woff1), a.woff1 + a.wn1 - 1)];  // clamped
+#pragma unroll
+      for (int q = 0; q < R; q += 8) {  // eight image values at a time: fewer registers held
+        float2 x[8];
+        float w[8];
+#pragma unroll
+        for (int r = q; r < R && r < q + 8; ++r) {
+          const int i = min(max(idx(r), a.woff1), a.woff1 + a.wn1 - 1);
+          x[r - q] = a.premul[pm + i];
+          w[r - q] = a.iphi[a.wn0 - a.woff1 + i];
+        }
+#pragma unroll
+        for (int r = q; r < R && r < q + 8; ++r) {
+          const bool ok = idx(r) >= a.woff1 && idx(r) < a.woff1 + a.wn1;
+          v[r] = ok ? cscale(cmul(v[r], x[r - q]), w0 * w[r - q]) : make_float2(0.f, 0.f);
+        }
+      }
+    } else if constexpr (SMP == 6) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = idx(r);
+        const bool ok = i >= a.woff0 && i < a.woff0 + a.wn0;
+        v[r] = a.src[ok ? in + off(r) : in + (int64_t)a.woff0 * st];
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = idx(r);
+        if (i < a.woff0 || i >= a.woff0 + a.wn0) v[r] = make_float2(0.f, 0.f);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = a.src[in + off(r)];
+      if (SMP == 0 && a.premul) {
+        float2 x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = a.premul[pm + off(r)];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = cmul(v[r], x[r]);
+      }
+    }
+  }
+
+  template <int R, class Idx, class Off>
+  __device__ __forceinline__ void store(const float2 (&v)[R], float scale, Idx idx, Off off) const {
+    if (!valid) return;
+    if constexpr (SMP == 2) {
+#pragma unroll
+      for (int q = 0; q < R; q += 8) {
+        int m[8];
+#pragma unroll
+        for (int r = q; r < R && r < q + 8; ++r) m[r - q] = a.out_inv[pm + off(r)];
+#pragma unroll
+        for (int r = q; r < R && r < q + 8; ++r)
+          if (m[r - q] >= 0) a.out_samples[smp + m[r - q]] = cscale(v[r], scale);
+      }
+    } else if constexpr (SMP == 5) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int k = idx(r);
+        if (k >= a.woff0 && k < a.woff0 + a.wn0)
+          a.crop_out[out + (int64_t)k * a.wn1] = cscale(v[r], scale * a.iphi[k - a.woff0] * w0);
+      }
+    } else if constexpr (SMP == 7) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int k = idx(r);
+        if (k >= a.woff1 && k < a.woff1 + a.wn1) a.data[out + k] = cscale(v[r], scale);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) a.data[out + off(r)] = cscale(v[r], scale);
+    }
+  }
+};
+
+// Butterfly bf of a pass with nb butterflies per line -> (line, butterfly): consecutive
+// threads take consecutive butterflies of a contiguous line, consecutive lines otherwise.
+__device__ __forceinline__ void tr_coords(const FftAxisArgs& a, int bf, const FastDiv& fnb, int& l, int& j) {
+  if (a.inner == 1) {
+    l = (int)fdiv(bf, fnb);
+    j = bf - l * (int)fnb.d;
+  } else {
+    l = bf & (a.lines - 1);
+    j = bf >> a.tr_lshift;
+  }
+}
+
+struct TrLds {
+  int LL, RP, JP;  // strides of line, pass-0 output digit and butterfly
+};
+
+template <int SMP, int DIR, int R>
+__device__ __forceinline__ void tr_pass0(const FftAxisArgs& a, float2* lds, const TrLds& s, uint32_t o0, uint32_t t0) {
+  const int nb = a.tr_r1.d, n = (int)a.n, total = nb << a.tr_lshift;
+  for (int bf = threadIdx.x; bf < total; bf += blockDim.x) {
+    int l, j;
+    tr_coords(a, bf, a.tr_r1, l, j);
+    const TrLine<SMP> line(a, o0, t0, l);
+    float2 v[R];
+    const int64_t b0 = j * line.st, step = nb * line.st;
+    if constexpr (R % 2 == 0) {
+      line.load(v, [&](int r) -> int { return j + ((r + R / 2) % R) * nb; },
+                [&](int r) -> int64_t { return b0 + ((r + R / 2) % R) * step; });
+    } else {
+      auto idx = [&](int r) -> int {
+        const int i = j + r * nb + n / 2;
+        return i >= n ? i - n : i;
+      };
+      line.load(v, idx, [&](int r) -> int64_t { return (int64_t)idx(r) * line.st; });
+    }
+    tr_dft<R, DIR>(v);
+    float2* d = lds + l * s.LL + j * s.JP;
+#pragma unroll
+    for (int r = 0; r < R; ++r) d[r * s.RP] = v[r];
+  }
+}
+
+template <int DIR, int R>
+__device__ __forceinline__ void tr_twiddle(float2 (&v)[R], const float2* tw, int j) {
+  // w^(j r) from the table entries for r = 1, 2, 3 and the multiples of 4: at most one product
+  float2 lo[4], hi[(R + 3) / 4];
+#pragma unroll
+  for (int b = 1; b < 4; ++b)
+    if (b < R) {
+      lo[b] = tw[j * b];
+      if (DIR > 0) lo[b].y = -lo[b].y;
+    }
+#pragma unroll
+  for (int q = 1; q < (R + 3) / 4; ++q) {
+    hi[q] = tw[j * 4 * q];
+    if (DIR > 0) hi[q].y = -hi[q].y;
+  }
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    const float2 w = r < 4 ? lo[r] : (r % 4 == 0 ? hi[r / 4] : cmul(hi[r / 4], lo[r % 4]));
+    v[r] = cmul(v[r], w);
+  }
+}
+
+template <int SMP, int DIR, int R>
+__device__ __forceinline__ void tr_pass1(const FftAxisArgs& a, const float2* lds, const float2* tw, const TrLds& s,
+                                         uint32_t o0, uint32_t t0, float scale) {
+  const int nb = a.tr_r0.d, n = (int)a.n, total = nb << a.tr_lshift;
+  for (int bf = threadIdx.x; bf < total; bf += blockDim.x) {
+    int l, j;
+    tr_coords(a, bf, a.tr_r0, l, j);
+    const float2* d = lds + l * s.LL + j * s.RP;
+    float2 v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = d[r * s.JP];
+    tr_twiddle<DIR, R>(v, tw, j);
+    tr_dft<R, DIR>(v);
+    const TrLine<SMP> line(a, o0, t0, l);
+    const int64_t b0 = j * line.st, step = nb * line.st;
+    if constexpr (R % 2 == 0) {
+      line.store(v, scale, [&](int r) -> int { return j + ((r + R / 2) % R) * nb; },
+                 [&](int r) -> int64_t { return b0 + ((r + R / 2) % R) * step; });
+    } else {
+      auto idx = [&](int r) -> int {
+        const int k = j + r * nb + n / 2;
+        return k >= n ? k - n : k;
+      };
+      line.store(v, scale, idx, [&](int r) -> int64_t { return (int64_t)idx(r) * line.st; });
+    }
+  }
+}
+
+#define TR_SMALL(F) F(2) F(3) F(4) F(5) F(6) F(8) F(9) F(10) F(12) F(15) F(16)
+#define TR_LARGE(F) F(18) F(20) F(24) F(25) F(27) F(30) F(32)
+
+// BIG: radices up to 32 (about twice the registers), else up to 16.
+template <int SMP, int DIR, bool BIG>
+__device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_in, uint32_t nbl) {
+  extern __shared__ float2 lds[];
+  const int n = (int)a.n, T = a.lines;
+  const bool contig = a.inner == 1;
+  float2* tw = lds + (contig ? T * (int)a.tr_r0.d * ((int)a.tr_r1.d | 1) : T * n);
+  for (int i = threadIdx.x; i < n; i += blockDim.x) tw[i] = a.twiddle[i];
+  uint32_t o0, t0 = 0;
+  TrLds s;
+  if (contig) {
+    o0 = bid_in << a.tr_lshift;
+    s.JP = 1;
+    s.RP = (int)a.tr_r1.d | 1;
+    s.LL = (int)a.tr_r0.d * s.RP;
+  } else {
+    // consecutive chunks (adjacent columns, which share cache lines) go to one XCD: the
+    // hardware deals workgroups round-robin over the 8 XCDs, each with its own L2
+    uint32_t bid = bid_in;
+    if ((nbl & 7) == 0) bid = (bid_in & 7) * (nbl >> 3) + (bid_in >> 3);
+    o0 = fdiv(bid, a.tr_chunks);
+    t0 = (bid - o0 * a.tr_chunks.d) << a.tr_lshift;
+    s.LL = 1;
+    s.JP = T;
+    s.RP = (int)a.tr_r1.d * T;
+  }
+#define TR_P0(R) case R: tr_pass0<SMP, DIR, R>(a, lds, s, o0, t0); break;
+  if constexpr (BIG) {
+    switch (a.tr_r0.d) { TR_SMALL(TR_P0) TR_LARGE(TR_P0) default: break; }
+  } else {
+    switch (a.tr_r0.d) { TR_SMALL(TR_P0) default: break; }
+  }
+#undef TR_P0
+  __syncthreads();
+  const float scale = rsqrtf((float)n);
+#define TR_P1(R) case R: tr_pass1<SMP, DIR, R>(a, lds, tw, s, o0, t0, scale); break;
+  if constexpr (BIG) {
+    switch (a.tr_r1.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
+  } else {
+    switch (a.tr_r1.d) { TR_SMALL(TR_P1) default: break; }
+  }
+#undef TR_P1
+}
+
+template <int SMP, int DIR, bool BIG>
+__global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 ? 1 : 0)) void fft_tr_kernel(FftAxisArgs a) {
+  fft_tr_body<SMP, DIR, BIG>(a, blockIdx.x, gridDim.x);
+}
+
+// Several passes (of different slices) in one launch, as fft_axis_multi_kernel below.
+template <int SMP, int DIR, bool BIG>
+__global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 ? 1 : 0)) void fft_tr_multi_kernel(FftMulti m) {
+  int i = 0;
+  while (i + 1 < m.n && (int)blockIdx.x >= m.start[i + 1]) ++i;
+  const FftAxisArgs a = m.d[i];
+  fft_tr_body<SMP, DIR, BIG>(a, blockIdx.x - m.start[i], m.start[i + 1] - m.start[i]);
+}
+
+}  // namespace
+
+// kernel variants: what the pass reads and writes (its direction follows, except for plain
+// passes)
+#define TR_VARIANTS(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1)
+
+template <bool BIG>
+hipError_t tr_launch_one(const FftLaunch& l, hipStream_t st) {
+  const dim3 gr((unsigned)l.blocks), bl((unsigned)l.threads);
+  switch (l.variant) {
+#define TR_LAUNCH(I, SMP, DIR) \
+  case I: hipLaunchKernelGGL((fft_tr_kernel<SMP, DIR, BIG>), gr, bl, l.lds, st, l.a); break;
+    TR_VARIANTS(TR_LAUNCH)
+#undef TR_LAUNCH
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <bool BIG>
+hipError_t tr_launch_many(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st) {
+  const dim3 gr((unsigned)m.start[m.n]), bl((unsigned)threads);
+  switch (variant) {
+#define TR_LAUNCH(I, SMP, DIR) \
+  case I: hipLaunchKernelGGL((fft_tr_multi_kernel<SMP, DIR, BIG>), gr, bl, lds, st, m); break;
+    TR_VARIANTS(TR_LAUNCH)
+#undef TR_LAUNCH
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace mx
