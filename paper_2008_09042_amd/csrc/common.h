@@ -83,6 +83,9 @@ struct FftAxisArgs {
   // one coil places its samples directly (no inverse-mask lookup per point)
   const int32_t* in_mask; const int32_t* in_lptr;
   const int32_t* out_inv; float2* out_samples;
+  // masked round trip (dir = -1): the forward transform, the points with in_inv < 0 set to
+  // zero, and the inverse, in one pass; sizes of the two-radix kernel only (fft_tr_supported)
+  int round_trip;
   int64_t coil_elems, nsamples;  // N, M
   uint32_t coil_magic, coil_shift;  // multiply-high division by N (set by fft_axis_launch)
   int lines;              // lines per workgroup (set by fft_axis_launch)
@@ -108,6 +111,7 @@ struct FftAxisArgs {
 };
 constexpr int WIN_PAD = 1, WIN_ROWS_IN = 2, WIN_COLS_OUT = 3;
 hipError_t fft_axis_launch(const FftAxisArgs& a, hipStream_t st);
+bool fft_tr_supported(int64_t n);  // n splits into two radices of at most 32
 // A pass prepared for launch (lines per workgroup, magic numbers, kernel variant, grid, LDS).
 struct FftLaunch {
   FftAxisArgs a;

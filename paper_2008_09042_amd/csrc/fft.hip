@@ -339,7 +339,7 @@ hipError_t tr_prepare(FftAxisArgs a, int smp, int r0, int r1, FftLaunch& out) {
   out.big = nb > 16;
   out.twl = false;
   // the kernel variants of TR_VARIANTS; the fused reads and writes fix the direction
-  static const int var[8] = {0, 2, 3, -1, 4, 5, 6, 7};
+  static const int var[9] = {0, 2, 3, -1, 4, 5, 6, 7, 8};
   out.variant = smp == 0 && a.dir > 0 ? 1 : var[smp];
   out.threads = threads;
   out.blocks = blocks(T);
@@ -375,7 +375,7 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
   a.lines = (int)T;
   const int64_t blocks = contiguous ? (a.outer + T - 1) / T : a.outer * ((a.inner + T - 1) / T);
   const size_t lds = (size_t)(tile_elems(n, a.lines, contiguous) + (twl ? n : 0)) * sizeof(float2);
-  int smp = a.in_inv ? 1 : a.out_inv ? 2 : 0;
+  int smp = a.round_trip ? 0 : a.in_inv ? 1 : a.out_inv ? 2 : 0;
   if (a.win || a.crop_out) {
     // the gridding window: pad on the first forward pass (rows), zero rows on the second
     // (columns), window columns out of the first inverse pass (rows), crop on the last (columns)
@@ -390,6 +390,13 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
     smp = a.crop_out ? 5 : a.win == WIN_PAD ? 4 : a.win == WIN_ROWS_IN ? 6 : 7;
   }
   out.tr = false;
+  if (a.round_trip) {
+    int r0, r1;
+    if (!a.in_inv || a.in_samples || a.out_inv || a.premul || a.win || a.crop_out || a.dir > 0 ||
+        a.outer * a.inner > 0x7fffffffLL || !tr_radices(n, r0, r1))
+      return hipErrorInvalidValue;
+    return tr_prepare(a, 8, r0, r1, out);
+  }
   if (smp <= 2 || (a.win || a.crop_out)) {
     int r0, r1;
     const bool inv = smp == 1 || smp == 5 || smp == 7;  // the direction that the pass belongs to
@@ -420,6 +427,11 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
   out.blocks = blocks;
   out.lds = lds;
   return hipSuccess;
+}
+
+bool fft_tr_supported(int64_t n) {
+  int r0, r1;
+  return n <= 1024 && tr_radices((int)n, r0, r1);
 }
 
 void fft_collect(std::vector<FftLaunch>* sink) { g_fft_collect = sink; }

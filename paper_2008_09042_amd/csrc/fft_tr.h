@@ -161,11 +161,25 @@ struct TrLine {
     } else {
       in = out = o * a.n * a.inner + t;
       if (SMP == 0 && a.premul) pm = (o - fdiv(o, a.tr_coil) * a.tr_coil.d) * a.n;
-      if constexpr (SMP == 1 || SMP == 2) {
+      if constexpr (SMP == 1 || SMP == 2 || SMP == 8) {
         const int64_t j = fdiv(o, a.tr_coil);
         pm = in - j * a.coil_elems;
         smp = j * a.nsamples;
       }
+    }
+  }
+
+  // v[r] *= 1 where the point of offset off(r) is sampled, 0 elsewhere (8)
+  template <int R, class Off>
+  __device__ __forceinline__ void mask(float2 (&v)[R], Off off) const {
+#pragma unroll
+    for (int q = 0; q < R; q += 8) {
+      int m[8];
+#pragma unroll
+      for (int r = q; r < R && r < q + 8; ++r) m[r - q] = a.in_inv[pm + off(r)];
+#pragma unroll
+      for (int r = q; r < R && r < q + 8; ++r)
+        if (m[r - q] < 0) v[r] = make_float2(0.f, 0.f);
     }
   }
 
@@ -324,17 +338,51 @@ __device__ __forceinline__ void tr_twiddle(float2 (&v)[R], const float2* tw, int
   }
 }
 
-template <int SMP, int DIR, int R>
-__device__ __forceinline__ void tr_pass1(const FftAxisArgs& a, const float2* lds, const float2* tw, const TrLds& s,
-                                         uint32_t o0, uint32_t t0, float scale) {
+// The middle of a masked round trip (8): pass 1 of the forward transform, the mask, and pass
+// 0 of the inverse, whose inputs j' + r R0 are the outputs that the thread holds.  The outputs
+// go back to the LDS row that the thread read, so no barrier parts the two.
+template <int R>
+__device__ __forceinline__ void tr_mask_pass(const FftAxisArgs& a, float2* lds, const float2* tw, const TrLds& s,
+                                             uint32_t o0, uint32_t t0) {
   const int nb = a.tr_r0.d, n = (int)a.n, total = nb << a.tr_lshift;
   for (int bf = threadIdx.x; bf < total; bf += blockDim.x) {
     int l, j;
     tr_coords(a, bf, a.tr_r0, l, j);
-    const float2* d = lds + l * s.LL + j * s.RP;
+    float2* d = lds + l * s.LL + j * s.RP;
     float2 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = d[r * s.JP];
+    tr_twiddle<-1, R>(v, tw, j);
+    tr_dft<R, -1>(v);
+    const TrLine<8> line(a, o0, t0, l);
+    const int64_t b0 = j * line.st, step = nb * line.st;
+    if constexpr (R % 2 == 0) {
+      line.mask(v, [&](int r) -> int64_t { return b0 + ((r + R / 2) % R) * step; });
+    } else {
+      line.mask(v, [&](int r) -> int64_t {
+        const int k = j + r * nb + n / 2;
+        return (int64_t)(k >= n ? k - n : k) * line.st;
+      });
+    }
+    tr_dft<R, 1>(v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) d[r * s.JP] = v[r];
+  }
+}
+
+// Pass 1 with fnb butterflies of radix R per line; the butterfly's LDS elements are rp apart
+// from the next butterfly's, jp from each other.
+template <int SMP, int DIR, int R>
+__device__ __forceinline__ void tr_pass1(const FftAxisArgs& a, const float2* lds, const float2* tw, const FastDiv& fnb,
+                                         int ll, int rp, int jp, uint32_t o0, uint32_t t0, float scale) {
+  const int nb = fnb.d, n = (int)a.n, total = nb << a.tr_lshift;
+  for (int bf = threadIdx.x; bf < total; bf += blockDim.x) {
+    int l, j;
+    tr_coords(a, bf, fnb, l, j);
+    const float2* d = lds + l * ll + j * rp;
+    float2 v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = d[r * jp];
     tr_twiddle<DIR, R>(v, tw, j);
     tr_dft<R, DIR>(v);
     const TrLine<SMP> line(a, o0, t0, l);
@@ -389,14 +437,34 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
   }
 #undef TR_P0
   __syncthreads();
-  const float scale = rsqrtf((float)n);
-#define TR_P1(R) case R: tr_pass1<SMP, DIR, R>(a, lds, tw, s, o0, t0, scale); break;
-  if constexpr (BIG) {
-    switch (a.tr_r1.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
-  } else {
-    switch (a.tr_r1.d) { TR_SMALL(TR_P1) default: break; }
-  }
+  if constexpr (SMP == 8) {
+#define TR_M(R) case R: tr_mask_pass<R>(a, lds, tw, s, o0, t0); break;
+    if constexpr (BIG) {
+      switch (a.tr_r1.d) { TR_SMALL(TR_M) TR_LARGE(TR_M) default: break; }
+    } else {
+      switch (a.tr_r1.d) { TR_SMALL(TR_M) default: break; }
+    }
+#undef TR_M
+    __syncthreads();
+    // pass 1 of the inverse: r1 butterflies of radix r0, rows and columns of the LDS tile swapped
+    const float scale = 1.f / (float)n;
+#define TR_P1(R) case R: tr_pass1<SMP, 1, R>(a, lds, tw, a.tr_r1, s.LL, s.JP, s.RP, o0, t0, scale); break;
+    if constexpr (BIG) {
+      switch (a.tr_r0.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
+    } else {
+      switch (a.tr_r0.d) { TR_SMALL(TR_P1) default: break; }
+    }
 #undef TR_P1
+  } else {
+    const float scale = rsqrtf((float)n);
+#define TR_P1(R) case R: tr_pass1<SMP, DIR, R>(a, lds, tw, a.tr_r0, s.LL, s.RP, s.JP, o0, t0, scale); break;
+    if constexpr (BIG) {
+      switch (a.tr_r1.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
+    } else {
+      switch (a.tr_r1.d) { TR_SMALL(TR_P1) default: break; }
+    }
+#undef TR_P1
+  }
 }
 
 template <int SMP, int DIR, bool BIG>
@@ -417,7 +485,7 @@ __global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 ? 1 : 0)) void fft
 
 // kernel variants: what the pass reads and writes (its direction follows, except for plain
 // passes)
-#define TR_VARIANTS(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1)
+#define TR_VARIANTS(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1) F(8, 8, -1)
 
 template <bool BIG>
 hipError_t tr_launch_one(const FftLaunch& l, hipStream_t st) {

@@ -205,6 +205,46 @@ hipError_t fft_dims(const Plan& p, const float2* src, float2* dst, int dir, cons
   return hipSuccess;
 }
 
+// F^H P F over the image axes (P keeps the sampled points): the forward passes from the last
+// axis to the second, the first axis there and back in one pass, and the inverse passes back.
+// One pass over memory fewer than the transform to the samples and the transform from them,
+// and no samples in between.
+bool round_trip_supported(const Plan& p) {
+  return p.sampling == MAXWELL_CARTESIAN && p.ndim >= 2 && p.d_inv && p.M > 0 &&
+         (int64_t)p.J * p.N <= 0x7fffffffLL && fft_tr_supported(p.n[0]);
+}
+hipError_t fft_round_trip(const Plan& p, const float2* src, float2* dst, const float2* premul, hipStream_t st) {
+  const int nd = p.ndim;
+  const float2* cur = src;
+  for (int t = 0; t < 2 * nd - 1; ++t) {
+    const int d = t < nd ? nd - 1 - t : t - nd + 1;
+    FftAxisArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.inner = a.outer_per_coil = 1;
+    for (int e = d + 1; e < nd; ++e) a.inner *= p.n[e];
+    for (int e = 0; e < d; ++e) a.outer_per_coil *= p.n[e];
+    a.data = dst;
+    a.src = cur;
+    a.n = p.n[d];
+    a.outer = (int64_t)p.J * a.outer_per_coil;
+    a.dir = t < nd ? -1 : 1;
+    a.twiddle = p.d_tw[d];
+    a.nrad = p.nrad[d];
+    for (int q = 0; q < p.nrad[d]; ++q) a.radix[q] = p.radix[d][q];
+    a.premul = t == 0 ? premul : nullptr;
+    a.coil_elems = p.N;
+    a.nsamples = p.M;
+    if (d == 0) {
+      a.round_trip = 1;
+      a.in_inv = p.d_inv;
+    }
+    hipError_t e = TIMED("fft_axis", fft_axis_launch(a, st));
+    if (e != hipSuccess) return e;
+    cur = dst;
+  }
+  return hipSuccess;
+}
+
 hipError_t fft_image(const Plan& p, const float2* src, float2* dst, int dir, const float2* premul,
                      hipStream_t st) {
   return fft_dims(p, src, dst, dir, premul, p.ndim, p.n, p.d_tw, p.nrad, p.radix, st);
@@ -815,7 +855,7 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
   // FP64 scalars and inner-product partials
   const size_t V = ((size_t)p.N + (size_t)p.J * (size_t)p.K) * 8;
   p.off_U = off; off += al(JM);
-  p.off_cg = off; off += 3 * al(V) + al(CG_SCALARS * sizeof(double)) + al(DOT_BLOCKS * sizeof(double));
+  p.off_cg = off; off += 3 * al(V) + al(CG_SCALARS * sizeof(double)) + al(2 * DOT_BLOCKS * sizeof(double));
   if (!p.fused) {
     // SENSE / ADMM (general path): 5 + 2 ndim image-sized buffers (z0 twice, u0, two
     // temporaries, the TV dual field twice), 5 sample-sized ones (F S p, z_k
@@ -1183,58 +1223,82 @@ hipError_t run_jvp(const Plan& p, const float2* x, const float2* c, const float2
 }
 
 // (ox, oc) = J^H (w (.) J[dx, dc]) + (lam_x dx, lam_c dc)
-hipError_t run_normal(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc,
-                      float lam_x, float lam_c, float2* ox, float2* oc, void* ws, hipStream_t st) {
+// (with part: the partials of <(dx, dc), (ox, oc)>)
+static hipError_t normal_op(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc,
+                            float lam_x, float lam_c, float2* ox, float2* oc, double* part, void* ws, hipStream_t st) {
   float2* u = wsp<float2>(ws, p.off_U);
   hipError_t e = run_jvp(p, x, c, dx, dc, u, ws, st);
   if (e != hipSuccess) return e;
   if (p.d_w && (e = TIMED("weights", weight_rows_launch(u, p.d_w, p.M, p.J, st))) != hipSuccess) return e;
   if ((e = run_adjoint(p, x, c, u, 1.0f, nullptr, ox, oc, ws, st, false, false)) != hipSuccess) return e;
-  if ((e = TIMED("normal_axpy", caxpy_launch(ox, dx, lam_x, p.N, st))) != hipSuccess) return e;
-  return TIMED("normal_axpy", caxpy_launch(oc, dc, lam_c, (int64_t)p.J * p.K, st));
+  return TIMED("normal_axpy", axpy_dot_launch(ox, oc, dx, dc, lam_x, lam_c, p.N, (int64_t)p.J * p.K, part, st));
 }
 
-// iters steps of conjugate gradients from zero on apply(dv) = b for a vector of two blocks
-// (n0 and n1 entries: the caller's x0 / x1, b0 / b1); rr (optional, device, iters + 1
-// doubles) receives <r_k, r_k>.  The work vectors r, d, q ([n0 | n1] each) and the FP64
-// scalars sit in the CG region of the workspace; nothing synchronises with the host.
-// apply(d0, d1, q0, q1) must not touch that region.
-template <class Apply>
-static hipError_t cg_loop(const Plan& p, Apply apply, int64_t n0, int64_t n1, const float2* b0, const float2* b1,
-                          int iters, float2* x0, float2* x1, double* rr, void* ws, hipStream_t st) {
-  const int64_t n = n0 + n1;
+hipError_t run_normal(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc,
+                      float lam_x, float lam_c, float2* ox, float2* oc, void* ws, hipStream_t st) {
+  return normal_op(p, x, c, dx, dc, lam_x, lam_c, ox, oc, nullptr, ws, st);
+}
+
+// The CG region of the workspace: the work vectors r, d, q ([n0 | n1] each), the FP64 scalars
+// and two arrays of partials.
+namespace {
+struct CgWs {
+  float2 *r, *d, *q;
+  double *rho, *part_a, *part_b;  // rho: two scalars, used in turn
+};
+CgWs cg_ws(const Plan& p, void* ws) {
   const size_t V = al(((size_t)p.N + (size_t)p.J * (size_t)p.K) * 8);
   char* base = wsp<char>(ws, p.off_cg);
-  float2* r = reinterpret_cast<float2*>(base);
-  float2* d = reinterpret_cast<float2*>(base + V);
-  float2* q = reinterpret_cast<float2*>(base + 2 * V);
-  double* sc = reinterpret_cast<double*>(base + 3 * V);
-  double *rho = sc, *rho_new = sc + 1, *dq = sc + 2, *alpha = sc + 3, *beta = sc + 4;
-  double* part = reinterpret_cast<double*>(base + 3 * V + al(CG_SCALARS * sizeof(double)));
+  CgWs c;
+  c.r = reinterpret_cast<float2*>(base);
+  c.d = reinterpret_cast<float2*>(base + V);
+  c.q = reinterpret_cast<float2*>(base + 2 * V);
+  c.rho = reinterpret_cast<double*>(base + 3 * V);
+  c.part_a = reinterpret_cast<double*>(base + 3 * V + al(CG_SCALARS * sizeof(double)));
+  c.part_b = c.part_a + DOT_BLOCKS;
+  return c;
+}
+}  // namespace
+
+// iters steps of conjugate gradients from zero on apply(dv) = b for a vector of two blocks
+// (n0 and n1 entries: the caller's x0 / x1); start(part) sets x = 0, r = d = b and the
+// partials of <r, r>; rr (optional, device, iters + 1 doubles) receives <r_k, r_k>.  Nothing
+// synchronises with the host.  apply(d0, d1, q0, q1, part) also leaves the partials of <d, q>
+// and must not touch the CG region otherwise.
+template <class Start, class Apply>
+static hipError_t cg_loop(const Plan& p, Start start, Apply apply, int64_t n0, int64_t n1, int iters, float2* x0,
+                          float2* x1, double* rr, void* ws, hipStream_t st) {
+  const CgWs c = cg_ws(p, ws);
   hipError_t e;
-  if ((e = zero_split_launch(x0, x1, n0, n1, st)) != hipSuccess) return e;
-  if ((e = copy_split_launch(r, r + n0, b0, b1, n0, n1, st)) != hipSuccess) return e;
-  if ((e = copy_split_launch(d, d + n0, b0, b1, n0, n1, st)) != hipSuccess) return e;
-  if ((e = TIMED("cg_dot", dot_launch(r, r, n, part, rho, st))) != hipSuccess) return e;
-  if (rr && (e = copy_scalar_launch(rho, rr, st)) != hipSuccess) return e;
+  if ((e = start(c.part_b)) != hipSuccess) return e;
+  if ((e = TIMED("cg_dot", sum_parts_launch(c.part_b, c.rho, rr, st))) != hipSuccess) return e;
   for (int k = 0; k < iters; ++k) {
-    if ((e = apply(d, d + n0, q, q + n0)) != hipSuccess) return e;
-    if ((e = TIMED("cg_dot", dot_launch(d, q, n, part, dq, st))) != hipSuccess) return e;
-    if ((e = cg_alpha_launch(rho, dq, alpha, st)) != hipSuccess) return e;
-    if ((e = TIMED("cg_update", cg_xr_launch(x0, x1, n0, n1, r, d, q, alpha, st))) != hipSuccess) return e;
-    if ((e = TIMED("cg_dot", dot_launch(r, r, n, part, rho_new, st))) != hipSuccess) return e;
-    if ((e = cg_beta_launch(rho, rho_new, beta, rr ? rr + k + 1 : nullptr, st)) != hipSuccess) return e;
-    if ((e = TIMED("cg_update", cg_d_launch(d, r, n, beta, st))) != hipSuccess) return e;
+    const double* rho = c.rho + (k & 1);
+    if ((e = apply(c.d, c.d + n0, c.q, c.q + n0, c.part_a)) != hipSuccess) return e;
+    if ((e = TIMED("cg_update", cg_xr_launch(x0, x1, n0, n1, c.r, c.d, c.q, rho, c.part_a, c.part_b, st))) != hipSuccess)
+      return e;
+    if (k + 1 < iters) {
+      e = TIMED("cg_update", cg_d_launch(c.d, c.r, n0 + n1, rho, c.part_b, c.rho + ((k + 1) & 1),
+                                         rr ? rr + k + 1 : nullptr, st));
+    } else if (rr) {  // no further step: <r, r> alone
+      e = TIMED("cg_dot", sum_parts_launch(c.part_b, rr + k + 1, nullptr, st));
+    }
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
 hipError_t run_cg(const Plan& p, const float2* x, const float2* c, const float2* bx, const float2* bc, float lam_x,
                   float lam_c, int iters, float2* dx, float2* dc, double* rr, void* ws, hipStream_t st) {
-  auto apply = [&](const float2* d0, const float2* d1, float2* q0, float2* q1) {
-    return run_normal(p, x, c, d0, d1, lam_x, lam_c, q0, q1, ws, st);
+  const int64_t JK = (int64_t)p.J * p.K;
+  auto start = [&](double* part) {
+    const CgWs w = cg_ws(p, ws);
+    return TIMED("cg_update", cg_start_launch(dx, dc, bx, bc, p.N, JK, w.r, w.d, part, st));
   };
-  return cg_loop(p, apply, p.N, (int64_t)p.J * p.K, bx, bc, iters, dx, dc, rr, ws, st);
+  auto apply = [&](const float2* d0, const float2* d1, float2* q0, float2* q1, double* part) {
+    return normal_op(p, x, c, d0, d1, lam_x, lam_c, q0, q1, part, ws, st);
+  };
+  return cg_loop(p, start, apply, p.N, JK, iters, dx, dc, rr, ws, st);
 }
 
 // ---- SENSE with fixed maps and the constrained reconstruction (Sec. II-C)
@@ -1248,19 +1312,32 @@ hipError_t run_sense_adjoint(const Plan& p, const float2* S, const float2* y, fl
 }
 
 // out = x + sum_j conj(S_j) (.) F_s^H F_s (S_j (.) x), the p-update operator of the ADMM
-hipError_t run_sense_normal(const Plan& p, const float2* S, const float2* x, float2* out, void* ws, hipStream_t st) {
-  float2* u = wsp<float2>(ws, p.off_U);
-  hipError_t e = encode_maps(p, S, x, u, ws, st);
+// (with part: the partials of <x, out>)
+static hipError_t sense_normal_op(const Plan& p, const float2* S, const float2* x, float2* out, double* part, void* ws,
+                                  hipStream_t st) {
+  hipError_t e;
+  if (round_trip_supported(p)) {
+    float2* Kb = wsp<float2>(ws, p.off_K);
+    if ((e = fft_round_trip(p, S, Kb, x, st)) != hipSuccess) return e;
+    e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, nullptr, p.N, p.J, 1.0f, nullptr, out, 0, st));
+  } else {
+    float2* u = wsp<float2>(ws, p.off_U);
+    if ((e = encode_maps(p, S, x, u, ws, st)) != hipSuccess) return e;
+    e = adjoint_maps(p, S, nullptr, u, 1.0f, nullptr, out, false, ws, st);
+  }
   if (e != hipSuccess) return e;
-  if ((e = adjoint_maps(p, S, nullptr, u, 1.0f, nullptr, out, false, ws, st)) != hipSuccess) return e;
-  return TIMED("sense_axpy", caxpy_launch(out, x, 1.0f, p.N, st));
+  return TIMED("sense_axpy", axpy_dot_launch(out, nullptr, x, nullptr, 1.0f, 0.f, p.N, 0, part, st));
+}
+
+hipError_t run_sense_normal(const Plan& p, const float2* S, const float2* x, float2* out, void* ws, hipStream_t st) {
+  return sense_normal_op(p, S, x, out, nullptr, ws, st);
 }
 
 namespace {
 struct AdmmWs {
   float2 *z0a, *z0b, *u0, *tN, *tN2, *P, *P2;
   float2 *Fp, *zka, *zkb, *uk, *tM;
-  double *part, *dist, *r2, *s2, *rho, *ufac;
+  double *part, *rho, *ufac;
 };
 AdmmWs admm_ws(const Plan& p, void* ws) {
   AdmmWs a;
@@ -1275,85 +1352,73 @@ AdmmWs admm_ws(const Plan& p, void* ws) {
   float2** mb[] = {&a.Fp, &a.zka, &a.zkb, &a.uk, &a.tM};
   for (auto q : mb) { *q = reinterpret_cast<float2*>(b); b += MB; }
   a.part = reinterpret_cast<double*>(b);
-  a.dist = a.part + (size_t)ball_part_doubles(p.J) - p.J;
   b += al((size_t)ball_part_doubles(p.J) * sizeof(double));
   double* sc = reinterpret_cast<double*>(b);
-  a.r2 = sc; a.s2 = sc + 1; a.rho = sc + 2; a.ufac = sc + 3;
+  a.rho = sc + 2; a.ufac = sc + 3;
   return a;
 }
 }  // namespace
 
 hipError_t run_tv_prox(const Plan& p, const float2* z, float lam, int iters, float2* x, void* ws, hipStream_t st) {
   const AdmmWs a = admm_ws(p, ws);
-  return TIMED("tv_prox", tv_prox_launch(p.ndim, p.n, z, nullptr, lam, iters, a.P, a.P2, x, st));
+  return TIMED("tv_prox", tv_prox_launch(p.ndim, p.n, TvInput{z, nullptr, nullptr, nullptr, lam}, iters, a.P, a.P2, x, st));
 }
 
 hipError_t run_ball_project(const Plan& p, const float2* w, const float2* y, const float* eps, float2* z, void* ws,
                             hipStream_t st) {
   const AdmmWs a = admm_ws(p, ws);
-  return TIMED("ball", ball_project_launch(w, y, eps, p.M, p.J, a.part, a.dist, z, st));
+  return TIMED("ball", ball_project_launch(w, nullptr, nullptr, y, eps, p.M, p.J, a.part, z, nullptr, st));
 }
 
 // The scaled ADMM iteration of Sec. II-C (z_0 prox, z_k ball projections, p-update by CG
 // on I + S^H F^H F S from the current p, dual update, residual-balanced rho).  p starts at
 // the SENSE combination S^H F^H y; z and u at zero.
+//
+// The p-update's residual z_0 - u_0 + S^H F^H (z_k - u_k) - (I + S^H F^H F S) p is formed as
+// z_0 - u_0 - p + S^H F^H (z_k - u_k - F S p): F S p is at hand, so one adjoint serves where
+// an adjoint and a whole normal operator would.  The residual balancing's factor on the duals
+// is applied by whoever reads them next.
 hipError_t run_admm(const Plan& p, const float2* S, const float2* y, const float* eps, float rho0, int iters,
                     int cg_iters, int tv_iters, float2* pimg, double* hist, void* ws, hipStream_t st) {
   AdmmWs a = admm_ws(p, ws);
+  const CgWs cg = cg_ws(p, ws);
   const int64_t N = p.N, JM = (int64_t)p.J * p.M;
-  double* part = wsp<double>(ws, p.off_cg + 3 * al(((size_t)p.N + (size_t)p.J * (size_t)p.K) * 8) +
-                                     al(CG_SCALARS * sizeof(double)));
   hipError_t e;
   if ((e = run_sense_adjoint(p, S, y, pimg, ws, st)) != hipSuccess) return e;
-  if ((e = zero_split_launch(a.z0a, a.u0, N, N, st)) != hipSuccess) return e;
-  if ((e = zero_split_launch(a.zka, a.uk, JM, JM, st)) != hipSuccess) return e;
-  if ((e = set_scalar_launch(a.rho, (double)rho0, st)) != hipSuccess) return e;
+  if ((e = admm_init_launch(a.z0a, a.u0, N, a.zka, a.uk, JM, (double)rho0, a.rho, a.ufac, st)) != hipSuccess) return e;
   if ((e = run_sense_encode(p, S, pimg, a.Fp, ws, st)) != hipSuccess) return e;
   float2 *z0 = a.z0a, *z0p = a.z0b, *zk = a.zka, *zkp = a.zkb;
-  auto sense_op = [&](const float2* d0, const float2*, float2* q0, float2*) {
-    return run_sense_normal(p, S, d0, q0, ws, st);
+  auto start = [&](double* part) {
+    return TIMED("cg_update", admm_start_launch(a.tN, z0, a.u0, a.ufac, pimg, N, a.tN2, cg.r, cg.d, part, st));
+  };
+  auto sense_op = [&](const float2* d0, const float2*, float2* q0, float2*, double* part) {
+    return sense_normal_op(p, S, d0, q0, part, ws, st);
   };
   for (int it = 0; it < iters; ++it) {
     std::swap(z0, z0p);  // z0p, zkp: the previous iterates
     std::swap(zk, zkp);
     // z0 = prox_{TV / rho}(p + u0)
-    if ((e = lincomb_launch(a.tN, pimg, 1.f, a.u0, 1.f, N, st)) != hipSuccess) return e;
-    if ((e = TIMED("tv_prox", tv_prox_launch(p.ndim, p.n, a.tN, a.rho, 0.f, tv_iters, a.P, a.P2, z0, st))) !=
+    if ((e = TIMED("tv_prox", tv_prox_launch(p.ndim, p.n, TvInput{pimg, a.u0, a.ufac, a.rho, 0.f}, tv_iters, a.P, a.P2,
+                                             z0, st))) != hipSuccess)
+      return e;
+    // z_k = ball projection of F S p + u_k; tM = z_k - u_k - F S p
+    if ((e = TIMED("ball", ball_project_launch(a.Fp, a.uk, a.ufac, y, eps, p.M, p.J, a.part, zk, a.tM, st))) !=
         hipSuccess)
       return e;
-    // z_k = ball projection of F S p + u_k
-    if ((e = lincomb_launch(a.tM, a.Fp, 1.f, a.uk, 1.f, JM, st)) != hipSuccess) return e;
-    if ((e = TIMED("ball", ball_project_launch(a.tM, y, eps, p.M, p.J, a.part, a.dist, zk, st))) != hipSuccess)
-      return e;
-    // rhs = z0 - u0 + S^H F^H (z_k - u_k);  res = rhs - (I + S^H F^H F S) p
-    if ((e = lincomb_launch(a.tM, zk, 1.f, a.uk, -1.f, JM, st)) != hipSuccess) return e;
     if ((e = run_sense_adjoint(p, S, a.tM, a.tN, ws, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.tN, z0, 1.f, N, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.tN, a.u0, -1.f, N, st)) != hipSuccess) return e;
-    if ((e = run_sense_normal(p, S, pimg, a.tN2, ws, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.tN, a.tN2, -1.f, N, st)) != hipSuccess) return e;
-    // p += CG(res)
-    if ((e = cg_loop(p, sense_op, N, 0, a.tN, nullptr, cg_iters, a.tN2, nullptr, nullptr, ws, st)) != hipSuccess)
-      return e;
+    // p += CG from zero on the residual
+    if ((e = cg_loop(p, start, sense_op, N, 0, cg_iters, a.tN2, nullptr, nullptr, ws, st)) != hipSuccess) return e;
     if ((e = caxpy_launch(pimg, a.tN2, 1.f, N, st)) != hipSuccess) return e;
     if ((e = run_sense_encode(p, S, pimg, a.Fp, ws, st)) != hipSuccess) return e;
-    // u += A p - z
-    if ((e = caxpy_launch(a.u0, pimg, 1.f, N, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.u0, z0, -1.f, N, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.uk, a.Fp, 1.f, JM, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.uk, zk, -1.f, JM, st)) != hipSuccess) return e;
-    // primal residual ||A p - z||^2 and dual residual ||A^H (z - z_prev)||^2 (before rho)
-    if ((e = lincomb_launch(a.tN, pimg, 1.f, z0, -1.f, N, st)) != hipSuccess) return e;
-    if ((e = lincomb_launch(a.tM, a.Fp, 1.f, zk, -1.f, JM, st)) != hipSuccess) return e;
-    if ((e = dot2_launch(a.tN, a.tM, N, JM, part, a.r2, st)) != hipSuccess) return e;
-    if ((e = lincomb_launch(a.tM, zk, 1.f, zkp, -1.f, JM, st)) != hipSuccess) return e;
+    // u += A p - z; tM = z_k - z_k of the step before; the primal residual's partials
+    if ((e = TIMED("admm_dual", admm_dual_launch(pimg, z0, a.u0, N, a.Fp, zk, zkp, a.uk, a.tM, JM, a.ufac, cg.part_a,
+                                                 st))) != hipSuccess)
+      return e;
+    // dual residual ||A^H (z - z_prev)||^2 (before rho)
     if ((e = run_sense_adjoint(p, S, a.tM, a.tN, ws, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.tN, z0, 1.f, N, st)) != hipSuccess) return e;
-    if ((e = caxpy_launch(a.tN, z0p, -1.f, N, st)) != hipSuccess) return e;
-    if ((e = dot_launch(a.tN, a.tN, N, part, a.s2, st)) != hipSuccess) return e;
-    if ((e = admm_rho_launch(a.r2, a.s2, a.rho, a.ufac, hist ? hist + 3 * it : nullptr, st)) != hipSuccess) return e;
-    if ((e = scale_dev_launch(a.u0, N, a.ufac, st)) != hipSuccess) return e;
-    if ((e = scale_dev_launch(a.uk, JM, a.ufac, st)) != hipSuccess) return e;
+    if ((e = admm_dres_launch(a.tN, z0, z0p, N, cg.part_b, st)) != hipSuccess) return e;
+    if ((e = admm_rho_launch(cg.part_a, cg.part_b, a.rho, a.ufac, hist ? hist + 3 * it : nullptr, st)) != hipSuccess)
+      return e;
   }
   return hipSuccess;
 }

@@ -8,11 +8,15 @@
 // virtual vector of N + J K entries.
 //
 // Inner products Re <a, b> = Re sum conj(a) b are accumulated in FP64: every thread sums its
-// grid-stride entries in order, the workgroup reduces its 256 sums by a fixed tree, and one
-// more workgroup reduces the DOT_BLOCKS partials by the same tree.  No atomics: the result
-// does not depend on timing.  The CG scalars (rho = <r, r>, <d, q>, the step and the
-// direction factor) stay in device memory in FP64 and are read by the update kernels, so a
-// CG solve runs with no host synchronisation and can be captured into a graph.
+// grid-stride entries in order, the workgroup reduces its 256 sums by a fixed tree, and the
+// DOT_BLOCKS partials are reduced by the same tree wherever the sum is read.  No atomics: the
+// result does not depend on timing.  The CG scalars stay in device memory in FP64, so a CG
+// solve runs with no host synchronisation and can be captured into a graph.
+//
+// The vectors of a CG step are short (0.5 MB at 256^2, 4 MB at 96 x 80 x 64) and each kernel
+// over them costs its launch and ramp (2-5 us), so a step takes three of them: the shift of
+// the operator's result with the partials of <d, q>; x, r and the partials of <r, r>; d.
+// Every workgroup of the last two forms the step's scalars itself from the 256 partials.
 #include "solver.h"
 
 namespace mx {
@@ -82,40 +86,66 @@ __device__ __forceinline__ void tree256(double* s) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(NT) void dot_partial_kernel(CSplit a, CSplit b, double* __restrict__ part) {
+// Sum of DOT_BLOCKS partials, the same value in every thread (s: NT doubles of LDS).
+__device__ __forceinline__ double sum_parts(const double* __restrict__ part, double* s) {
+  static_assert(DOT_BLOCKS == NT, "one partial per thread");
+  __syncthreads();
+  s[threadIdx.x] = part[threadIdx.x];
+  tree256(s);
+  return s[0];
+}
+
+// (q0 | q1) += (l0 d0 | l1 d1); with part, the partials of <d, q> for the new q
+template <bool DOT>
+__global__ __launch_bounds__(NT) void axpy_dot_kernel(Split q, CSplit d, float l0, float l1, double* __restrict__ part) {
   __shared__ double s[NT];
-  const int64_t n = a.n0 + a.n1;
+  const int64_t n = q.n0 + q.n1;
   double acc = 0.0;
+#pragma unroll 4
   for (int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) {
-    const float2 u = a.at(e), v = b.at(e);
-    acc += (double)u.x * (double)v.x + (double)u.y * (double)v.y;
+    const float l = e < q.n0 ? l0 : l1;
+    const float2 dv = d.at(e);
+    float2 qv = q.at(e);
+    qv.x += l * dv.x;
+    qv.y += l * dv.y;
+    q.at(e) = qv;
+    if (DOT) acc += (double)dv.x * (double)qv.x + (double)dv.y * (double)qv.y;
+  }
+  if (!DOT) return;
+  s[threadIdx.x] = acc;
+  tree256(s);
+  if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+}
+
+// x = 0, r = d = b and the partials of <r, r>
+__global__ __launch_bounds__(NT) void cg_start_kernel(Split x, CSplit b, float2* __restrict__ r, float2* __restrict__ d,
+                                                      double* __restrict__ part) {
+  __shared__ double s[NT];
+  const int64_t n = x.n0 + x.n1;
+  double acc = 0.0;
+#pragma unroll 4
+  for (int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) {
+    const float2 v = b.at(e);
+    x.at(e) = make_float2(0.f, 0.f);
+    r[e] = v;
+    d[e] = v;
+    acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
   }
   s[threadIdx.x] = acc;
   tree256(s);
   if (threadIdx.x == 0) part[blockIdx.x] = s[0];
 }
 
-__global__ __launch_bounds__(NT) void dot_final_kernel(const double* __restrict__ part, int nparts,
-                                                       double* __restrict__ out) {
+// alpha = rho / <d, q> (0 when <d, q> = 0); x += alpha d, r -= alpha q, partials of <r, r>
+__global__ __launch_bounds__(NT) void cg_xr_kernel(Split x, float2* __restrict__ r, const float2* __restrict__ d,
+                                                   const float2* __restrict__ q, const double* __restrict__ rho,
+                                                   const double* __restrict__ part_dq, double* __restrict__ part_rr) {
   __shared__ double s[NT];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += NT) acc += part[i];
-  s[threadIdx.x] = acc;
-  tree256(s);
-  if (threadIdx.x == 0) *out = s[0];
-}
-
-// alpha = rho / <d, q> (0 when <d, q> = 0)
-__global__ void cg_alpha_kernel(const double* __restrict__ rho, const double* __restrict__ dq,
-                                double* __restrict__ alpha) {
-  if (threadIdx.x == 0) *alpha = *dq != 0.0 ? *rho / *dq : 0.0;
-}
-
-// x += alpha d, r -= alpha q
-__global__ void cg_xr_kernel(Split x, float2* __restrict__ r, const float2* __restrict__ d,
-                             const float2* __restrict__ q, const double* __restrict__ alpha) {
-  const float a = (float)*alpha;
+  const double dq = sum_parts(part_dq, s);
+  const float a = (float)(dq != 0.0 ? *rho / dq : 0.0);
   const int64_t n = x.n0 + x.n1;
+  double acc = 0.0;
+#pragma unroll 4
   for (int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) {
     const float2 dv = d[e], qv = q[e];
     float2& xv = x.at(e);
@@ -125,31 +155,43 @@ __global__ void cg_xr_kernel(Split x, float2* __restrict__ r, const float2* __re
     rv.x -= a * qv.x;
     rv.y -= a * qv.y;
     r[e] = rv;
+    acc += (double)rv.x * (double)rv.x + (double)rv.y * (double)rv.y;
   }
+  __syncthreads();  // s[0] read by all
+  s[threadIdx.x] = acc;
+  tree256(s);
+  if (threadIdx.x == 0) part_rr[blockIdx.x] = s[0];
 }
 
-// beta = rho_new / rho (0 when rho = 0); rho = rho_new; rr = rho_new
-__global__ void cg_beta_kernel(double* __restrict__ rho, const double* __restrict__ rho_new,
-                               double* __restrict__ beta, double* __restrict__ rr) {
-  if (threadIdx.x != 0) return;
-  *beta = *rho != 0.0 ? *rho_new / *rho : 0.0;
-  *rho = *rho_new;
-  if (rr) *rr = *rho_new;
-}
-
-// d = r + beta d
-__global__ void cg_d_kernel(float2* __restrict__ d, const float2* __restrict__ r, int64_t n,
-                            const double* __restrict__ beta) {
-  const float b = (float)*beta;
+// rho_new = <r, r> from its partials, beta = rho_new / rho (0 when rho = 0): d = r + beta d; the
+// first workgroup keeps rho_new in *rho_next (not rho, which the others may still read) and rr
+__global__ __launch_bounds__(NT) void cg_d_kernel(float2* __restrict__ d, const float2* __restrict__ r, int64_t n,
+                                                  const double* __restrict__ rho, const double* __restrict__ part_rr,
+                                                  double* __restrict__ rho_next, double* __restrict__ rr) {
+  __shared__ double s[NT];
+  const double rho_new = sum_parts(part_rr, s);
+  const float b = (float)(*rho != 0.0 ? rho_new / *rho : 0.0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *rho_next = rho_new;
+    if (rr) *rr = rho_new;
+  }
+#pragma unroll 4
   for (int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) {
     const float2 rv = r[e];
-    float2 dv = d[e];
+    const float2 dv = d[e];
     d[e] = make_float2(rv.x + b * dv.x, rv.y + b * dv.y);
   }
 }
 
-__global__ void copy_scalar_kernel(const double* __restrict__ src, double* __restrict__ dst) {
-  if (threadIdx.x == 0) *dst = *src;
+// *out = sum of the partials, and *out2 if given
+__global__ __launch_bounds__(NT) void sum_parts_kernel(const double* __restrict__ part, double* __restrict__ out,
+                                                       double* __restrict__ out2) {
+  __shared__ double s[NT];
+  const double v = sum_parts(part, s);
+  if (threadIdx.x == 0) {
+    *out = v;
+    if (out2) *out2 = v;
+  }
 }
 
 // out[e] = sum_i part[i * stride + e] in index order (plain FP32 adds)
@@ -201,41 +243,39 @@ hipError_t zero_split_launch(float2* d0, float2* d1, int64_t n0, int64_t n1, hip
   return hipGetLastError();
 }
 
-hipError_t dot_launch(const float2* a, const float2* b, int64_t n, double* part, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(dot_partial_kernel, dim3(DOT_BLOCKS), dim3(NT), 0, st, CSplit{a, nullptr, n, 0},
-                     CSplit{b, nullptr, n, 0}, part);
-  hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(NT), 0, st, part, DOT_BLOCKS, out);
+hipError_t axpy_dot_launch(float2* q0, float2* q1, const float2* d0, const float2* d1, float l0, float l1, int64_t n0,
+                           int64_t n1, double* part, hipStream_t st) {
+  const Split q{q0, q1, n0, n1};
+  const CSplit d{d0, d1, n0, n1};
+  if (part)
+    hipLaunchKernelGGL(axpy_dot_kernel<true>, dim3(DOT_BLOCKS), dim3(NT), 0, st, q, d, l0, l1, part);
+  else if (n0 + n1 > 0)
+    hipLaunchKernelGGL(axpy_dot_kernel<false>, dim3(grid_for(n0 + n1)), dim3(NT), 0, st, q, d, l0, l1, part);
   return hipGetLastError();
 }
 
-hipError_t dot2_launch(const float2* a0, const float2* a1, int64_t n0, int64_t n1, double* part, double* out,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(dot_partial_kernel, dim3(DOT_BLOCKS), dim3(NT), 0, st, CSplit{a0, a1, n0, n1},
-                     CSplit{a0, a1, n0, n1}, part);
-  hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(NT), 0, st, part, DOT_BLOCKS, out);
-  return hipGetLastError();
-}
-
-hipError_t cg_alpha_launch(const double* rho, const double* dq, double* alpha, hipStream_t st) {
-  hipLaunchKernelGGL(cg_alpha_kernel, dim3(1), dim3(64), 0, st, rho, dq, alpha);
+hipError_t cg_start_launch(float2* x0, float2* x1, const float2* b0, const float2* b1, int64_t n0, int64_t n1, float2* r,
+                           float2* d, double* part, hipStream_t st) {
+  hipLaunchKernelGGL(cg_start_kernel, dim3(DOT_BLOCKS), dim3(NT), 0, st, Split{x0, x1, n0, n1}, CSplit{b0, b1, n0, n1},
+                     r, d, part);
   return hipGetLastError();
 }
 
 hipError_t cg_xr_launch(float2* x0, float2* x1, int64_t n0, int64_t n1, float2* r, const float2* d, const float2* q,
-                        const double* alpha, hipStream_t st) {
-  if (n0 + n1 <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cg_xr_kernel, dim3(grid_for(n0 + n1)), dim3(NT), 0, st, Split{x0, x1, n0, n1}, r, d, q, alpha);
+                        const double* rho, const double* part_dq, double* part_rr, hipStream_t st) {
+  hipLaunchKernelGGL(cg_xr_kernel, dim3(DOT_BLOCKS), dim3(NT), 0, st, Split{x0, x1, n0, n1}, r, d, q, rho, part_dq,
+                     part_rr);
   return hipGetLastError();
 }
 
-hipError_t cg_beta_launch(double* rho, const double* rho_new, double* beta, double* rr, hipStream_t st) {
-  hipLaunchKernelGGL(cg_beta_kernel, dim3(1), dim3(64), 0, st, rho, rho_new, beta, rr);
+hipError_t cg_d_launch(float2* d, const float2* r, int64_t n, const double* rho, const double* part_rr,
+                       double* rho_next, double* rr, hipStream_t st) {
+  hipLaunchKernelGGL(cg_d_kernel, dim3(grid_for(n, 1024)), dim3(NT), 0, st, d, r, n, rho, part_rr, rho_next, rr);
   return hipGetLastError();
 }
 
-hipError_t cg_d_launch(float2* d, const float2* r, int64_t n, const double* beta, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cg_d_kernel, dim3(grid_for(n)), dim3(NT), 0, st, d, r, n, beta);
+hipError_t sum_parts_launch(const double* part, double* out, double* out2, hipStream_t st) {
+  hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(NT), 0, st, part, out, out2);
   return hipGetLastError();
 }
 
@@ -248,11 +288,6 @@ hipError_t sum_rows_launch(float2* out, const float2* part, int n, int64_t strid
 hipError_t sum_doubles_launch(double* out, const double* part, int n, int64_t stride, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(sum_doubles_kernel, dim3(1), dim3(64), 0, st, out, part, n, stride);
-  return hipGetLastError();
-}
-
-hipError_t copy_scalar_launch(const double* src, double* dst, hipStream_t st) {
-  hipLaunchKernelGGL(copy_scalar_kernel, dim3(1), dim3(64), 0, st, src, dst);
   return hipGetLastError();
 }
 

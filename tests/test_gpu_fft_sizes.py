@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from oracle import Oracle  # noqa: E402
+from oracle.admm import sense_normal  # noqa: E402
 from _common import assert_close  # noqa: E402
 
 DEV = "cuda:0"
@@ -39,6 +40,8 @@ def run(dims, J, rng, **sampling):
     assert_close(e, op.encode(x, c), 1e-5, coils=True)
     assert_close(H(gx).reshape(-1), gx_ref, 1e-5)
     assert_close(H(gc), gc_ref, 1e-5, coils=True)
+    S = cg(J, N)  # the masked round trip along the first axis, or the two transforms
+    assert_close(H(plan.sense_normal(T(S), T(x))).reshape(-1), sense_normal(op, S, x), 1e-5)
 
 
 CART = [(2, 4), (4, 2), (6, 16), (10, 18), (12, 20), (24, 30), (36, 64), (54, 50), (80, 90), (100, 108), (120, 144),
