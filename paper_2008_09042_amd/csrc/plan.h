@@ -60,7 +60,7 @@ struct Plan {
   float2* d_core_f32 = nullptr;      // FP32 core copies in fragment order (FP32 plans only)
   int G_fwd = 2, G_adj = 8;    // coils per plane workgroup (set at plan creation)
   int split_apply = 0, split_adj = 0;  // dense basis GEMMs: split-K factors tuned at plan creation
-  bool skinny_apply = false, skinny_adj = false;  // dense basis: streaming kernels chosen at plan creation
+  bool stream_apply = false, stream_adj = false;  // dense basis: streaming kernels chosen at plan creation
   float gscale = 1.0f;         // prod_d (-1)^(n_d/2) / sqrt(N)
   // non-Cartesian sampling (Kaiser-Bessel NUFFT, 2D)
   int g[2] = {0, 0};             // oversampled grid
@@ -88,7 +88,6 @@ struct Plan {
   size_t off_T1 = 0, off_T3 = 0, off_xt = 0, off_Z = 0, off_gxp = 0, off_T3b = 0, off_T1b = 0, off_G = 0, off_Ys = 0, off_cpart = 0;
   size_t off_U = 0, off_cg = 0;  // Gauss-Newton / CG: JVP result; r, d, q, FP64 scalars
   size_t off_admm = 0;           // SENSE / ADMM state (general path only)
-  size_t off_cfrag = 0;          // dense apply: fragment-ordered coefficients (0: generic GEMM)
   size_t off_adjp = 0;           // dense adjoint: row-chunk partials of the streaming kernel
   int part_blocks = 0;
 

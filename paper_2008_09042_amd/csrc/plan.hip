@@ -717,17 +717,14 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
       return hip_err(e);
   }
 
-  // dense basis: for each of the two basis products, the streaming kernel (few coils) or the
-  // tiled GEMM at one split-K factor, picked by timing the candidates on scratch operands of
+  // dense basis: for each of the two basis products, the streaming kernel or the tiled GEMM at
+  // one split-K factor, picked by timing the candidates on scratch operands of
   // the plan's shapes; the choices persist in the tuning cache (tune.h), keyed by the GPU
-  // architecture and the shape.  MAXWELL_GEMM_AUTOTUNE=0: the rule (streaming apply where
-  // supported, streaming adjoint up to 16 coils, no split) without timing.
+  // architecture and the shape.  MAXWELL_GEMM_AUTOTUNE=0: the streaming kernels without timing.
   if (p.basis_kind == MAXWELL_BASIS_DENSE && !p.fused && p.J > 0 && p.K > 0 && p.N > 0) {
-    const bool stream_ok = skinny_apply_supported(p.N, p.K, p.J) && (reinterpret_cast<uintptr_t>(p.dense) & 15u) == 0;
     const char* env = std::getenv("MAXWELL_GEMM_AUTOTUNE");
     if (env && env[0] == '0') {
-      p.skinny_apply = stream_ok;
-      p.skinny_adj = stream_ok && p.J <= 16;
+      p.stream_apply = p.stream_adj = true;
     } else {
       const size_t nbuf = (size_t)p.J * std::max<int64_t>(p.N, p.K) * 8;  // c, S, h and gc all fit
       const size_t max_ws = (size_t)256 << 20;
@@ -758,30 +755,28 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
         };
         std::ostringstream shape;
         shape << device_arch() << " N=" << p.N << " K=" << p.K << " J=" << p.J << " prec=" << p.precision
-              << " stream=" << (stream_ok ? 1 : 0);
-        const int ca = tuned_choice("dense_apply " + shape.str(), [&]() -> int {
+              << " odd=" << ((reinterpret_cast<uintptr_t>(p.dense) & 15u) != 0 ? 1 : 0);
+        const int ca = tuned_choice("stream_apply " + shape.str(), [&]() -> int {
           float gemm_ms = -1.f;
           const int split = gemm_autotune(dense_apply_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm_ms);
-          if (!stream_ok || skinny_frag_bytes(p.K, p.J) > max_ws) return split;
-          const float sk = time_ms([&]() { return skinny_apply_launch(p.dense, p.N, p.K, A, p.J, p.precision, bufW, C, 0); });
+          const float sk = time_ms([&]() { return stream_apply_launch(p.dense, p.N, p.K, A, p.J, p.precision, C, 0); });
           return (sk > 0.f && (gemm_ms <= 0.f || sk < gemm_ms)) ? -1 : split;
         });
-        const int cd = tuned_choice("dense_adjoint " + shape.str(), [&]() -> int {
+        const int cd = tuned_choice("stream_adjoint " + shape.str(), [&]() -> int {
           float gemm_ms = -1.f;
           const int split = gemm_autotune(dense_adjoint_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm_ms);
-          if (!stream_ok || skinny_adjoint_bytes(p.N, p.K, p.J) > max_ws) return split;
+          if (stream_adjoint_bytes(p.N, p.K, p.J) > max_ws) return split;
           const float sk = time_ms([&]() {
-            return skinny_adjoint_launch(p.dense, p.N, p.K, A, p.J, p.precision, 1.0f, nullptr, bufW, C, 0);
+            return stream_adjoint_launch(p.dense, p.N, p.K, A, nullptr, p.J, p.precision, 1.0f, nullptr, bufW, C, 0);
           });
           return (sk > 0.f && (gemm_ms <= 0.f || sk < gemm_ms)) ? -1 : split;
         });
-        p.skinny_apply = ca < 0;
-        p.skinny_adj = cd < 0;
+        p.stream_apply = ca < 0;
+        p.stream_adj = cd < 0;
         p.split_apply = ca < 0 ? 0 : ca;
         p.split_adj = cd < 0 ? 0 : cd;
       } else {
-        p.skinny_apply = stream_ok;
-        p.skinny_adj = stream_ok && p.J <= 16;
+        p.stream_apply = p.stream_adj = true;
       }
       (void)hipStreamSynchronize(0);
       if (bufA) (void)hipFree(bufA);
@@ -838,13 +833,9 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
     p.off_cpart = off;
     off += al(core_adj_part_bytes(p.cg.R, p.cg.K, p.J));
   }
-  if (p.skinny_apply) {
-    p.off_cfrag = off;
-    off += al(skinny_frag_bytes(p.K, p.J));
-  }
-  if (p.skinny_adj) {
+  if (p.stream_adj) {
     p.off_adjp = off;
-    off += al(skinny_adjoint_bytes(p.N, p.K, p.J));
+    off += al(stream_adjoint_bytes(p.N, p.K, p.J));
   }
   p.off_E = off; off += al(JM);
   p.off_gemm = off; off += al(gemm_ws);
@@ -964,9 +955,8 @@ static hipError_t core_adjoint(const Plan& p, const float2* T1b, float2* gc, flo
 hipError_t run_basis_apply(const Plan& p, const float2* c, float2* S, void* ws, hipStream_t st) {
   void* gws = wsp<void>(ws, p.off_gemm);
   if (p.basis_kind == MAXWELL_BASIS_DENSE) {
-    if (p.off_cfrag)  // streaming kernel for few coils
-      return TIMED("gemm_dense_apply", skinny_apply_launch(p.dense, p.N, p.K, c, p.J, p.precision,
-                                                           wsp<void>(ws, p.off_cfrag), S, st));
+    if (p.stream_apply)
+      return TIMED("gemm_dense_apply", stream_apply_launch(p.dense, p.N, p.K, c, p.J, p.precision, S, st));
     return TIMED("gemm_dense_apply", gemm_launch(dense_apply_args(p, c, S), p.precision, gws, st));
   }
   GemmArgs g[4];
@@ -983,8 +973,8 @@ hipError_t run_basis_apply(const Plan& p, const float2* c, float2* S, void* ws, 
 hipError_t run_basis_adjoint(const Plan& p, const float2* S, float2* c, float alpha, const float* alpha_dev,
                              void* ws, hipStream_t st) {
   void* gws = wsp<void>(ws, p.off_gemm);
-  if (p.basis_kind == MAXWELL_BASIS_DENSE && p.off_adjp)  // streaming kernel for up to 16 coils
-    return TIMED("gemm_dense_adjoint", skinny_adjoint_launch(p.dense, p.N, p.K, S, p.J, p.precision, alpha,
+  if (p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_adj)
+    return TIMED("gemm_dense_adjoint", stream_adjoint_launch(p.dense, p.N, p.K, S, nullptr, p.J, p.precision, alpha,
                                                              alpha_dev, wsp<void>(ws, p.off_adjp), c, st));
   if (p.basis_kind == MAXWELL_BASIS_DENSE) {
     GemmArgs g = dense_adjoint_args(p, S, c);
@@ -1145,6 +1135,31 @@ hipError_t run_forward_loss(const Plan& p, const float2* x, const float2* c, con
   return hipSuccess;
 }
 
+// The K region of the workspace = F_s^H y (general path); alpha and scale_dev are left holding
+// the part of s = alpha * (*scale_dev) that is still to be applied.
+static hipError_t adjoint_transform(const Plan& p, const float2* y, float& alpha, const float*& scale_dev, void* ws,
+                                    hipStream_t st, bool ordered) {
+  float2* Kb = wsp<float2>(ws, p.off_K);
+  hipError_t e;
+  if (p.sampling == MAXWELL_NONCARTESIAN) {
+    const NufftArgs na = nufft_args(p);
+    float2* G = wsp<float2>(ws, p.off_G);
+    const float al0 = alpha;
+    const float* sd = scale_dev;
+    // `ordered`: y is a residual written in the spread's sample order (no staging pass)
+    if ((e = TIMED("nufft_spread", spread_launch(na, y, al0, sd, wsp<float2>(ws, p.off_Ys), G, st, ordered))) !=
+        hipSuccess)
+      return e;
+    alpha = 1.0f;  // the scale was applied by the spread
+    scale_dev = nullptr;
+    return fft_grid_window(p, nullptr, nullptr, G, Kb, +1, st);  // crop in the last pass
+  }
+  if (fuse_sampling(p))  // the first pass reads the samples through the inverse mask
+    return fft_dims(p, Kb, Kb, +1, nullptr, p.ndim, p.n, p.d_tw, p.nrad, p.radix, st, y, nullptr);
+  if ((e = TIMED("scatter", scatter_launch(y, p.M, p.d_inv, p.N, p.J, Kb, st))) != hipSuccess) return e;
+  return fft_image(p, Kb, Kb, +1, nullptr, st);
+}
+
 // gx = s sum_j conj(S_j) (.) F_s^H y_j for coil maps S [J][N] (general path), s = alpha *
 // (*scale_dev); with want_h the K region of the workspace is left holding
 // h_j = s conj(x) (.) F_s^H y_j, the input of the basis adjoint.
@@ -1152,28 +1167,8 @@ static hipError_t adjoint_maps(const Plan& p, const float2* S, const float2* x, 
                                const float* scale_dev, float2* gx, bool want_h, void* ws, hipStream_t st,
                                bool ordered = false) {
   float2* Kb = wsp<float2>(ws, p.off_K);
-  hipError_t e;
-  if (p.sampling == MAXWELL_NONCARTESIAN) {
-    const NufftArgs na = nufft_args(p);
-    float2* G = wsp<float2>(ws, p.off_G);
-    // `ordered`: y is a residual written in the spread's sample order (no staging pass)
-    if ((e = TIMED("nufft_spread", spread_launch(na, y, alpha, scale_dev, wsp<float2>(ws, p.off_Ys), G, st,
-                                                 ordered))) !=
-        hipSuccess)
-      return e;
-    if ((e = fft_grid_window(p, nullptr, nullptr, G, Kb, +1, st)) != hipSuccess) return e;  // crop in the last pass
-    alpha = 1.0f;  // the scale was applied by the spread
-    scale_dev = nullptr;
-  } else {
-    if (fuse_sampling(p)) {  // the first pass reads the samples through the inverse mask
-      if ((e = fft_dims(p, Kb, Kb, +1, nullptr, p.ndim, p.n, p.d_tw, p.nrad, p.radix, st, y, nullptr)) !=
-          hipSuccess)
-        return e;
-    } else {
-      if ((e = TIMED("scatter", scatter_launch(y, p.M, p.d_inv, p.N, p.J, Kb, st))) != hipSuccess) return e;
-      if ((e = fft_image(p, Kb, Kb, +1, nullptr, st)) != hipSuccess) return e;
-    }
-  }
+  hipError_t e = adjoint_transform(p, y, alpha, scale_dev, ws, st, ordered);
+  if (e != hipSuccess) return e;
   return TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, x, p.N, p.J, alpha, scale_dev, gx, want_h ? 1 : 0, st));
 }
 
@@ -1183,12 +1178,33 @@ hipError_t run_adjoint(const Plan& p, const float2* x, const float2* c, const fl
   if (p.fused) return fused_adjoint(p, x, c, y, alpha, scale_dev, gx, gc, ws, st, maps_ready, transfer);
   float2* S = wsp<float2>(ws, p.off_S);
   float2* Kb = wsp<float2>(ws, p.off_K);
+  const bool ordered = transfer && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer;
+  const bool dense = p.basis_kind == MAXWELL_BASIS_DENSE;
+  // dense basis: the streaming products form what they need of g = F_s^H y themselves, the
+  // image gradient from maps that stay in registers (unless this call has them already), the
+  // coefficients' from h = conj(x) (.) g
+  const bool stream_gx = gx && dense && p.stream_apply && !maps_ready;
+  const bool stream_gc = gc && dense && p.stream_adj;
   hipError_t e;
-  if (gx && !maps_ready) {
+  if (gx && !maps_ready && !stream_gx) {
     if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
   }
-  const bool ordered = transfer && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer;
-  if ((e = adjoint_maps(p, S, x, y, alpha, scale_dev, gx, gc != nullptr, ws, st, ordered)) != hipSuccess) return e;
+  if ((e = adjoint_transform(p, y, alpha, scale_dev, ws, st, ordered)) != hipSuccess) return e;
+  if (stream_gx) {
+    e = TIMED("dense_gx", stream_gx_launch(p.dense, p.N, p.K, c, p.J, p.precision, Kb, alpha, scale_dev, gx, st));
+    if (e != hipSuccess) return e;
+  }
+  if (stream_gc) {
+    if (gx && !stream_gx) {
+      e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, x, p.N, p.J, alpha, scale_dev, gx, 0, st));
+      if (e != hipSuccess) return e;
+    }
+    return TIMED("gemm_dense_adjoint", stream_adjoint_launch(p.dense, p.N, p.K, Kb, x, p.J, p.precision, alpha,
+                                                             scale_dev, wsp<void>(ws, p.off_adjp), gc, st));
+  }
+  float2* gxc = stream_gx ? nullptr : gx;
+  e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, x, p.N, p.J, alpha, scale_dev, gxc, gc ? 1 : 0, st));
+  if (e != hipSuccess) return e;
   if (gc) return run_basis_adjoint(p, Kb, gc, 1.0f, nullptr, ws, st);
   return hipSuccess;
 }

@@ -1,22 +1,22 @@
-// Dense basis apply and adjoint for few coils (skinny.hip).
+// Dense basis products as streams of the basis (stream_apply.hip, stream_adjoint.hip).
 #pragma once
 
 #include "common.h"
 
 namespace mx {
 
-// Shapes the streaming kernel takes: K a multiple of 4 (32-byte row runs), 1 <= J <= 64.
-bool skinny_apply_supported(int64_t N, int64_t K, int J);
-// Bytes of the fragment-ordered c operand the call builds.
-size_t skinny_frag_bytes(int64_t K, int J);
-// S [J][N] = B [N][K] c^T for c [J][K]; B 16-byte aligned; frag holds skinny_frag_bytes.
-// c [J][K] = alpha (* alpha_dev) B^H h for h [J][N]; ws holds skinny_adjoint_bytes (the
-// row-chunk partials, summed in a fixed order).  Same shapes as the apply (the plan uses it
-// for J <= 16, where it beats the tiled GEMM).
-size_t skinny_adjoint_bytes(int64_t N, int64_t K, int J);
-hipError_t skinny_adjoint_launch(const float2* B, int64_t N, int64_t K, const float2* h, int J, int precision,
-                                 float alpha, const float* alpha_dev, void* ws, float2* c, hipStream_t st);
-hipError_t skinny_apply_launch(const float2* B, int64_t N, int64_t K, const float2* c, int J, int precision,
-                               void* frag, float2* S, hipStream_t st);
+// S [J][N] = B [N][K] c^T for c [J][K].
+hipError_t stream_apply_launch(const float2* B, int64_t N, int64_t K, const float2* c, int J, int precision, float2* S,
+                               hipStream_t st);
+// gx[n] = s sum_j conj((B c_j)[n]) g[j][n], s = alpha (* alpha_dev): the maps are formed and
+// consumed in registers.
+hipError_t stream_gx_launch(const float2* B, int64_t N, int64_t K, const float2* c, int J, int precision,
+                            const float2* g, float alpha, const float* alpha_dev, float2* gx, hipStream_t st);
+// c [J][K] = s B^H h, with h = conj(x) (.) g formed on the way when x [N] is given and h = g
+// otherwise; ws holds stream_adjoint_bytes (the row chunks' partials, summed in a fixed order).
+size_t stream_adjoint_bytes(int64_t N, int64_t K, int J);
+hipError_t stream_adjoint_launch(const float2* B, int64_t N, int64_t K, const float2* g, const float2* x, int J,
+                                 int precision, float alpha, const float* alpha_dev, void* ws, float2* c,
+                                 hipStream_t st);
 
 }  // namespace mx
