@@ -112,6 +112,7 @@ struct FftAxisArgs {
 constexpr int WIN_PAD = 1, WIN_ROWS_IN = 2, WIN_COLS_OUT = 3;
 hipError_t fft_axis_launch(const FftAxisArgs& a, hipStream_t st);
 bool fft_tr_supported(int64_t n);  // n splits into two radices of at most 32
+bool fft_tr_radices(int64_t n, int& r0, int& r1);  // into which: r0 >= r1
 // A pass prepared for launch (lines per workgroup, magic numbers, kernel variant, grid, LDS).
 struct FftLaunch {
   FftAxisArgs a;

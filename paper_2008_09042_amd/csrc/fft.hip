@@ -429,9 +429,11 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
   return hipSuccess;
 }
 
+bool fft_tr_radices(int64_t n, int& r0, int& r1) { return n <= 1024 && tr_radices((int)n, r0, r1); }
+
 bool fft_tr_supported(int64_t n) {
   int r0, r1;
-  return n <= 1024 && tr_radices((int)n, r0, r1);
+  return fft_tr_radices(n, r0, r1);
 }
 
 void fft_collect(std::vector<FftLaunch>* sink) { g_fft_collect = sink; }

@@ -122,6 +122,119 @@ __device__ __forceinline__ void dft_small<5>(float2 (&v)[5], int dir) {
   v[3] = csub(t2, ru2);
 }
 
+// ---- DFTs of every radix used, in registers: composite ones by the two-factor split with
+// compile-time constants
+constexpr double tr_cos(double x) {  // Taylor series about 0 for |x| <= pi
+  double t = 1.0, s = 1.0;
+  for (int k = 1; k < 20; ++k) {
+    t *= -x * x / ((2.0 * k - 1.0) * (2.0 * k));
+    s += t;
+  }
+  return s;
+}
+constexpr double tr_sin(double x) {
+  double t = x, s = x;
+  for (int k = 1; k < 20; ++k) {
+    t *= -x * x / ((2.0 * k) * (2.0 * k + 1.0));
+    s += t;
+  }
+  return s;
+}
+template <int N>
+struct TrTab {  // cos and sin of 2 pi m / N
+  float c[N], s[N];
+  constexpr TrTab() : c(), s() {
+    for (int m = 0; m < N; ++m) {
+      const int q = 2 * m > N ? m - N : m;
+      const double x = 6.283185307179586476925286766559 * q / N;
+      c[m] = (float)tr_cos(x);
+      s[m] = (float)tr_sin(x);
+    }
+  }
+};
+
+template <int R, int DIR>
+__device__ __forceinline__ void tr_dft(float2 (&v)[R]);
+
+// R = A B: input index B a + b, DFTs over a, the products w_R^(b k1), DFTs over b; output
+// k1 + A k2.
+template <int A, int B, int DIR>
+__device__ __forceinline__ void tr_comp(float2 (&v)[A * B]) {
+  constexpr int R = A * B;
+  constexpr TrTab<R> tab;
+  float2 t[B][A];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+#pragma unroll
+    for (int q = 0; q < A; ++q) t[b][q] = v[B * q + b];
+    tr_dft<A, DIR>(t[b]);
+#pragma unroll
+    for (int k = 1; k < A; ++k) {
+      const int m = b * k;
+      if (m == 0) continue;
+      if (4 * m == R) t[b][k] = mul_mi(t[b][k], DIR);
+      else if (2 * m == R) t[b][k] = make_float2(-t[b][k].x, -t[b][k].y);
+      else if (4 * m == 3 * R) t[b][k] = mul_mi(t[b][k], -DIR);
+      else t[b][k] = cmul(t[b][k], make_float2(tab.c[m], DIR < 0 ? -tab.s[m] : tab.s[m]));
+    }
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < A; ++k1) {
+    float2 u[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) u[b] = t[b][k1];
+    tr_dft<B, DIR>(u);
+#pragma unroll
+    for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = u[k2];
+  }
+}
+
+template <int R, int DIR>
+__device__ __forceinline__ void tr_dft(float2 (&v)[R]) {
+  if constexpr (R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 16) dft_small<R>(v, DIR);
+  else if constexpr (R == 6) tr_comp<2, 3, DIR>(v);
+  else if constexpr (R == 9) tr_comp<3, 3, DIR>(v);
+  else if constexpr (R == 10) tr_comp<2, 5, DIR>(v);
+  else if constexpr (R == 12) tr_comp<4, 3, DIR>(v);
+  else if constexpr (R == 15) tr_comp<3, 5, DIR>(v);
+  else if constexpr (R == 18) tr_comp<2, 9, DIR>(v);
+  else if constexpr (R == 20) tr_comp<4, 5, DIR>(v);
+  else if constexpr (R == 24) tr_comp<8, 3, DIR>(v);
+  else if constexpr (R == 25) tr_comp<5, 5, DIR>(v);
+  else if constexpr (R == 27) tr_comp<3, 9, DIR>(v);
+  else if constexpr (R == 30) tr_comp<2, 15, DIR>(v);
+  else {
+    static_assert(R == 32, "radix");
+    tr_comp<4, 8, DIR>(v);
+  }
+}
+
+// v[r] *= w^(j r), w = exp(-+2 pi i / n) from its table tw
+template <int DIR, int R>
+__device__ __forceinline__ void tr_twiddle(float2 (&v)[R], const float2* tw, int j) {
+  // w^(j r) from the table entries for r = 1, 2, 3 and the multiples of 4: at most one product
+  float2 lo[4], hi[(R + 3) / 4];
+#pragma unroll
+  for (int b = 1; b < 4; ++b)
+    if (b < R) {
+      lo[b] = tw[j * b];
+      if (DIR > 0) lo[b].y = -lo[b].y;
+    }
+#pragma unroll
+  for (int q = 1; q < (R + 3) / 4; ++q) {
+    hi[q] = tw[j * 4 * q];
+    if (DIR > 0) hi[q].y = -hi[q].y;
+  }
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    const float2 w = r < 4 ? lo[r] : (r % 4 == 0 ? hi[r / 4] : cmul(hi[r / 4], lo[r % 4]));
+    v[r] = cmul(v[r], w);
+  }
+}
+
+#define TR_SMALL(F) F(2) F(3) F(4) F(5) F(6) F(8) F(9) F(10) F(12) F(15) F(16)
+#define TR_LARGE(F) F(18) F(20) F(24) F(25) F(27) F(30) F(32)
+
 // Division of x < 2^31 by a divisor 1 <= d < 2^20 known only at run time, as a
 // multiply-high, an add and a shift (Granlund and Montgomery, "Division by invariant
 // integers using multiplication", 1994): with l = ceil(log2 d) and
@@ -227,6 +340,9 @@ __device__ __forceinline__ void lds_fft_lines(float2* lds, const LdsLines& tg, i
 template <int N> struct CtPlan;
 template <> struct CtPlan<256> { static constexpr int P = 2, R0 = 16, R1 = 16; };
 template <> struct CtPlan<128> { static constexpr int P = 2, R0 = 16, R1 = 8; };
+template <> struct CtPlan<96> { static constexpr int P = 2, R0 = 12, R1 = 8; };
+template <> struct CtPlan<80> { static constexpr int P = 2, R0 = 10, R1 = 8; };
+template <> struct CtPlan<48> { static constexpr int P = 2, R0 = 8, R1 = 6; };
 template <> struct CtPlan<64> { static constexpr int P = 2, R0 = 8, R1 = 8; };
 template <> struct CtPlan<32> { static constexpr int P = 2, R0 = 8, R1 = 4; };
 template <> struct CtPlan<16> { static constexpr int P = 1, R0 = 16, R1 = 1; };
@@ -293,6 +409,71 @@ __device__ __forceinline__ void stockham_pass_ct(float2* lds, int T, int LS, int
     }
     __syncthreads();
   }
+}
+
+// One Stockham pass with compile-time size, radix, stride and direction over a run-time number
+// of lines T <= TMAX (fT its divider): every butterfly of the pass is held at once, lines
+// spread over consecutive threads.
+template <int N, int R, int Ns, int DIR, int NTHREADS, int TMAX>
+__device__ __forceinline__ void stockham_pass_lines(float2* lds, const FastDiv& fT, int LS, int ES, const float2* tw,
+                                                    int tid) {
+  constexpr int nR = N / R;
+  constexpr int MAXQ = (TMAX * nR + NTHREADS - 1) / NTHREADS;
+  constexpr int STW = N / (Ns * R);
+  const int total = (int)fT.d * nR;
+  float2 v[MAXQ][R];
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const int bf = tid + q * NTHREADS;
+    if (bf < total) {
+      const int j = (int)fdiv(bf, fT), base = (bf - j * (int)fT.d) * LS;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[q][r] = lds[base + (j + r * nR) * ES];
+      if (Ns > 1) {
+        const int k = j % Ns;
+        float2 wp[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if ((1 << b) < R) {
+            wp[b] = tw[k * (1 << b) * STW];
+            if (DIR > 0) wp[b].y = -wp[b].y;
+          }
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          float2 w = make_float2(1.f, 0.f);
+          bool first = true;
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            if (r & (1 << b)) {
+              w = first ? wp[b] : cmul(w, wp[b]);
+              first = false;
+            }
+          v[q][r] = cmul(v[q][r], w);
+        }
+      }
+      tr_dft<R, DIR>(v[q]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const int bf = tid + q * NTHREADS;
+    if (bf < total) {
+      const int j = (int)fdiv(bf, fT), base = (bf - j * (int)fT.d) * LS;
+      const int idxD = (j / Ns) * Ns * R + (j % Ns);
+#pragma unroll
+      for (int r = 0; r < R; ++r) lds[base + (idxD + r * Ns) * ES] = v[q][r];
+    }
+  }
+  __syncthreads();
+}
+
+template <int N, int DIR, int NTHREADS, int TMAX>
+__device__ __forceinline__ void lds_fft_ct_lines(float2* lds, const FastDiv& fT, int LS, int ES, const float2* tw,
+                                                 int tid) {
+  using P = CtPlan<N>;
+  stockham_pass_lines<N, P::R0, 1, DIR, NTHREADS, TMAX>(lds, fT, LS, ES, tw, tid);
+  if constexpr (P::P > 1) stockham_pass_lines<N, P::R1, P::R0, DIR, NTHREADS, TMAX>(lds, fT, LS, ES, tw, tid);
 }
 
 // The same pass over the lines one wave owns: in each chunk of Tc = min(CH / N, TL) lines
@@ -444,6 +625,47 @@ __device__ __forceinline__ void lds_fft_ct(float2* lds, int T, int LS, int ES, c
   if (tid < 0) tid = threadIdx.x;
   stockham_pass_ct<N, P::R0, 1, NTHREADS, CH>(lds, T, LS, ES, tw, dir, tid);
   if constexpr (P::P > 1) stockham_pass_ct<N, P::R1, P::R0, NTHREADS, CH>(lds, T, LS, ES, tw, dir, tid);
+}
+
+// ---------------------------------------------------------------- two radices, run-time size
+// The transform of T lines (a power of two, innermost in LDS: element i of line l at i ES + l)
+// of length n = R0 R1 with both radices at most 16, in place: two passes, each holding the
+// thread's butterflies (at most MAXQ) between two barriers.
+template <int R, int DIR, int T, int NTHREADS, bool LAST>
+__device__ __forceinline__ void two_radix_pass(float2* lds, int ES, int n, const float2* tw) {
+  constexpr int MAXQ = 16 * T / NTHREADS;  // n / R <= 16 butterflies per line
+  const int nR = n / R, l = threadIdx.x % T, j0 = threadIdx.x / T;
+  float2 v[MAXQ][R];
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const int j = j0 + q * (NTHREADS / T);
+    if (j < nR) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[q][r] = lds[(j + r * nR) * ES + l];
+      if (LAST) tr_twiddle<DIR, R>(v[q], tw, j);
+      tr_dft<R, DIR>(v[q]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const int j = j0 + q * (NTHREADS / T);
+    if (j < nR) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) lds[(LAST ? j + r * nR : j * R + r) * ES + l] = v[q][r];
+    }
+  }
+  __syncthreads();
+}
+
+template <int DIR, int T, int NTHREADS>
+__device__ __forceinline__ void lds_fft_two_radix(float2* lds, int ES, int n, int r0, int r1, const float2* tw) {
+#define TR_TWO(R) case R: two_radix_pass<R, DIR, T, NTHREADS, false>(lds, ES, n, tw); break;
+  switch (r0) { TR_SMALL(TR_TWO) default: break; }
+#undef TR_TWO
+#define TR_TWO(R) case R: two_radix_pass<R, DIR, T, NTHREADS, true>(lds, ES, n, tw); break;
+  switch (r1) { TR_SMALL(TR_TWO) default: break; }
+#undef TR_TWO
 }
 
 }  // namespace mx

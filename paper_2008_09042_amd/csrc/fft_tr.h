@@ -36,91 +36,6 @@ namespace {
 // 512 x 512 and 16 coils 11-16 against 19-27 us.
 constexpr int TR_NT = 256;
 
-constexpr double tr_cos(double x) {  // Taylor series about 0 for |x| <= pi
-  double t = 1.0, s = 1.0;
-  for (int k = 1; k < 20; ++k) {
-    t *= -x * x / ((2.0 * k - 1.0) * (2.0 * k));
-    s += t;
-  }
-  return s;
-}
-constexpr double tr_sin(double x) {
-  double t = x, s = x;
-  for (int k = 1; k < 20; ++k) {
-    t *= -x * x / ((2.0 * k) * (2.0 * k + 1.0));
-    s += t;
-  }
-  return s;
-}
-template <int N>
-struct TrTab {  // cos and sin of 2 pi m / N
-  float c[N], s[N];
-  constexpr TrTab() : c(), s() {
-    for (int m = 0; m < N; ++m) {
-      const int q = 2 * m > N ? m - N : m;
-      const double x = 6.283185307179586476925286766559 * q / N;
-      c[m] = (float)tr_cos(x);
-      s[m] = (float)tr_sin(x);
-    }
-  }
-};
-
-template <int R, int DIR>
-__device__ __forceinline__ void tr_dft(float2 (&v)[R]);
-
-// R = A B: input index B a + b, DFTs over a, the products w_R^(b k1), DFTs over b; output
-// k1 + A k2.
-template <int A, int B, int DIR>
-__device__ __forceinline__ void tr_comp(float2 (&v)[A * B]) {
-  constexpr int R = A * B;
-  constexpr TrTab<R> tab;
-  float2 t[B][A];
-#pragma unroll
-  for (int b = 0; b < B; ++b) {
-#pragma unroll
-    for (int q = 0; q < A; ++q) t[b][q] = v[B * q + b];
-    tr_dft<A, DIR>(t[b]);
-#pragma unroll
-    for (int k = 1; k < A; ++k) {
-      const int m = b * k;
-      if (m == 0) continue;
-      if (4 * m == R) t[b][k] = mul_mi(t[b][k], DIR);
-      else if (2 * m == R) t[b][k] = make_float2(-t[b][k].x, -t[b][k].y);
-      else if (4 * m == 3 * R) t[b][k] = mul_mi(t[b][k], -DIR);
-      else t[b][k] = cmul(t[b][k], make_float2(tab.c[m], DIR < 0 ? -tab.s[m] : tab.s[m]));
-    }
-  }
-#pragma unroll
-  for (int k1 = 0; k1 < A; ++k1) {
-    float2 u[B];
-#pragma unroll
-    for (int b = 0; b < B; ++b) u[b] = t[b][k1];
-    tr_dft<B, DIR>(u);
-#pragma unroll
-    for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = u[k2];
-  }
-}
-
-template <int R, int DIR>
-__device__ __forceinline__ void tr_dft(float2 (&v)[R]) {
-  if constexpr (R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 16) dft_small<R>(v, DIR);
-  else if constexpr (R == 6) tr_comp<2, 3, DIR>(v);
-  else if constexpr (R == 9) tr_comp<3, 3, DIR>(v);
-  else if constexpr (R == 10) tr_comp<2, 5, DIR>(v);
-  else if constexpr (R == 12) tr_comp<4, 3, DIR>(v);
-  else if constexpr (R == 15) tr_comp<3, 5, DIR>(v);
-  else if constexpr (R == 18) tr_comp<2, 9, DIR>(v);
-  else if constexpr (R == 20) tr_comp<4, 5, DIR>(v);
-  else if constexpr (R == 24) tr_comp<8, 3, DIR>(v);
-  else if constexpr (R == 25) tr_comp<5, 5, DIR>(v);
-  else if constexpr (R == 27) tr_comp<3, 9, DIR>(v);
-  else if constexpr (R == 30) tr_comp<2, 15, DIR>(v);
-  else {
-    static_assert(R == 32, "radix");
-    tr_comp<4, 8, DIR>(v);
-  }
-}
-
 // Where one line of a tile comes from and goes to.  SMP as in fft_axis_body, with the
 // gridding window's passes visiting only the lines that carry work: the pad pass (4) takes
 // its lines from the J wn0 window rows, the crop pass (5) from the wn1 window columns.
@@ -316,28 +231,6 @@ __device__ __forceinline__ void tr_pass0(const FftAxisArgs& a, float2* lds, cons
   }
 }
 
-template <int DIR, int R>
-__device__ __forceinline__ void tr_twiddle(float2 (&v)[R], const float2* tw, int j) {
-  // w^(j r) from the table entries for r = 1, 2, 3 and the multiples of 4: at most one product
-  float2 lo[4], hi[(R + 3) / 4];
-#pragma unroll
-  for (int b = 1; b < 4; ++b)
-    if (b < R) {
-      lo[b] = tw[j * b];
-      if (DIR > 0) lo[b].y = -lo[b].y;
-    }
-#pragma unroll
-  for (int q = 1; q < (R + 3) / 4; ++q) {
-    hi[q] = tw[j * 4 * q];
-    if (DIR > 0) hi[q].y = -hi[q].y;
-  }
-#pragma unroll
-  for (int r = 1; r < R; ++r) {
-    const float2 w = r < 4 ? lo[r] : (r % 4 == 0 ? hi[r / 4] : cmul(hi[r / 4], lo[r % 4]));
-    v[r] = cmul(v[r], w);
-  }
-}
-
 // The middle of a masked round trip (8): pass 1 of the forward transform, the mask, and pass
 // 0 of the inverse, whose inputs j' + r R0 are the outputs that the thread holds.  The outputs
 // go back to the LDS row that the thread read, so no barrier parts the two.
@@ -399,9 +292,6 @@ __device__ __forceinline__ void tr_pass1(const FftAxisArgs& a, const float2* lds
     }
   }
 }
-
-#define TR_SMALL(F) F(2) F(3) F(4) F(5) F(6) F(8) F(9) F(10) F(12) F(15) F(16)
-#define TR_LARGE(F) F(18) F(20) F(24) F(25) F(27) F(30) F(32)
 
 // BIG: radices up to 32 (about twice the registers), else up to 16.
 template <int SMP, int DIR, bool BIG>

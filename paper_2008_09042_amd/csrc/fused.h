@@ -11,14 +11,14 @@ struct PlaneArgs {
   const float2* T3;                  // [J][n2][r0][r1]  (core x_4 c x_3 U2)
   const float2* xt;                  // [n2][n0][n1]     image, readout axis first, times the
                                      //                  chessboard sign (-1)^(i0 + i1)
+  const float2* T3c;                 // plane_jvp: T3 of the coefficients' direction
+  const float2* xt2;                 //            and xt of the image's direction
   const int32_t* pos;                // [L]  k0 * n1 + k1 of each sampled line
   float2* Z;                         // [J][n2][L]  plane-DFT samples (fwd out / adj in)
   float2* T3b;                       // [J][n2][r0][r1] adjoint out (or null)
   float2* gxpart;                    // [ngroups][n2][n0][n1] adjoint out (or null)
   const float2* tw0;                 // twiddles for n0, n1
   const float2* tw1;
-  int nrad0, nrad1;
-  int rad0[12], rad1[12];
   int precision;
   // Factor operands in matrix-core fragment order, built at plan time (frag_operand_launch):
   const void* U0F;                   // A of P = U0 V:        A(i0, p0) = U0[i0][p0]
@@ -46,6 +46,7 @@ struct LineArgs {
   const float2* tw2;
   int nrad2;
   int rad2[12];
+  int two0, two1;                    // n2 = two0 two1, both at most 16, or 0
 };
 
 bool fused_supported(int64_t n0, int64_t n1, int64_t n2, int64_t r0, int64_t r1, int precision);
@@ -57,6 +58,8 @@ size_t frag_operand_bytes(int no, int nk, int is_b, int precision);
 hipError_t frag_operand_launch(const float2* src, int no, int nk, int64_t so, int64_t sk, int conj, int is_b,
                                int precision, void* dst, hipStream_t st);
 hipError_t plane_fwd_launch(const PlaneArgs& a, hipStream_t st);
+// Z = the sampled plane DFT of xt2 (.) map(T3) + xt (.) map(T3c)
+hipError_t plane_jvp_launch(const PlaneArgs& a, hipStream_t st);
 hipError_t plane_adj_launch(const PlaneArgs& a, hipStream_t st);
 int line_blocks(int J, int64_t L);
 hipError_t line_fwd_launch(const LineArgs& a, hipStream_t st);

@@ -390,8 +390,6 @@ PlaneArgs plane_args(const Plan& p, void* ws, int G) {
   a.pos = p.d_pos;
   a.Z = wsp<float2>(ws, p.off_Z);
   a.tw0 = p.d_tw[0]; a.tw1 = p.d_tw[1];
-  a.nrad0 = p.nrad[0]; a.nrad1 = p.nrad[1];
-  for (int q = 0; q < 12; ++q) { a.rad0[q] = p.radix[0][q]; a.rad1[q] = p.radix[1][q]; }
   a.precision = p.precision;
   a.U0F = p.U0F;
   a.U1TF = p.U1TF;
@@ -411,6 +409,7 @@ LineArgs line_args(const Plan& p) {
   a.tw2 = p.d_tw[2];
   a.nrad2 = p.nrad[2];
   for (int q = 0; q < 12; ++q) a.rad2[q] = p.radix[2][q];
+  if (!fft_tr_radices(p.n[2], a.two0, a.two1) || a.two0 > 16) a.two0 = a.two1 = 0;
   return a;
 }
 
@@ -618,21 +617,34 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
     p.fused = true;
     p.L = (int64_t)pos.size();
     {
-      // coils per plane workgroup: the largest group (up to 16) that still gives every
-      // compute unit a workgroup; larger groups amortise the per-workgroup set-up (the
-      // forward's x share, held in registers across the group's coils) and, in the adjoint,
-      // mean fewer gx partials to sum
+      // coils per plane workgroup: the time of a launch is about its rounds over the compute
+      // units (one workgroup each: the plane fills the LDS) times the coils of a group, plus
+      // half a coil's worth of set-up per workgroup.  Halving from 16 until every compute
+      // unit had a workgroup took 2 coils in 2 rounds where 3 fit one (64 planes, 12 coils).
+      // The adjoint's groups each write a gx partial: no more of them than the halving rule
+      // gives, and the fewest at equal cost.
       int dev = 0, cus = 256;
       if (hipGetDevice(&dev) == hipSuccess &&
           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
-      auto pick = [&](int gmax) {
-        int G = gmax;
-        while (G > 1 && p.n[2] * ((p.J + G - 1) / G) < cus) G /= 2;
-        return G;
+      auto groups = [&](int G) { return (p.J + G - 1) / G; };
+      int halved = 16;
+      while (halved > 1 && p.n[2] * groups(halved) < cus) halved /= 2;
+      auto pick = [&](int max_groups) {
+        int best = halved;
+        double cost = 0.0;
+        for (int G = std::min(16, p.J); G >= 1; --G) {
+          if (groups(G) > max_groups || groups(G) * (int64_t)G - p.J >= G) continue;
+          const double c = (double)((p.n[2] * groups(G) + cus - 1) / cus) * (G + 0.5);
+          if (cost == 0.0 || c < cost) {
+            cost = c;
+            best = G;
+          }
+        }
+        return best;
       };
-      p.G_fwd = pick(16);
-      p.G_adj = pick(16);
+      p.G_fwd = pick(p.J);
+      p.G_adj = pick(groups(halved));
     }
     if ((e = hipMalloc(&p.d_pos, pos.size() * sizeof(int32_t))) != hipSuccess) return hip_err(e);
     if ((e = hipMemcpy(p.d_pos, pos.data(), pos.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
@@ -992,21 +1004,42 @@ hipError_t run_basis_adjoint(const Plan& p, const float2* S, float2* c, float al
 }
 
 // ---- fused path pieces
-static hipError_t fused_prepare(const Plan& p, const float2* x, const float2* c, void* ws, hipStream_t st) {
+
+// T1 = core x_4 c, T3 = T1 x_3 U2
+static hipError_t fused_factors(const Plan& p, const float2* c, float2* T1, float2* T3, void* ws, hipStream_t st) {
   void* gws = wsp<void>(ws, p.off_gemm);
-  hipError_t e = core_forward(p, c, wsp<float2>(ws, p.off_T1), ws, st);
+  hipError_t e = core_forward(p, c, T1, ws, st);
   if (e != hipSuccess) return e;
   if (p.mode3_direct) {
     Mode3Args m = mode3_args(p);
-    m.T1 = wsp<float2>(ws, p.off_T1);
-    m.T3 = wsp<float2>(ws, p.off_T3);
-    e = TIMED("mode3_fwd", mode3_fwd_launch(m, p.precision, st));
-  } else {
-    e = TIMED("gemm_mode3", gemm_launch(fused_T3_args(p, wsp<float2>(ws, p.off_T1), wsp<float2>(ws, p.off_T3)),
-                                        p.precision, gws, st));
+    m.T1 = T1;
+    m.T3 = T3;
+    return TIMED("mode3_fwd", mode3_fwd_launch(m, p.precision, st));
   }
+  return TIMED("gemm_mode3", gemm_launch(fused_T3_args(p, T1, T3), p.precision, gws, st));
+}
+
+static hipError_t fused_image(const Plan& p, const float2* x, float2* xt, hipStream_t st) {
+  return TIMED("transpose_x", transpose_launch(x, p.n[0] * p.n[1], p.n[2], (int)p.n[1], xt, st));
+}
+
+static hipError_t fused_prepare(const Plan& p, const float2* x, const float2* c, void* ws, hipStream_t st) {
+  hipError_t e = fused_factors(p, c, wsp<float2>(ws, p.off_T1), wsp<float2>(ws, p.off_T3), ws, st);
   if (e != hipSuccess) return e;
-  return TIMED("transpose_x", transpose_launch(x, p.n[0] * p.n[1], p.n[2], (int)p.n[1], wsp<float2>(ws, p.off_xt), st));
+  return fused_image(p, x, wsp<float2>(ws, p.off_xt), st);
+}
+
+// Z = the plane DFT samples of J[dx, dc] at the prepared (x, c).  The direction's factors and
+// image sit where the adjoint leaves its own later: T3b, T1b and the gx partials.
+static hipError_t fused_jvp(const Plan& p, const float2* dx, const float2* dc, void* ws, hipStream_t st) {
+  float2 *T3c = wsp<float2>(ws, p.off_T3b), *xt2 = wsp<float2>(ws, p.off_gxp);
+  hipError_t e = fused_factors(p, dc, wsp<float2>(ws, p.off_T1b), T3c, ws, st);
+  if (e != hipSuccess) return e;
+  if ((e = fused_image(p, dx, xt2, st)) != hipSuccess) return e;
+  PlaneArgs pa = plane_args(p, ws, p.G_fwd);
+  pa.T3c = T3c;
+  pa.xt2 = xt2;
+  return TIMED("plane_jvp", plane_jvp_launch(pa, st));
 }
 
 // out: E (y null) or the weighted residual; with `transfer` (y given) the residual goes out
@@ -1037,8 +1070,7 @@ static hipError_t fused_adjoint(const Plan& p, const float2* x, const float2* c,
     if (gx) {
       if ((e = fused_prepare(p, x, c, ws, st)) != hipSuccess) return e;
     } else {
-      e = TIMED("transpose_x", transpose_launch(x, p.n[0] * p.n[1], p.n[2], (int)p.n[1], wsp<float2>(ws, p.off_xt), st));
-      if (e != hipSuccess) return e;
+      if ((e = fused_image(p, x, wsp<float2>(ws, p.off_xt), st)) != hipSuccess) return e;
     }
   }
   // the scale: in the line kernel, or (transfer) where the outputs are written
@@ -1228,30 +1260,58 @@ hipError_t run_grad(const Plan& p, const float2* x, const float2* c, const float
 // ---- Gauss-Newton step (Sec. II-B, Eq. (6) and Eq. (7))
 
 // J[dx, dc] = E(dx, c) + E(x, dc): E is bilinear, so the Jacobian-vector product of Eq. (7)
-// is two encodes; the second goes through the E region of the workspace.
+// is two encodes; the second goes through the E region of the workspace.  On the fused path
+// the two meet in the plane, before the transform.
 hipError_t run_jvp(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc, float2* y,
                    void* ws, hipStream_t st) {
-  hipError_t e = run_encode(p, dx, c, y, ws, st);
-  if (e != hipSuccess) return e;
+  hipError_t e;
+  if (p.fused) {
+    if ((e = fused_prepare(p, x, c, ws, st)) != hipSuccess || (e = fused_jvp(p, dx, dc, ws, st)) != hipSuccess) return e;
+    LineArgs la = line_args(p);
+    la.Z = wsp<float2>(ws, p.off_Z);
+    la.out = y;
+    return TIMED("line_fwd", line_fwd_launch(la, st));
+  }
+  if ((e = run_encode(p, dx, c, y, ws, st)) != hipSuccess) return e;
   float2* E = wsp<float2>(ws, p.off_E);
   if ((e = run_encode(p, x, dc, E, ws, st)) != hipSuccess) return e;
   return TIMED("jvp_sum", caxpy_launch(y, E, 1.0f, (int64_t)p.J * p.M, st));
 }
 
 // (ox, oc) = J^H (w (.) J[dx, dc]) + (lam_x dx, lam_c dc)
-// (with part: the partials of <(dx, dc), (ox, oc)>)
+// (with part: the partials of <(dx, dc), (ox, oc)>).  On the fused path (x, c) has been
+// prepared by the caller, and the samples stay between the plane kernels: the readout is
+// fully sampled, so its DFT and inverse around the weights are one pass over Z, and without
+// weights the identity, n2 gscale^2 = 1 / (n0 n1) taken by the outputs' scale.
 static hipError_t normal_op(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc,
                             float lam_x, float lam_c, float2* ox, float2* oc, double* part, void* ws, hipStream_t st) {
-  float2* u = wsp<float2>(ws, p.off_U);
-  hipError_t e = run_jvp(p, x, c, dx, dc, u, ws, st);
-  if (e != hipSuccess) return e;
-  if (p.d_w && (e = TIMED("weights", weight_rows_launch(u, p.d_w, p.M, p.J, st))) != hipSuccess) return e;
-  if ((e = run_adjoint(p, x, c, u, 1.0f, nullptr, ox, oc, ws, st, false, false)) != hipSuccess) return e;
+  hipError_t e;
+  if (p.fused) {
+    float2* Z = wsp<float2>(ws, p.off_Z);
+    if ((e = fused_jvp(p, dx, dc, ws, st)) != hipSuccess) return e;
+    float alpha = (float)(1.0 / ((double)p.n[0] * (double)p.n[1]));
+    if (p.d_w) {
+      LineArgs la = line_args(p);
+      la.Z = Z;
+      la.Zw = Z;  // each workgroup reads its lines before writing them
+      la.w = p.d_w;
+      alpha = 1.0f;
+      if ((e = TIMED("line_fwd", line_fwd_launch(la, st))) != hipSuccess) return e;
+    }
+    if ((e = fused_adjoint(p, x, c, Z, alpha, nullptr, ox, oc, ws, st, true, true)) != hipSuccess) return e;
+  } else {
+    float2* u = wsp<float2>(ws, p.off_U);
+    if ((e = run_jvp(p, x, c, dx, dc, u, ws, st)) != hipSuccess) return e;
+    if (p.d_w && (e = TIMED("weights", weight_rows_launch(u, p.d_w, p.M, p.J, st))) != hipSuccess) return e;
+    if ((e = run_adjoint(p, x, c, u, 1.0f, nullptr, ox, oc, ws, st, false, false)) != hipSuccess) return e;
+  }
   return TIMED("normal_axpy", axpy_dot_launch(ox, oc, dx, dc, lam_x, lam_c, p.N, (int64_t)p.J * p.K, part, st));
 }
 
 hipError_t run_normal(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc,
                       float lam_x, float lam_c, float2* ox, float2* oc, void* ws, hipStream_t st) {
+  hipError_t e;
+  if (p.fused && (e = fused_prepare(p, x, c, ws, st)) != hipSuccess) return e;
   return normal_op(p, x, c, dx, dc, lam_x, lam_c, ox, oc, nullptr, ws, st);
 }
 
@@ -1307,6 +1367,8 @@ static hipError_t cg_loop(const Plan& p, Start start, Apply apply, int64_t n0, i
 hipError_t run_cg(const Plan& p, const float2* x, const float2* c, const float2* bx, const float2* bc, float lam_x,
                   float lam_c, int iters, float2* dx, float2* dc, double* rr, void* ws, hipStream_t st) {
   const int64_t JK = (int64_t)p.J * p.K;
+  hipError_t e;
+  if (p.fused && (e = fused_prepare(p, x, c, ws, st)) != hipSuccess) return e;  // once for every step
   auto start = [&](double* part) {
     const CgWs w = cg_ws(p, ws);
     return TIMED("cg_update", cg_start_launch(dx, dc, bx, bc, p.N, JK, w.r, w.d, part, st));

@@ -44,8 +44,7 @@ constexpr int TW_OFF = STAGE_OFF + STAGE_ELEMS;  // twiddles of n0 and n1 (2 x P
 constexpr int LDS_ELEMS = TW_OFF + 2 * PMAX;
 // the adjoint's Wb partials (8 waves x 9 tiles x 256) overwrite the plane and staging regions
 static_assert(NWAVE * 9 * 256 <= PLANE_ELEMS + STAGE_ELEMS, "Wb partials must fit");
-constexpr int FFT_CHUNK_FWD = PMAX * PMAX;       // elements per register chunk of a transform pass
-constexpr int FFT_CHUNK_ADJ = PMAX * PMAX / 2;   // run-time plane sizes in plane_adj_kernel (P and gx held)
+constexpr int FFT_CHUNK = PMAX * PMAX;           // elements per register chunk of a transform pass
 constexpr int SCAT = 4;                          // samples per thread loaded ahead of the scatter
 
 // ---------------------------------------------------------------- plane geometry
@@ -97,9 +96,18 @@ struct Share {
   bool on;
 };
 
-template <int N0, int N1, int RB>
+// The wave's index in a scalar register with run-time rank blocks (and in the JVP kernel):
+// uniform branches and offsets, no spills (the run-time adjoint had 61, at 96 x 80 78 -> 64 us).
+// The compile-time rank blocks fit as they are and lose 2 % to it (128 x 128: 402 -> 410 us).
+template <bool SCALAR>
+__device__ __forceinline__ int wave_index() {
+  const int w = threadIdx.x >> 6;
+  return SCALAR ? __builtin_amdgcn_readfirstlane(w) : w;
+}
+
+template <bool SCALAR, int N0, int N1, int RB>
 __device__ __forceinline__ Share plane_share(const Geo<N0, N1, RB>& g) {
-  const int wave = threadIdx.x >> 6;
+  const int wave = wave_index<SCALAR>();
   Share s;
   s.q = NWAVE / g.n1b;
   s.cb = wave % g.n1b;
@@ -129,39 +137,56 @@ __device__ __forceinline__ void load_twiddles(const PlaneArgs& a, const Geo<N0, 
   for (int e = threadIdx.x; e < g.n1; e += PT) tw1[e] = a.tw1[e];
 }
 
+// The transform of T lines of a run-time length n (a multiple of 16 up to 128 without prime
+// factors above 5), one compile-time size each: two radices per line, every butterfly of a
+// pass held at once.  Run-time radices (8, 4, 3 at 96) cost a pass and two barriers more, and
+// index divisions: plane_fwd of 96 x 80 planes, FP32 121 -> 54 us with it and the coil
+// groups that the plan picks.
+template <int DIR>
+__device__ __forceinline__ void plane_lines(float2* lds, int n, int T, int LS, int ES, const float2* tw, int tid) {
+  const FastDiv fT = fast_div((uint32_t)T);
+  switch (n) {
+    case 16: lds_fft_ct_lines<16, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+    case 32: lds_fft_ct_lines<32, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+    case 48: lds_fft_ct_lines<48, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+    case 64: lds_fft_ct_lines<64, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+    case 80: lds_fft_ct_lines<80, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+    case 96: lds_fft_ct_lines<96, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+    default: lds_fft_ct_lines<128, DIR, PT, PMAX>(lds, fT, LS, ES, tw, tid); break;
+  }
+}
+
 // 2D centred DFT of the plane (chessboard signs applied by the caller); ends synchronised.
-// CH elements of a pass are held in registers at a time.
-template <int CH, int N0, int N1, int RB, int QB = 0>
-__device__ __forceinline__ void plane_fft(const PlaneArgs& a, const Geo<N0, N1, RB>& g, float2* lds, int dir) {
+template <int DIR, int N0, int N1, int RB, int QB = 0>
+__device__ __forceinline__ void plane_fft(const Geo<N0, N1, RB>& g, float2* lds) {
   const float2* tw0 = lds + TW_OFF;
   const float2* tw1 = tw0 + PMAX;
   int tid = threadIdx.x;  // opaque: the passes' addresses are not hoisted out of the coil loop
   asm volatile("" : "+v"(tid));
   // wave-owned lines (no barrier inside the transform of one axis) where a chunk holds at
   // least 16 lines per wave; otherwise every pass synchronises the workgroup
+  constexpr int CH = FFT_CHUNK;
   auto rows = [&]() {
     if constexpr (N1 != 0 && wave_lines_fit<N1, PT, CH, N0>()) {
-      lds_fft_ct_wave<N1, PT, CH, N0, QB>(lds, g.PS, 1, tw1, dir, tid);
+      lds_fft_ct_wave<N1, PT, CH, N0, QB>(lds, g.PS, 1, tw1, DIR, tid);
       __syncthreads();
     } else if constexpr (N1 != 0) {
-      lds_fft_ct<N1, PT, CH>(lds, g.n0, g.PS, 1, tw1, dir, tid);
+      lds_fft_ct<N1, PT, CH>(lds, g.n0, g.PS, 1, tw1, DIR, tid);
     } else {
-      LdsLines t{g.n0, g.PS, 1};
-      lds_fft_lines<PT, CH>(lds, t, g.n1, a.rad1, a.nrad1, tw1, dir);
+      plane_lines<DIR>(lds, g.n1, g.n0, g.PS, 1, tw1, tid);
     }
   };
   auto cols = [&]() {
     if constexpr (N0 != 0 && wave_lines_fit<N0, PT, CH, N1>()) {
-      lds_fft_ct_wave<N0, PT, CH, N1, QB>(lds, 1, g.PS, tw0, dir, tid);
+      lds_fft_ct_wave<N0, PT, CH, N1, QB>(lds, 1, g.PS, tw0, DIR, tid);
       __syncthreads();
     } else if constexpr (N0 != 0) {
-      lds_fft_ct<N0, PT, CH>(lds, g.n1, 1, g.PS, tw0, dir, tid);
+      lds_fft_ct<N0, PT, CH>(lds, g.n1, 1, g.PS, tw0, DIR, tid);
     } else {
-      LdsLines t{g.n1, 1, g.PS};
-      lds_fft_lines<PT, CH>(lds, t, g.n0, a.rad0, a.nrad0, tw0, dir);
+      plane_lines<DIR>(lds, g.n0, g.n1, 1, g.PS, tw0, tid);
     }
   };
-  if (dir < 0) { rows(); cols(); } else { cols(); rows(); }
+  if (DIR < 0) { rows(); cols(); } else { cols(); rows(); }
 }
 
 // ---------------------------------------------------------------- coil map
@@ -203,9 +228,9 @@ __device__ __forceinline__ WSlots w_slots(const Geo<N0, N1, RB>& g, int tid) {
 }
 
 template <int N0, int N1, int RB>
-__device__ __forceinline__ void w_load(const PlaneArgs& a, const Geo<N0, N1, RB>& g, int j, int i2, const WSlots& sl,
+__device__ __forceinline__ void w_load(const float2* T3, const Geo<N0, N1, RB>& g, int j, int i2, const WSlots& sl,
                                        WPrefetch& w) {
-  const float2* src = a.T3 + ((size_t)j * g.n2 + i2) * g.r0 * g.r1;
+  const float2* src = T3 + ((size_t)j * g.n2 + i2) * g.r0 * g.r1;
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -284,7 +309,7 @@ __device__ __forceinline__ void coil_p(const Geo<N0, N1, RB>& g, const float2* l
 template <int PREC, int N0, int N1, int RB>
 __device__ __forceinline__ void adjoint_w(const PlaneArgs& a, const Geo<N0, N1, RB>& g, int j, int i2, float2* lds,
                                           int lane, int tid) {
-  const int wave = threadIdx.x >> 6, grp = lane >> 4;
+  const int wave = wave_index<RB == 0>(), grp = lane >> 4;
   const int qy = NWAVE / g.n0b, yb = wave % g.n0b, kq = wave / g.n0b;
   const bool on = kq < qy;
   const int sp = frag_b_step_bytes<PREC>(g.r1b) / 16;  // 16-byte pieces of one step (<= 2 PT)
@@ -423,6 +448,28 @@ __device__ __forceinline__ void coil_map(const void* u0f, const void* u1tf, cons
   __syncthreads();  // U0 is consumed; the plane region is free
 }
 
+// The L sampled points of the transformed plane -> Z[j][i2], with the output chessboard sign.
+template <int N0, int N1, int RB>
+__device__ __forceinline__ void plane_gather(const PlaneArgs& a, const Geo<N0, N1, RB>& g, const float2* lds, int j,
+                                             int i2, int tid, const int (&pq)[SCAT]) {
+  float2* zo = a.Z + ((size_t)j * g.n2 + i2) * a.L;
+#pragma unroll
+  for (int k = 0; k < SCAT; ++k)
+    if (pq[k] >= 0) {
+      const int k0 = pq[k] / g.n1, k1 = pq[k] - k0 * g.n1;
+      float2 v = lds[k0 * g.PS + k1];
+      if ((k0 + k1) & 1) v = make_float2(-v.x, -v.y);
+      zo[tid + k * PT] = v;
+    }
+  for (int l = tid + SCAT * PT; l < a.L; l += PT) {  // beyond the preloaded positions
+    const int q = a.pos[l];
+    const int k0 = q / g.n1, k1 = q - k0 * g.n1;
+    float2 v = lds[k0 * g.PS + k1];
+    if ((k0 + k1) & 1) v = make_float2(-v.x, -v.y);
+    zo[l] = v;
+  }
+}
+
 template <int PREC, int N0, int N1, int RB, bool HALF = false>
 __global__ __launch_bounds__(PT) void plane_fwd_kernel(PlaneArgs a) {
   __shared__ float2 lds[LDS_ELEMS];
@@ -431,7 +478,7 @@ __global__ __launch_bounds__(PT) void plane_fwd_kernel(PlaneArgs a) {
   int i2, gi;
   plane_block(ngrp, g.n2, i2, gi);
   const float2* xp = a.xt + (size_t)i2 * g.n0 * g.n1;
-  const Share sh = plane_share(g);
+  const Share sh = plane_share<RB == 0>(g);
   int pq[SCAT];  // sampled plane positions, the same for every coil
 #pragma unroll
   for (int k = 0; k < SCAT; ++k) pq[k] = (int)threadIdx.x + k * PT < a.L ? a.pos[threadIdx.x + k * PT] : -1;
@@ -439,7 +486,7 @@ __global__ __launch_bounds__(PT) void plane_fwd_kernel(PlaneArgs a) {
   const int j0 = gi * a.G, j1 = min(a.J, (gi + 1) * a.G);
   const WSlots wsl = w_slots<PREC>(g, (int)threadIdx.x);
   WPrefetch w;  // W of the next coil, loaded one coil ahead
-  if (j0 < j1) w_load(a, g, j0, i2, wsl, w);
+  if (j0 < j1) w_load(a.T3, g, j0, i2, wsl, w);
   // the x values of the wave's share, the same for every coil: loaded once
   float2 xr[8][4];
   {
@@ -459,7 +506,7 @@ __global__ __launch_bounds__(PT) void plane_fwd_kernel(PlaneArgs a) {
     const int lane = tid & 63, grp = lane >> 4;
     f32x4 pr[8], pi[8];
     coil_map<PREC, HALF>(a.U0F, a.U1TF, g, lds, sh, lane, tid, w, pr, pi);
-    if (j + 1 < j1) w_load(a, g, j + 1, i2, wsl, w);
+    if (j + 1 < j1) w_load(a.T3, g, j + 1, i2, wsl, w);
     // m = x (.) P; the input chessboard sign of the centred DFT is carried by xt
     if (sh.on) {
 #pragma unroll
@@ -476,23 +523,107 @@ __global__ __launch_bounds__(PT) void plane_fwd_kernel(PlaneArgs a) {
       }
     }
     __syncthreads();
-    plane_fft<FFT_CHUNK_FWD>(a, g, lds, -1);
-    float2* zo = a.Z + ((size_t)j * g.n2 + i2) * a.L;
+    plane_fft<-1>(g, lds);
+    plane_gather(a, g, lds, j, i2, tid, pq);
+    __syncthreads();  // the gather is done with the plane
+  }
+}
+
+// The plane of a Jacobian-vector product (Eq. (7)): m = xt2 (.) P + xt (.) P', P the map of T3 (the
+// coefficients), P' that of T3c (their direction), xt2 and xt the image's direction and the
+// image; one transform and one gather where two encodes took two.  Both V = W U1^T come
+// first; then P and P' tile by tile from the same U0 fragments, so that m is all that is held
+// (P and P' whole would take 128 registers).
+template <int PREC, int N0, int N1, int RB>
+__global__ __launch_bounds__(PT) void plane_jvp_kernel(PlaneArgs a) {
+  constexpr bool HALF = false;
+  __shared__ float2 lds[LDS_ELEMS];
+  const Geo<N0, N1, RB> g(a);
+  const int ngrp = (a.J + a.G - 1) / a.G;
+  int i2, gi;
+  plane_block(ngrp, g.n2, i2, gi);
+  const size_t plane = (size_t)i2 * g.n0 * g.n1;
+  const Share sh = plane_share<true>(g);
+  int pq[SCAT];  // sampled plane positions, the same for every coil
 #pragma unroll
-    for (int k = 0; k < SCAT; ++k)
-      if (pq[k] >= 0) {
-        const int k0 = pq[k] / g.n1, k1 = pq[k] - k0 * g.n1;
-        float2 v = lds[k0 * g.PS + k1];
-        if ((k0 + k1) & 1) v = make_float2(-v.x, -v.y);
-        zo[tid + k * PT] = v;
-      }
-    for (int l = tid + SCAT * PT; l < a.L; l += PT) {  // beyond the preloaded positions
-      const int q = a.pos[l];
-      const int k0 = q / g.n1, k1 = q - k0 * g.n1;
-      float2 v = lds[k0 * g.PS + k1];
-      if ((k0 + k1) & 1) v = make_float2(-v.x, -v.y);
-      zo[l] = v;
+  for (int k = 0; k < SCAT; ++k) pq[k] = (int)threadIdx.x + k * PT < a.L ? a.pos[threadIdx.x + k * PT] : -1;
+  load_twiddles(a, g, lds);
+  const int j0 = gi * a.G, j1 = min(a.J, (gi + 1) * a.G);
+  const WSlots wsl = w_slots<PREC>(g, (int)threadIdx.x);
+  WPrefetch w;  // W of the next coil's map, loaded one coil ahead
+  if (j0 < j1) w_load(a.T3, g, j0, i2, wsl, w);
+  for (int j = j0; j < j1; ++j) {
+    int tid = threadIdx.x;  // opaque per coil, as in the forward kernel
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, grp = lane >> 4;
+    WPrefetch w2;
+    w_load(a.T3c, g, j, i2, wsl, w2);
+    typename Tile<PREC>::B v1[3], v2[3];
+    {
+      typename Tile<PREC>::B u1[3];
+#pragma unroll
+      for (int s = 0; s < 3; ++s)
+        if (s < g.r1b) u1[s] = frag_b<PREC>(a.U1TF, g.n1b, sh.cb, s, lane);
+      const int n = g.n0b * g.r0b * 128;  // 16-byte pieces of U0, as in coil_map
+      const uint4* src = reinterpret_cast<const uint4*>(a.U0F);
+      uint4* dst = reinterpret_cast<uint4*>(lds);
+      for (int e = tid; e < n; e += PT) dst[e] = src[e];
+      w_store<PREC>(g, lds, tid, w);
+      __syncthreads();
+      coil_v<PREC, HALF>(g, lds, lane, u1, v1);
+      __syncthreads();  // W is consumed
+      w_store<PREC>(g, lds, tid, w2);
+      __syncthreads();
+      coil_v<PREC, HALF>(g, lds, lane, u1, v2);
     }
+    float2 m[8][4];
+    {
+      const float2 *xpa = a.xt2 + plane, *xpb = a.xt + plane;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int rb = sh.part + i * sh.q;
+        if (sh.on && rb < g.n0b) {
+          float2 xa[4], xb[4];  // in flight across the tile's products
+          const int o = (16 * rb + 4 * grp) * g.n1 + 16 * sh.cb + (lane & 15);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            xa[r] = xpa[o + r * g.n1];
+            xb[r] = xpb[o + r * g.n1];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          typename Tile<PREC>::Acc c1 = Tile<PREC>::zero(), c2 = Tile<PREC>::zero();
+#pragma unroll
+          for (int s = 0; s < 3; ++s)
+            if (s < g.r0b) {
+              const typename Tile<PREC>::A u = frag_a<PREC>(lds, g.r0b, rb, s, lane);
+              rank_mma<PREC>(c1, u, v1[s], HALF && s == g.r0b - 1);
+              rank_mma<PREC>(c2, u, v2[s], HALF && s == g.r0b - 1);
+            }
+          f32x4 pr, pi, qr, qi;
+          Tile<PREC>::finish(c1, pr, pi);
+          Tile<PREC>::finish(c2, qr, qi);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            m[i][r] = cadd(cmul(make_float2(pr[r], pi[r]), xa[r]), cmul(make_float2(qr[r], qi[r]), xb[r]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();  // U0 is consumed; the plane region is free
+    if (sh.on) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int rb = sh.part + i * sh.q;
+        if (rb < g.n0b) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) lds[(16 * rb + 4 * grp + r) * g.PS + 16 * sh.cb + (lane & 15)] = m[i][r];
+        }
+      }
+    }
+    if (j + 1 < j1) w_load(a.T3, g, j + 1, i2, wsl, w);
+    __syncthreads();
+    plane_fft<-1>(g, lds);
+    plane_gather(a, g, lds, j, i2, tid, pq);
     __syncthreads();  // the gather is done with the plane
   }
 }
@@ -515,13 +646,12 @@ __device__ __forceinline__ void adj_map_load(const PlaneArgs& a, const Geo<N0, N
   if (i < 8 && rb < g.n0b && s < g.r0b) m.ring[k & 3] = frag_a<PREC>(a.U0SF, g.r0b, rb, s, lane);
 }
 
-// Adjoint plane kernel, two forms.  plane_adj_kernel (BF16-split plans) forms the coil map
-// before the transform, with U0 staged in the plane region, and holds P across it (the
-// transform then works in half-plane chunks).  plane_adj_late_kernel (FP32 plans) forms
-// each P tile after the transform where gx uses it, with U0 read from memory; its
-// transform holds whole passes.  Measured at 128 x 128 planes, the first is faster in
-// BF16-split (its matrix-core steps are short, so U0 read latency from memory shows) and
-// the second in FP32.
+// Adjoint plane kernel, two forms.  plane_adj_kernel (BF16-split plans of compile-time plane
+// sizes) forms the coil map before the transform, with U0 staged in the plane region, and
+// holds P across it.  plane_adj_late_kernel (FP32 plans, and run-time plane sizes) forms
+// each P tile after the transform where gx uses it, with U0 read from memory.  Measured at
+// 128 x 128 planes, the first is faster in BF16-split (its matrix-core steps are short, so U0
+// read latency from memory shows) and the second in FP32.
 template <int PREC, int N0, int N1, int RB, bool FULL = false>
 __global__ __launch_bounds__(PT) void plane_adj_kernel(PlaneArgs a) {
   __shared__ __align__(16) float2 lds[LDS_ELEMS];
@@ -531,7 +661,7 @@ __global__ __launch_bounds__(PT) void plane_adj_kernel(PlaneArgs a) {
   plane_block(ngrp, g.n2, i2, gi);
   const float2* xp = a.xt + (size_t)i2 * g.n0 * g.n1;
   const bool want_gx = FULL || a.gxpart != nullptr;  // FULL: gx and T3b both wanted, known at compile time
-  const Share sh = plane_share(g);
+  const Share sh = plane_share<RB == 0>(g);
   int zq[SCAT];  // sampled plane positions, the same for every coil
 #pragma unroll
   for (int k = 0; k < SCAT; ++k) zq[k] = (int)threadIdx.x + k * PT < a.L ? a.pos[threadIdx.x + k * PT] : -1;
@@ -555,7 +685,7 @@ __global__ __launch_bounds__(PT) void plane_adj_kernel(PlaneArgs a) {
     f32x4 pr[8], pi[8];
     if (want_gx) {
       WPrefetch w;
-      w_load(a, g, j, i2, w_slots<PREC>(g, tid), w);  // offsets recomputed: no registers held across coils
+      w_load(a.T3, g, j, i2, w_slots<PREC>(g, tid), w);  // offsets recomputed: no registers held across coils
       // B c recomputed, with U0 and U1 carrying the output chessboard sign: P' = s P
       coil_map<PREC, false>(a.U0SF, a.U1TSF, g, lds, sh, lane, tid, w, pr, pi);
     }
@@ -583,7 +713,7 @@ __global__ __launch_bounds__(PT) void plane_adj_kernel(PlaneArgs a) {
     __syncthreads();
     // compile-time plane sizes: whole passes over wave-owned lines (fewer barriers)
     // last pass two line steps at a time: the map and gx stay in registers across it
-    plane_fft<(N0 != 0 ? FFT_CHUNK_FWD : FFT_CHUNK_ADJ), N0, N1, RB, 2>(a, g, lds, +1);
+    plane_fft<1, N0, N1, RB, 2>(g, lds);
     // g = s g' (g' the plane after the transform, s the output chessboard sign):
     // gx += conj(P) s g' = conj(P') g' in registers (P' = s P from the signed factors);
     // h = conj(x) s g' = conj(s x) g' into the plane, s x being what xt holds.  x in two
@@ -657,7 +787,7 @@ __global__ __launch_bounds__(PT) void plane_adj_late_kernel(PlaneArgs a) {
   plane_block(ngrp, g.n2, i2, gi);
   const float2* xp = a.xt + (size_t)i2 * g.n0 * g.n1;
   const bool want_gx = FULL || a.gxpart != nullptr;  // FULL: gx and T3b both wanted, known at compile time
-  const Share sh = plane_share(g);
+  const Share sh = plane_share<RB == 0>(g);
   int zq[SCAT];  // sampled plane positions, the same for every coil
 #pragma unroll
   for (int k = 0; k < SCAT; ++k) zq[k] = (int)threadIdx.x + k * PT < a.L ? a.pos[threadIdx.x + k * PT] : -1;
@@ -680,7 +810,7 @@ __global__ __launch_bounds__(PT) void plane_adj_late_kernel(PlaneArgs a) {
     }
     if (want_gx) {
       WPrefetch w;
-      w_load(a, g, j, i2, w_slots<PREC>(g, tid), w);  // offsets recomputed: no registers held across coils
+      w_load(a.T3, g, j, i2, w_slots<PREC>(g, tid), w);  // offsets recomputed: no registers held across coils
       w_store<PREC>(g, lds, tid, w);              // the stage region is free (previous coil done)
     }
     // zero-filled scatter (with the chessboard sign)
@@ -705,7 +835,7 @@ __global__ __launch_bounds__(PT) void plane_adj_late_kernel(PlaneArgs a) {
       lds[k0 * g.PS + k1] = v;
     }
     __syncthreads();
-    plane_fft<FFT_CHUNK_FWD>(a, g, lds, +1);  // nothing held across it but gx: whole passes
+    plane_fft<1>(g, lds);  // nothing held across it but gx: whole passes
     // g = s g' (g' the plane after the transform, s the output chessboard sign):
     // gx += conj(P) s g' in registers; h = conj(x) s g' = conj(s x) g' into the plane, s x
     // being what xt holds.  Each P tile is formed just before its use.
@@ -823,83 +953,97 @@ constexpr int LT = 32;     // lines per workgroup
 constexpr int LNT = 256;   // threads
 constexpr int LMAXN = 256; // max n2 on this path
 
-template <int N2>
-__device__ __forceinline__ void line_fft(const LineArgs& a, float2* tile, const float2* tw, int n, int dir) {
+// LDS of a line workgroup with a run-time readout: the tile, the twiddles, the reduction.
+constexpr int LU = 8;      // elements per thread whose loads are issued together
+__host__ __device__ inline size_t line_lds_bytes(int n2) {
+  return (size_t)LNT * sizeof(double) + ((size_t)n2 * (LT + 1) + n2) * sizeof(float2);
+}
+
+// A compile-time readout (128) or a run-time one: two radices of at most 16 where it splits
+// so (nearly every size up to 256), else radix by radix.  Two radices took line_fwd from
+// 54 to 25 us at a readout of 100 (20 coils, 1536 lines).
+template <int N2, int DIR>
+__device__ __forceinline__ void line_fft(const LineArgs& a, float2* tile, const float2* tw, int n) {
   if constexpr (N2 != 0) {
-    lds_fft_ct<N2, LNT, N2 * LT>(tile, LT, 1, LT + 1, tw, dir);
+    lds_fft_ct<N2, LNT, N2 * LT>(tile, LT, 1, LT + 1, tw, DIR);
+  } else if (a.two0) {
+    lds_fft_two_radix<DIR, LT, LNT>(tile, LT + 1, n, a.two0, a.two1, tw);
   } else {
     LdsLines tg{LT, 1, LT + 1};
-    lds_fft_lines<LNT, LMAXN * LT / 2>(tile, tg, n, a.rad2, a.nrad2, tw, dir);
+    lds_fft_lines<LNT, LMAXN * LT / 2>(tile, tg, n, a.rad2, a.nrad2, tw, DIR);
   }
 }
 
+// What a line workgroup does with its lines: their samples (E, or the weighted residual) out;
+// the weighted residual taken back along the readout (the transfer layout); or both.
 template <int N2>
 __global__ __launch_bounds__(LNT) void line_fwd_kernel(LineArgs a) {
-  __shared__ float2 tile[(N2 ? N2 : LMAXN) * (LT + 1)];  // sized to the readout: more workgroups per CU
-  __shared__ float2 tw[N2 ? N2 : LMAXN];
-  __shared__ double red[LNT];
+  extern __shared__ double lds_line[];
   const int lblocks = (a.L + LT - 1) / LT;
   const int j = blockIdx.x / lblocks, l0 = (blockIdx.x % lblocks) * LT;
   const int n = N2 ? N2 : a.n2, ES = LT + 1;
+  double* red = lds_line;
+  float2* tile = reinterpret_cast<float2*>(lds_line + LNT);
+  float2* tw = tile + n * ES;
   for (int e = threadIdx.x; e < n; e += LNT) tw[e] = a.tw2[e];
-  // With the compile-time readout, the thread's Z values are loaded together, unguarded (lines
-  // past L read line L - 1 and are zeroed), before any is stored; then the measured samples of
-  // its outputs, ahead of the transform.
-  constexpr int YQ = N2 ? N2 * LT / LNT : 1;
-  if constexpr (N2 != 0) {
+  // the thread's Z values loaded together, unguarded (lines past L read line L - 1 and are
+  // zeroed), before any is stored
+  constexpr int YQ = N2 ? N2 * LT / LNT : LU;
+  const int total = n * LT;
+  for (int e0 = threadIdx.x; e0 < total; e0 += YQ * LNT) {
     float2 zv[YQ];
 #pragma unroll
     for (int q = 0; q < YQ; ++q) {
-      const int e = threadIdx.x + q * LNT, i2 = e / LT, l = e % LT;
+      const int e = min(e0 + q * LNT, total - 1), i2 = e / LT, l = e % LT;
       zv[q] = a.Z[((size_t)j * n + i2) * a.L + min(l0 + l, (int)a.L - 1)];
     }
 #pragma unroll
     for (int q = 0; q < YQ; ++q) {
-      const int e = threadIdx.x + q * LNT, i2 = e / LT, l = e % LT;
+      const int e = e0 + q * LNT, i2 = e / LT, l = e % LT;
+      if (!N2 && e >= total) continue;
       const float m = l0 + l < a.L ? ((i2 & 1) ? -1.f : 1.f) : 0.f;
       tile[i2 * ES + l] = make_float2(zv[q].x * m, zv[q].y * m);
     }
-  } else {
-    for (int e = threadIdx.x; e < n * LT; e += LNT) {
-      const int i2 = e / LT, l = e % LT;
-      float2 v = make_float2(0.f, 0.f);
-      if (l0 + l < a.L) v = a.Z[((size_t)j * n + i2) * a.L + l0 + l];
-      if (i2 & 1) v = make_float2(-v.x, -v.y);
-      tile[i2 * ES + l] = v;
-    }
   }
+  // The lines of the workgroup are one contiguous run of samples: element e of it is sample
+  // m0 + e.  With the compile-time readout the measured samples of the thread's outputs are
+  // loaded ahead of the transform.
+  const size_t m0 = (size_t)l0 * n;
+  const int valid = (int)min((size_t)total, (size_t)a.M - m0);  // elements of lines below L
+  const float2* y = a.y ? a.y + (size_t)j * a.M + m0 : nullptr;
   float2 yv[YQ];
   if constexpr (N2 != 0) {
-    if (a.y) {
+    if (y) {
 #pragma unroll
-      for (int q = 0; q < YQ; ++q) {
-        const int e = threadIdx.x + q * LNT, l = e / N2, k2 = e % N2;
-        yv[q] = a.y[(size_t)j * a.M + (size_t)min(l0 + l, (int)a.L - 1) * N2 + k2];
-      }
+      for (int q = 0; q < YQ; ++q) yv[q] = y[min((int)threadIdx.x + q * LNT, valid - 1)];
     }
   }
   __syncthreads();
-  line_fft<N2>(a, tile, tw, n, -1);
+  line_fft<N2, -1>(a, tile, tw, n);
   double acc = 0.0;
+  const FastDiv fn = fast_div((uint32_t)n);
+  for (int e0 = threadIdx.x; e0 < total; e0 += YQ * LNT) {
+    if constexpr (N2 == 0) {
+      if (y) {
 #pragma unroll
-  for (int q = 0; q < (N2 ? YQ : 1); ++q)
-  for (int e = threadIdx.x + q * LNT; e < n * LT; e += (N2 ? n * LT : LNT)) {
-    const int l = e / n, k2 = e % n;
-    if (l0 + l >= a.L) continue;
-    float2 v = tile[k2 * ES + l];
-    const float s = (k2 & 1) ? -a.gscale : a.gscale;
-    v = cscale(v, s);
-    const size_t m = (size_t)(l0 + l) * n + k2;
-    const size_t o = (size_t)j * a.M + m;
-    if (a.y) {
-      const float2 d = csub(v, N2 ? yv[q] : a.y[o]);
-      const float wm = a.w ? a.w[m] : 1.0f;
-      acc += (double)wm * ((double)d.x * d.x + (double)d.y * d.y);
-      const float2 r = cscale(d, wm);
-      if (a.out) a.out[o] = r;
-      if (a.Zw) tile[k2 * ES + l] = (k2 & 1) ? make_float2(-r.x, -r.y) : r;  // each entry is this thread's
-    } else {
-      a.out[o] = v;
+        for (int q = 0; q < YQ; ++q) yv[q] = y[min(e0 + q * LNT, valid - 1)];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < YQ; ++q) {
+      const int e = e0 + q * LNT;
+      if (e >= valid) continue;
+      const int l = N2 ? e / n : (int)fdiv(e, fn), k2 = e - l * n;
+      const size_t o = (size_t)j * a.M + m0 + e;
+      float2 v = cscale(tile[k2 * ES + l], (k2 & 1) ? -a.gscale : a.gscale);
+      if (a.y || a.w) {  // the residual against y (0 if there is none), weighted
+        const float2 d = a.y ? csub(v, yv[q]) : v;
+        const float wm = a.w ? a.w[m0 + e] : 1.0f;
+        acc += (double)wm * ((double)d.x * d.x + (double)d.y * d.y);
+        v = cscale(d, wm);
+      }
+      if (a.out) a.out[o] = v;
+      if (a.Zw) tile[k2 * ES + l] = (k2 & 1) ? make_float2(-v.x, -v.y) : v;  // each entry is this thread's
     }
   }
   if (a.part) {
@@ -916,8 +1060,8 @@ __global__ __launch_bounds__(LNT) void line_fwd_kernel(LineArgs a) {
     // are on chip (the adjoint's first step, as the adjoint line kernel computes it, without
     // the adjoint's scale, which the adjoint applies at its ends)
     if (!a.part) __syncthreads();
-    line_fft<N2>(a, tile, tw, n, +1);
-    for (int e = threadIdx.x; e < n * LT; e += LNT) {
+    line_fft<N2, 1>(a, tile, tw, n);
+    for (int e = threadIdx.x; e < total; e += LNT) {
       const int i2 = e / LT, l = e % LT;
       if (l0 + l >= a.L) continue;
       const float2 v = tile[i2 * ES + l];
@@ -928,42 +1072,39 @@ __global__ __launch_bounds__(LNT) void line_fwd_kernel(LineArgs a) {
 
 template <int N2>
 __global__ __launch_bounds__(LNT) void line_adj_kernel(LineArgs a) {
-  __shared__ float2 tile[(N2 ? N2 : LMAXN) * (LT + 1)];
-  __shared__ float2 tw[N2 ? N2 : LMAXN];
+  extern __shared__ double lds_line[];
   const int lblocks = (a.L + LT - 1) / LT;
   const int j = blockIdx.x / lblocks, l0 = (blockIdx.x % lblocks) * LT;
   const int n = N2 ? N2 : a.n2, ES = LT + 1;
+  float2* tile = reinterpret_cast<float2*>(lds_line + LNT);
+  float2* tw = tile + n * ES;
   for (int e = threadIdx.x; e < n; e += LNT) tw[e] = a.tw2[e];
-  if constexpr (N2 != 0) {
-    // the thread's samples loaded together and unguarded (lines past L read line L - 1 and
-    // are zeroed), as in the forward line kernel
-    constexpr int YQ = N2 * LT / LNT;
+  // the thread's samples loaded together and unguarded (past the last sample the last is read
+  // and zeroed), as in the forward line kernel
+  constexpr int YQ = N2 ? N2 * LT / LNT : LU;
+  const int total = n * LT;
+  const size_t m0 = (size_t)l0 * n;
+  const int valid = (int)min((size_t)total, (size_t)a.M - m0);
+  const float2* y = a.yin + (size_t)j * a.M + m0;
+  const FastDiv fn = fast_div((uint32_t)n);
+  for (int e0 = threadIdx.x; e0 < total; e0 += YQ * LNT) {
     float2 yv[YQ];
 #pragma unroll
-    for (int q = 0; q < YQ; ++q) {
-      const int e = threadIdx.x + q * LNT, l = e / N2, k2 = e % N2;
-      yv[q] = a.yin[(size_t)j * a.M + (size_t)min(l0 + l, (int)a.L - 1) * N2 + k2];
-    }
+    for (int q = 0; q < YQ; ++q) yv[q] = y[min(e0 + q * LNT, valid - 1)];
 #pragma unroll
     for (int q = 0; q < YQ; ++q) {
-      const int e = threadIdx.x + q * LNT, l = e / N2, k2 = e % N2;
-      const float m = l0 + l < a.L ? ((k2 & 1) ? -1.f : 1.f) : 0.f;
+      const int e = e0 + q * LNT;
+      if (!N2 && e >= total) continue;
+      const int l = N2 ? e / n : (int)fdiv(e, fn), k2 = e - l * n;
+      const float m = e < valid ? ((k2 & 1) ? -1.f : 1.f) : 0.f;
       tile[k2 * ES + l] = make_float2(yv[q].x * m, yv[q].y * m);
-    }
-  } else {
-    for (int e = threadIdx.x; e < n * LT; e += LNT) {
-      const int l = e / n, k2 = e % n;
-      float2 v = make_float2(0.f, 0.f);
-      if (l0 + l < a.L) v = a.yin[(size_t)j * a.M + (size_t)(l0 + l) * n + k2];
-      if (k2 & 1) v = make_float2(-v.x, -v.y);
-      tile[k2 * ES + l] = v;
     }
   }
   __syncthreads();
-  line_fft<N2>(a, tile, tw, n, +1);
+  line_fft<N2, 1>(a, tile, tw, n);
   float s = a.gscale * a.alpha;
   if (a.scale_dev) s *= *a.scale_dev;
-  for (int e = threadIdx.x; e < n * LT; e += LNT) {
+  for (int e = threadIdx.x; e < total; e += LNT) {
     const int i2 = e / LT, l = e % LT;
     if (l0 + l >= a.L) continue;
     const float2 v = tile[i2 * ES + l];
@@ -1034,11 +1175,20 @@ void adj_launch(dim3 grid, dim3 block, const PlaneArgs& a, hipStream_t st) {
       hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, RB3, true, true>), grid, block, 0, st, a);
     else if (rb3 && full) hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, RB3, true>), grid, block, 0, st, a);
     else if (rb3) hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, RB3>), grid, block, 0, st, a);
+    else if (full && N0 == 0)  // run-time plane sizes; at 128 x 128 it would spill
+      hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0, N0 == 0>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0>), grid, block, 0, st, a);
   } else {
-    if (rb3 && full) hipLaunchKernelGGL((plane_adj_kernel<PREC, N0, N1, RB3, true>), grid, block, 0, st, a);
-    else if (rb3) hipLaunchKernelGGL((plane_adj_kernel<PREC, N0, N1, RB3>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((plane_adj_kernel<PREC, N0, N1, 0>), grid, block, 0, st, a);
+    if constexpr (N0 == 0) {
+      // run-time plane sizes: the map held across the transform spilled 126 registers (128 x 96
+      // planes 412 -> 296 us with the late form, 48 x 128 265 -> 166, 96 x 80 106 -> 78)
+      if (full) hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0>), grid, block, 0, st, a);
+    } else {
+      if (rb3 && full) hipLaunchKernelGGL((plane_adj_kernel<PREC, N0, N1, RB3, true>), grid, block, 0, st, a);
+      else if (rb3) hipLaunchKernelGGL((plane_adj_kernel<PREC, N0, N1, RB3>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((plane_adj_kernel<PREC, N0, N1, 0>), grid, block, 0, st, a);
+    }
   }
 }
 
@@ -1066,10 +1216,28 @@ hipError_t plane_launch_prec(const PlaneArgs& a, bool adj, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int PREC>
+hipError_t jvp_launch_prec(const PlaneArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)(a.n2 * ((a.J + a.G - 1) / a.G))), block(PT);
+  if (a.n0 == 128 && a.n1 == 128) {
+    if (a.r0p == 48 && a.r1p == 48)
+      hipLaunchKernelGGL((plane_jvp_kernel<PREC, 128, 128, 3>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((plane_jvp_kernel<PREC, 128, 128, 0>), grid, block, 0, st, a);
+  } else {
+    hipLaunchKernelGGL((plane_jvp_kernel<PREC, 0, 0, 0>), grid, block, 0, st, a);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t plane_fwd_launch(const PlaneArgs& a, hipStream_t st) {
   return a.precision == 1 ? plane_launch_prec<1>(a, false, st) : plane_launch_prec<0>(a, false, st);
+}
+
+hipError_t plane_jvp_launch(const PlaneArgs& a, hipStream_t st) {
+  return a.precision == 1 ? jvp_launch_prec<1>(a, st) : jvp_launch_prec<0>(a, st);
 }
 
 hipError_t plane_adj_launch(const PlaneArgs& a, hipStream_t st) {
@@ -1080,15 +1248,17 @@ int line_blocks(int J, int64_t L) { return (int)(J * ((L + LT - 1) / LT)); }
 
 hipError_t line_fwd_launch(const LineArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)line_blocks(a.J, a.L)), block(LNT);
-  if (a.n2 == 128) hipLaunchKernelGGL(line_fwd_kernel<128>, grid, block, 0, st, a);
-  else hipLaunchKernelGGL(line_fwd_kernel<0>, grid, block, 0, st, a);
+  const size_t lds = line_lds_bytes(a.n2);
+  if (a.n2 == 128) hipLaunchKernelGGL(line_fwd_kernel<128>, grid, block, lds, st, a);
+  else hipLaunchKernelGGL(line_fwd_kernel<0>, grid, block, lds, st, a);
   return hipGetLastError();
 }
 
 hipError_t line_adj_launch(const LineArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)line_blocks(a.J, a.L)), block(LNT);
-  if (a.n2 == 128) hipLaunchKernelGGL(line_adj_kernel<128>, grid, block, 0, st, a);
-  else hipLaunchKernelGGL(line_adj_kernel<0>, grid, block, 0, st, a);
+  const size_t lds = line_lds_bytes(a.n2);
+  if (a.n2 == 128) hipLaunchKernelGGL(line_adj_kernel<128>, grid, block, lds, st, a);
+  else hipLaunchKernelGGL(line_adj_kernel<0>, grid, block, lds, st, a);
   return hipGetLastError();
 }
 
