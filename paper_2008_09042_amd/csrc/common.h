@@ -86,6 +86,10 @@ struct FftAxisArgs {
   // masked round trip (dir = -1): the forward transform, the points with in_inv < 0 set to
   // zero, and the inverse, in one pass; sizes of the two-radix kernel only (fft_tr_supported)
   int round_trip;
+  // with the samples out, or in a round trip: the weighted residual w (E - y) against the
+  // measured samples in their place, and the FP64 loss partials sum w |E - y|^2, one per
+  // workgroup (two-radix kernel; out_samples may be null with the loss alone wanted)
+  const float2* res_y; const float* res_w; double* res_part;
   int64_t coil_elems, nsamples;  // N, M
   uint32_t coil_magic, coil_shift;  // multiply-high division by N (set by fft_axis_launch)
   int lines;              // lines per workgroup (set by fft_axis_launch)

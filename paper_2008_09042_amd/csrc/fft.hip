@@ -339,7 +339,7 @@ hipError_t tr_prepare(FftAxisArgs a, int smp, int r0, int r1, FftLaunch& out) {
   out.big = nb > 16;
   out.twl = false;
   // the kernel variants of TR_VARIANTS; the fused reads and writes fix the direction
-  static const int var[9] = {0, 2, 3, -1, 4, 5, 6, 7, 8};
+  static const int var[11] = {0, 2, 3, -1, 4, 5, 6, 7, 8, 9, 10};
   out.variant = smp == 0 && a.dir > 0 ? 1 : var[smp];
   out.threads = threads;
   out.blocks = blocks(T);
@@ -395,7 +395,14 @@ hipError_t fft_axis_prepare(const FftAxisArgs& args, FftLaunch& out) {
     if (!a.in_inv || a.in_samples || a.out_inv || a.premul || a.win || a.crop_out || a.dir > 0 ||
         a.outer * a.inner > 0x7fffffffLL || !tr_radices(n, r0, r1))
       return hipErrorInvalidValue;
-    return tr_prepare(a, 8, r0, r1, out);
+    return tr_prepare(a, a.res_y ? 10 : 8, r0, r1, out);
+  }
+  if (a.res_y) {
+    int r0, r1;
+    if (!a.out_inv || a.in_inv || a.premul || a.win || a.crop_out || a.dir > 0 || a.outer * a.inner > 0x7fffffffLL ||
+        !tr_radices(n, r0, r1) || r0 > 16)
+      return hipErrorInvalidValue;
+    return tr_prepare(a, 9, r0, r1, out);
   }
   if (smp <= 2 || (a.win || a.crop_out)) {
     int r0, r1;

@@ -76,11 +76,59 @@ struct TrLine {
     } else {
       in = out = o * a.n * a.inner + t;
       if (SMP == 0 && a.premul) pm = (o - fdiv(o, a.tr_coil) * a.tr_coil.d) * a.n;
-      if constexpr (SMP == 1 || SMP == 2 || SMP == 8) {
+      if constexpr (SMP == 1 || SMP == 2 || SMP >= 8) {
         const int64_t j = fdiv(o, a.tr_coil);
         pm = in - j * a.coil_elems;
         smp = j * a.nsamples;
       }
+    }
+  }
+
+  // the samples of points [q, q + C) of offsets off(r), -1 where unsampled (9, 10)
+  template <int R, class Off>
+  __device__ __forceinline__ void samples(int (&m)[R], Off off, int q, int C) const {
+    const int32_t* inv = (SMP == 9 ? a.out_inv : a.in_inv) + pm;
+#pragma unroll
+    for (int r = q; r < R && r < q + C; ++r) m[r] = inv[off(r)];
+  }
+
+  // all of them ahead of the transform that forms the points, where they fit the registers
+  template <int R, class Off>
+  __device__ __forceinline__ void samples_ahead(int (&m)[R], Off off) const {
+    if constexpr (R <= 16) {
+      samples(m, off, 0, R);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // v[r] = w (E - y) for E = scale v at the sampled points, 0 elsewhere, and acc += w |E - y|^2
+  // (FP64); use(r, m) sees v[r] as sample m, m < 0 where the point is unsampled (9, 10)
+  template <int R, class Off, class Use>
+  __device__ __forceinline__ void residual(float2 (&v)[R], int (&m)[R], float scale, double& acc, Off off, Use use) const {
+    const float2* ys = a.res_y + smp;
+    const float* ws = a.res_w ? a.res_w : (const float*)a.res_y;  // unweighted: loaded and not used
+    const bool weighted = a.res_w;
+    constexpr int C = R > 16 ? 4 : 8;  // points whose loads are in flight together: more would spill
+#pragma unroll
+    for (int q = 0; q < R; q += C) {
+      float2 y[C];
+      float w[C];
+      if constexpr (R > 16) samples(m, off, q, C);
+#pragma unroll
+      for (int r = q; r < R && r < q + C; ++r) {
+        y[r - q] = ys[max(m[r], 0)];
+        w[r - q] = ws[max(m[r], 0)];
+      }
+#pragma unroll
+      for (int r = q; r < R && r < q + C; ++r) {
+        const bool on = m[r] >= 0;
+        const float dx = on ? v[r].x * scale - y[r - q].x : 0.f, dy = on ? v[r].y * scale - y[r - q].y : 0.f;
+        const float wr = on ? (weighted ? w[r - q] : 1.f) : 0.f;
+        acc += (double)wr * ((double)dx * dx + (double)dy * dy);
+        v[r] = make_float2(dx * wr, dy * wr);
+        use(r, m[r]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
@@ -231,31 +279,41 @@ __device__ __forceinline__ void tr_pass0(const FftAxisArgs& a, float2* lds, cons
   }
 }
 
-// The middle of a masked round trip (8): pass 1 of the forward transform, the mask, and pass
-// 0 of the inverse, whose inputs j' + r R0 are the outputs that the thread holds.  The outputs
-// go back to the LDS row that the thread read, so no barrier parts the two.
+// Offset of output r of butterfly j of pass 1 within the line's image (below 2^31 points)
 template <int R>
+__device__ __forceinline__ uint32_t tr_out_off(int j, int r, int nb, int n, int64_t st) {
+  if constexpr (R % 2 == 0) return (uint32_t)(j + ((r + R / 2) % R) * nb) * (uint32_t)st;
+  const int k = j + r * nb + n / 2;
+  return (uint32_t)(k >= n ? k - n : k) * (uint32_t)st;
+}
+
+// The middle of a round trip: pass 1 of the forward transform, the mask (8) or the weighted
+// residual against the measured samples (10), zero where unsampled, and pass 0 of the
+// inverse, whose inputs j' + r R0 are the outputs that the thread holds.  The outputs go back
+// to the LDS row that the thread read, so no barrier parts the two.
+template <int SMP, int R>
 __device__ __forceinline__ void tr_mask_pass(const FftAxisArgs& a, float2* lds, const float2* tw, const TrLds& s,
-                                             uint32_t o0, uint32_t t0) {
+                                             uint32_t o0, uint32_t t0, double& acc) {
   const int nb = a.tr_r0.d, n = (int)a.n, total = nb << a.tr_lshift;
   for (int bf = threadIdx.x; bf < total; bf += blockDim.x) {
     int l, j;
     tr_coords(a, bf, a.tr_r0, l, j);
+    auto off = [&](int r) { return tr_out_off<R>(j, r, nb, n, a.inner); };
+    int m[R];
+    if constexpr (SMP == 10) TrLine<SMP>(a, o0, t0, l).samples_ahead(m, off);
     float2* d = lds + l * s.LL + j * s.RP;
     float2 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = d[r * s.JP];
     tr_twiddle<-1, R>(v, tw, j);
     tr_dft<R, -1>(v);
-    const TrLine<8> line(a, o0, t0, l);
-    const int64_t b0 = j * line.st, step = nb * line.st;
-    if constexpr (R % 2 == 0) {
-      line.mask(v, [&](int r) -> int64_t { return b0 + ((r + R / 2) % R) * step; });
+    const TrLine<SMP> line(a, o0, t0, l);
+    if constexpr (SMP == 8) {
+      line.mask(v, off);
     } else {
-      line.mask(v, [&](int r) -> int64_t {
-        const int k = j + r * nb + n / 2;
-        return (int64_t)(k >= n ? k - n : k) * line.st;
-      });
+      double sum = 0.0;
+      line.residual(v, m, rsqrtf((float)n), sum, off, [](int, int) {});
+      if (line.valid) acc += sum;
     }
     tr_dft<R, 1>(v);
 #pragma unroll
@@ -267,20 +325,32 @@ __device__ __forceinline__ void tr_mask_pass(const FftAxisArgs& a, float2* lds, 
 // from the next butterfly's, jp from each other.
 template <int SMP, int DIR, int R>
 __device__ __forceinline__ void tr_pass1(const FftAxisArgs& a, const float2* lds, const float2* tw, const FastDiv& fnb,
-                                         int ll, int rp, int jp, uint32_t o0, uint32_t t0, float scale) {
+                                         int ll, int rp, int jp, uint32_t o0, uint32_t t0, float scale,
+                                         double& acc) {
   const int nb = fnb.d, n = (int)a.n, total = nb << a.tr_lshift;
   for (int bf = threadIdx.x; bf < total; bf += blockDim.x) {
     int l, j;
     tr_coords(a, bf, fnb, l, j);
+    const TrLine<SMP> line(a, o0, t0, l);
+    int m[R];
+    auto moff = [&](int r) { return tr_out_off<R>(j, r, nb, n, line.st); };
+    if constexpr (SMP == 9) line.samples_ahead(m, moff);
     const float2* d = lds + l * ll + j * rp;
     float2 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = d[r * jp];
     tr_twiddle<DIR, R>(v, tw, j);
     tr_dft<R, DIR>(v);
-    const TrLine<SMP> line(a, o0, t0, l);
     const int64_t b0 = j * line.st, step = nb * line.st;
-    if constexpr (R % 2 == 0) {
+    if constexpr (SMP == 9) {
+      double sum = 0.0;
+      const bool keep = line.valid && a.out_samples;
+      float2* os = a.out_samples + line.smp;
+      line.residual(v, m, scale, sum, moff, [&](int r, int mr) {
+        if (mr >= 0 && keep) os[mr] = v[r];
+      });
+      if (line.valid) acc += sum;
+    } else if constexpr (R % 2 == 0) {
       line.store(v, scale, [&](int r) -> int { return j + ((r + R / 2) % R) * nb; },
                  [&](int r) -> int64_t { return b0 + ((r + R / 2) % R) * step; });
     } else {
@@ -327,8 +397,9 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
   }
 #undef TR_P0
   __syncthreads();
-  if constexpr (SMP == 8) {
-#define TR_M(R) case R: tr_mask_pass<R>(a, lds, tw, s, o0, t0); break;
+  double acc = 0.0;
+  if constexpr (SMP == 8 || SMP == 10) {
+#define TR_M(R) case R: tr_mask_pass<SMP, R>(a, lds, tw, s, o0, t0, acc); break;
     if constexpr (BIG) {
       switch (a.tr_r1.d) { TR_SMALL(TR_M) TR_LARGE(TR_M) default: break; }
     } else {
@@ -337,8 +408,8 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
 #undef TR_M
     __syncthreads();
     // pass 1 of the inverse: r1 butterflies of radix r0, rows and columns of the LDS tile swapped
-    const float scale = 1.f / (float)n;
-#define TR_P1(R) case R: tr_pass1<SMP, 1, R>(a, lds, tw, a.tr_r1, s.LL, s.JP, s.RP, o0, t0, scale); break;
+    const float scale = SMP == 8 ? 1.f / (float)n : rsqrtf((float)n);
+#define TR_P1(R) case R: tr_pass1<SMP, 1, R>(a, lds, tw, a.tr_r1, s.LL, s.JP, s.RP, o0, t0, scale, acc); break;
     if constexpr (BIG) {
       switch (a.tr_r0.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
     } else {
@@ -347,7 +418,7 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
 #undef TR_P1
   } else {
     const float scale = rsqrtf((float)n);
-#define TR_P1(R) case R: tr_pass1<SMP, DIR, R>(a, lds, tw, a.tr_r0, s.LL, s.RP, s.JP, o0, t0, scale); break;
+#define TR_P1(R) case R: tr_pass1<SMP, DIR, R>(a, lds, tw, a.tr_r0, s.LL, s.RP, s.JP, o0, t0, scale, acc); break;
     if constexpr (BIG) {
       switch (a.tr_r1.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
     } else {
@@ -355,16 +426,28 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
     }
 #undef TR_P1
   }
+  if constexpr (SMP == 9 || SMP == 10) {
+    // the workgroup's loss partial, by a fixed tree
+    __shared__ double red[TR_NT / 64];
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) acc += __shfl_down(acc, h);
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < (int)blockDim.x / 64; ++w) acc += red[w];
+      a.res_part[bid_in] = acc;
+    }
+  }
 }
 
 template <int SMP, int DIR, bool BIG>
-__global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 ? 1 : 0)) void fft_tr_kernel(FftAxisArgs a) {
+__global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 || (!BIG && SMP >= 9) ? 1 : 0)) void fft_tr_kernel(FftAxisArgs a) {
   fft_tr_body<SMP, DIR, BIG>(a, blockIdx.x, gridDim.x);
 }
 
 // Several passes (of different slices) in one launch, as fft_axis_multi_kernel below.
 template <int SMP, int DIR, bool BIG>
-__global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 ? 1 : 0)) void fft_tr_multi_kernel(FftMulti m) {
+__global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 || (!BIG && SMP >= 9) ? 1 : 0)) void fft_tr_multi_kernel(FftMulti m) {
   int i = 0;
   while (i + 1 < m.n && (int)blockIdx.x >= m.start[i + 1]) ++i;
   const FftAxisArgs a = m.d[i];
@@ -373,16 +456,19 @@ __global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 ? 1 : 0)) void fft
 
 }  // namespace
 
-// kernel variants: what the pass reads and writes (its direction follows, except for plain
+// Kernel variants: what the pass reads and writes (its direction follows, except for plain
 // passes)
-#define TR_VARIANTS(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1) F(8, 8, -1)
+#define TR_VARIANTS(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1) F(8, 8, -1) \
+  F(9, 9, -1) F(10, 10, -1)
+// the forward pass with the residual is prepared for radices up to 16 alone
+#define TR_BUILT(SMP) (BIG && SMP == 9 ? 10 : SMP)
 
 template <bool BIG>
 hipError_t tr_launch_one(const FftLaunch& l, hipStream_t st) {
   const dim3 gr((unsigned)l.blocks), bl((unsigned)l.threads);
   switch (l.variant) {
 #define TR_LAUNCH(I, SMP, DIR) \
-  case I: hipLaunchKernelGGL((fft_tr_kernel<SMP, DIR, BIG>), gr, bl, l.lds, st, l.a); break;
+  case I: hipLaunchKernelGGL((fft_tr_kernel<TR_BUILT(SMP), DIR, BIG>), gr, bl, l.lds, st, l.a); break;
     TR_VARIANTS(TR_LAUNCH)
 #undef TR_LAUNCH
     default: return hipErrorInvalidValue;
@@ -395,7 +481,7 @@ hipError_t tr_launch_many(int variant, int threads, size_t lds, const FftMulti& 
   const dim3 gr((unsigned)m.start[m.n]), bl((unsigned)threads);
   switch (variant) {
 #define TR_LAUNCH(I, SMP, DIR) \
-  case I: hipLaunchKernelGGL((fft_tr_multi_kernel<SMP, DIR, BIG>), gr, bl, lds, st, m); break;
+  case I: hipLaunchKernelGGL((fft_tr_multi_kernel<TR_BUILT(SMP), DIR, BIG>), gr, bl, lds, st, m); break;
     TR_VARIANTS(TR_LAUNCH)
 #undef TR_LAUNCH
     default: return hipErrorInvalidValue;

@@ -90,6 +90,8 @@ struct Plan {
   size_t off_admm = 0;           // SENSE / ADMM state (general path only)
   size_t off_adjp = 0;           // dense adjoint: row-chunk partials of the streaming kernel
   int part_blocks = 0;
+  int res_blocks = 0;            // Cartesian: workgroups of the pass that forms the residual itself (0: none does)
+  bool res_forward = false;      // the forward's last pass does too, not only the gradient's round trip
 
   size_t bytes_x() const { return (size_t)N * 8; }
   size_t bytes_c() const { return (size_t)J * (size_t)K * 8; }

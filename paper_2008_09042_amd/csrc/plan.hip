@@ -161,12 +161,21 @@ void tucker_adjoint_args(const Plan& p, const float2* h, float2* tA, float2* tB,
 template <typename T>
 T* wsp(void* ws, size_t off) { return reinterpret_cast<T*>(reinterpret_cast<char*>(ws) + off); }
 
+// Measured samples that a pass forms the weighted residual against (FftAxisArgs::res_y).
+struct ResidualOf {
+  const float2* y;
+  const float* w;
+  double* part;
+};
+
 // Centred unitary DFT over every axis of J stacked arrays of shape dims[0..nd).
 // Axis passes over [J][dims]; optionally the first pass reads the samples through the inverse
-// mask (in_samples [J][M]) and the last writes them (out_samples).
+// mask (in_samples [J][M]) and the last writes them (out_samples), or with `res` their weighted
+// residual (out_samples may then be null).
 hipError_t fft_dims(const Plan& p, const float2* src, float2* dst, int dir, const float2* premul, int nd,
                     const int64_t* dims, float2* const* tw, const int* nrad, const int (*radix)[12], hipStream_t st,
-                    const float2* in_samples = nullptr, float2* out_samples = nullptr) {
+                    const float2* in_samples = nullptr, float2* out_samples = nullptr,
+                    const ResidualOf* res = nullptr) {
   const float2* cur = src;
   for (int t = 0; t < nd; ++t) {
     const int d = nd - 1 - t;
@@ -192,9 +201,14 @@ hipError_t fft_dims(const Plan& p, const float2* src, float2* dst, int dir, cons
       a.in_mask = p.d_mask;
       a.in_lptr = p.d_lptr;
     }
-    if (t == nd - 1 && out_samples) {
+    if (t == nd - 1 && (out_samples || res)) {
       a.out_inv = p.d_inv;
       a.out_samples = out_samples;
+      if (res) {
+        a.res_y = res->y;
+        a.res_w = res->w;
+        a.res_part = res->part;
+      }
     }
     a.coil_elems = p.N;
     a.nsamples = p.M;
@@ -205,7 +219,8 @@ hipError_t fft_dims(const Plan& p, const float2* src, float2* dst, int dir, cons
   return hipSuccess;
 }
 
-// F^H P F over the image axes (P keeps the sampled points): the forward passes from the last
+// F^H P F over the image axes (P keeps the sampled points), or with `res` F^H of the weighted
+// residual w (P F - y): the forward passes from the last
 // axis to the second, the first axis there and back in one pass, and the inverse passes back.
 // One pass over memory fewer than the transform to the samples and the transform from them,
 // and no samples in between.
@@ -213,7 +228,8 @@ bool round_trip_supported(const Plan& p) {
   return p.sampling == MAXWELL_CARTESIAN && p.ndim >= 2 && p.d_inv && p.M > 0 &&
          (int64_t)p.J * p.N <= 0x7fffffffLL && fft_tr_supported(p.n[0]);
 }
-hipError_t fft_round_trip(const Plan& p, const float2* src, float2* dst, const float2* premul, hipStream_t st) {
+hipError_t fft_round_trip(const Plan& p, const float2* src, float2* dst, const float2* premul, hipStream_t st,
+                          const ResidualOf* res = nullptr) {
   const int nd = p.ndim;
   const float2* cur = src;
   for (int t = 0; t < 2 * nd - 1; ++t) {
@@ -237,12 +253,44 @@ hipError_t fft_round_trip(const Plan& p, const float2* src, float2* dst, const f
     if (d == 0) {
       a.round_trip = 1;
       a.in_inv = p.d_inv;
+      if (res) {
+        a.res_y = res->y;
+        a.res_w = res->w;
+        a.res_part = res->part;
+      }
     }
     hipError_t e = TIMED("fft_axis", fft_axis_launch(a, st));
     if (e != hipSuccess) return e;
     cur = dst;
   }
   return hipSuccess;
+}
+
+// Workgroups of the pass along the first axis, each with a loss partial, where it can form the
+// residual itself (and the partials fit the region of a sample array); else 0.
+int residual_pass_blocks(const Plan& p, bool& forward) {
+  forward = false;
+  if (!round_trip_supported(p)) return 0;
+  FftAxisArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = p.n[0];
+  a.inner = p.N / p.n[0];
+  a.outer = p.J;
+  a.outer_per_coil = 1;
+  a.dir = -1;
+  a.round_trip = 1;
+  a.in_inv = p.d_inv;
+  a.coil_elems = p.N;
+  a.nsamples = p.M;
+  FftLaunch l;
+  if (fft_axis_prepare(a, l) != hipSuccess || l.blocks > (int64_t)p.J * p.M) return 0;
+  // The forward alone (its last pass, samples out): 12.4 us for the pass at 256^2, 32 coils,
+  // against 10.8 and 5 of a residual kernel, which also is a launch.  With radices above 16 the
+  // residual's registers leave too few wavefronts: 177 us at 512^2, 128 coils, against 118 + 26.
+  // There and back it gains at every size, for the residual is neither written nor read
+  // (512^2, 128 coils: one pass of about 200 us against 118 + 26 + 122).
+  forward = !l.big;
+  return (int)l.blocks;
 }
 
 hipError_t fft_image(const Plan& p, const float2* src, float2* dst, int dir, const float2* premul,
@@ -857,7 +905,8 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
   // Gauss-Newton / CG: the JVP result, the work vectors r, d, q ([N | J K] each), and the
   // FP64 scalars and inner-product partials
   const size_t V = ((size_t)p.N + (size_t)p.J * (size_t)p.K) * 8;
-  p.off_U = off; off += al(JM);
+  p.off_U = off; off += al(JM);  // also the loss partials of a transform that forms the residual
+  p.res_blocks = p.fused ? 0 : residual_pass_blocks(p, p.res_forward);
   p.off_cg = off; off += 3 * al(V) + al(CG_SCALARS * sizeof(double)) + al(2 * DOT_BLOCKS * sizeof(double));
   if (!p.fused) {
     // SENSE / ADMM (general path): 5 + 2 ndim image-sized buffers (z0 twice, u0, two
@@ -1153,6 +1202,17 @@ hipError_t run_forward_loss(const Plan& p, const float2* x, const float2* c, con
     if (loss) return TIMED("reduce_loss", reduce_loss_launch(part, line_blocks(p.J, p.L), loss, st));
     return hipSuccess;
   }
+  if (p.res_forward) {  // the last pass writes the residual and its loss partials
+    float2* S = wsp<float2>(ws, p.off_S);
+    const ResidualOf res{y, p.d_w, wsp<double>(ws, p.off_U)};
+    if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
+    if ((e = fft_dims(p, S, wsp<float2>(ws, p.off_K), -1, x, p.ndim, p.n, p.d_tw, p.nrad, p.radix, st, nullptr, r,
+                      &res)) != hipSuccess)
+      return e;
+    const double* rp = res.part;
+    if (loss) return TIMED("reduce_loss", reduce_loss_launch(rp, p.res_blocks, loss, st));
+    return hipSuccess;
+  }
   float2* E = wsp<float2>(ws, p.off_E);
   if ((e = run_encode(p, x, c, E, ws, st)) != hipSuccess) return e;
   if (transfer && r && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer) {
@@ -1204,24 +1264,16 @@ static hipError_t adjoint_maps(const Plan& p, const float2* S, const float2* x, 
   return TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, x, p.N, p.J, alpha, scale_dev, gx, want_h ? 1 : 0, st));
 }
 
-hipError_t run_adjoint(const Plan& p, const float2* x, const float2* c, const float2* y, float alpha,
-                       const float* scale_dev, float2* gx, float2* gc, void* ws, hipStream_t st,
-                       bool maps_ready, bool transfer) {
-  if (p.fused) return fused_adjoint(p, x, c, y, alpha, scale_dev, gx, gc, ws, st, maps_ready, transfer);
+// gx and gc from g = F_s^H y in the K region and, unless stream_gx, the maps in the S region.
+// Dense basis: the streaming products form what they need of g themselves, the image
+// gradient (stream_gx) from maps that stay in registers, the coefficients' from
+// h = conj(x) (.) g.
+static hipError_t adjoint_finish(const Plan& p, const float2* x, const float2* c, float alpha, const float* scale_dev,
+                                 float2* gx, float2* gc, void* ws, hipStream_t st, bool stream_gx) {
   float2* S = wsp<float2>(ws, p.off_S);
   float2* Kb = wsp<float2>(ws, p.off_K);
-  const bool ordered = transfer && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer;
-  const bool dense = p.basis_kind == MAXWELL_BASIS_DENSE;
-  // dense basis: the streaming products form what they need of g = F_s^H y themselves, the
-  // image gradient from maps that stay in registers (unless this call has them already), the
-  // coefficients' from h = conj(x) (.) g
-  const bool stream_gx = gx && dense && p.stream_apply && !maps_ready;
-  const bool stream_gc = gc && dense && p.stream_adj;
+  const bool stream_gc = gc && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_adj;
   hipError_t e;
-  if (gx && !maps_ready && !stream_gx) {
-    if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
-  }
-  if ((e = adjoint_transform(p, y, alpha, scale_dev, ws, st, ordered)) != hipSuccess) return e;
   if (stream_gx) {
     e = TIMED("dense_gx", stream_gx_launch(p.dense, p.N, p.K, c, p.J, p.precision, Kb, alpha, scale_dev, gx, st));
     if (e != hipSuccess) return e;
@@ -1241,6 +1293,21 @@ hipError_t run_adjoint(const Plan& p, const float2* x, const float2* c, const fl
   return hipSuccess;
 }
 
+hipError_t run_adjoint(const Plan& p, const float2* x, const float2* c, const float2* y, float alpha,
+                       const float* scale_dev, float2* gx, float2* gc, void* ws, hipStream_t st,
+                       bool maps_ready, bool transfer) {
+  if (p.fused) return fused_adjoint(p, x, c, y, alpha, scale_dev, gx, gc, ws, st, maps_ready, transfer);
+  float2* S = wsp<float2>(ws, p.off_S);
+  const bool ordered = transfer && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer;
+  const bool stream_gx = gx && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_apply && !maps_ready;
+  hipError_t e;
+  if (gx && !maps_ready && !stream_gx) {
+    if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
+  }
+  if ((e = adjoint_transform(p, y, alpha, scale_dev, ws, st, ordered)) != hipSuccess) return e;
+  return adjoint_finish(p, x, c, alpha, scale_dev, gx, gc, ws, st, stream_gx);
+}
+
 hipError_t run_grad(const Plan& p, const float2* x, const float2* c, const float2* y, float2* gx, float2* gc,
                     double* loss, void* ws, hipStream_t st) {
   const bool want = gx || gc;
@@ -1251,8 +1318,17 @@ hipError_t run_grad(const Plan& p, const float2* x, const float2* c, const float
               : p.fused            ? wsp<float2>(ws, p.off_Z)
               : p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer ? wsp<float2>(ws, p.off_Ys)
                                    : wsp<float2>(ws, p.off_E);
-  hipError_t e = run_forward_loss(p, x, c, y, r, loss, ws, st, true);
-  if (e != hipSuccess) return e;
+  hipError_t e;
+  if (want && p.res_blocks) {  // the first axis there and back around the residual, no samples in between
+    float2 *S = wsp<float2>(ws, p.off_S), *Kb = wsp<float2>(ws, p.off_K);
+    const ResidualOf res{y, p.d_w, wsp<double>(ws, p.off_U)};
+    if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
+    if ((e = fft_round_trip(p, S, Kb, x, st, &res)) != hipSuccess) return e;
+    const double* rp = res.part;
+    if (loss && (e = TIMED("reduce_loss", reduce_loss_launch(rp, p.res_blocks, loss, st))) != hipSuccess) return e;
+    return adjoint_finish(p, x, c, 2.0f, nullptr, gx, gc, ws, st, false);
+  }
+  if ((e = run_forward_loss(p, x, c, y, r, loss, ws, st, true)) != hipSuccess) return e;
   if (!want) return hipSuccess;
   return run_adjoint(p, x, c, r, 2.0f, nullptr, gx, gc, ws, st, true, true);
 }
