@@ -54,6 +54,7 @@ struct Plan {
   bool mode3_direct = false;   // dedicated third-mode product kernels (r2 <= 64)
   const void *U2F = nullptr, *U2CF = nullptr;
   // dedicated core contraction kernels (Tucker basis, J <= 64)
+  bool tucker_rows = false;      // general path: the products next to the coil images as streams
   bool core_direct = false;
   CoreGeom cg{};
   uint16_t* d_core_split = nullptr;  // BF16-split core planes (BF16_SPLIT plans only)

@@ -24,6 +24,7 @@
 #include "solver.h"
 #include "admm.h"
 #include "skinny.h"
+#include "tucker_stream.h"
 #include "plan.h"
 #include "tune.h"
 
@@ -729,6 +730,8 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
       return hip_err(e);
     if ((e = hipStreamSynchronize(0)) != hipSuccess) return hip_err(e);
   }
+  p.tucker_rows = p.basis_kind == MAXWELL_BASIS_TUCKER && !p.fused &&
+                  tucker_rows_supported(p.n[0], p.n[1], p.n[2], p.r[1], p.r[2], p.precision == MAXWELL_BF16_SPLIT);
   if (p.basis_kind == MAXWELL_BASIS_TUCKER && core_supported(p.J)) {
     p.core_direct = true;
     p.cg = core_geom(p.r[0] * p.r[1] * p.r[2], (int)p.K);
@@ -1013,6 +1016,12 @@ static hipError_t core_adjoint(const Plan& p, const float2* T1b, float2* gc, flo
   return TIMED("gemm_core_adjoint", gemm_launch(g[3], p.precision, wsp<void>(ws, p.off_gemm), st));
 }
 
+static TuckerRows rows_of(const Plan& p) {
+  return TuckerRows{p.n[0], p.n[1], p.n[2], p.r[0], p.r[1], p.r[2], p.J, p.U[1], p.U[2], p.precision == MAXWELL_BF16_SPLIT};
+}
+static bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
+
+// The maps also leave T2 = core x_4 c x_1 U0 in the tB region (Tucker).
 hipError_t run_basis_apply(const Plan& p, const float2* c, float2* S, void* ws, hipStream_t st) {
   void* gws = wsp<void>(ws, p.off_gemm);
   if (p.basis_kind == MAXWELL_BASIS_DENSE) {
@@ -1024,11 +1033,28 @@ hipError_t run_basis_apply(const Plan& p, const float2* c, float2* S, void* ws, 
   tucker_apply_args(p, c, wsp<float2>(ws, p.off_tA), wsp<float2>(ws, p.off_tB), S, g);
   hipError_t e0 = core_forward(p, c, wsp<float2>(ws, p.off_tA), ws, st);
   if (e0 != hipSuccess) return e0;
-  for (int i = 1; i < 4; ++i) {
+  const bool rows = p.tucker_rows && aligned16(S);
+  for (int i = 1; i < (rows ? 2 : 4); ++i) {
     hipError_t e = TIMED("gemm_tucker_chain", gemm_launch(g[i], p.precision, gws, st));
     if (e != hipSuccess) return e;
   }
+  if (rows) return TIMED("tucker_maps", tucker_maps_launch(rows_of(p), wsp<float2>(ws, p.off_tB), S, st));
   return hipSuccess;
+}
+
+// From coil images g: gx (T2 = core x_4 c x_1 U0 in the tB region) and gc, either may be null
+static hipError_t tucker_finish(const Plan& p, const float2* x, const float2* g, float alpha, const float* alpha_dev,
+                                float2* gx, float2* gc, void* ws, hipStream_t st) {
+  float2 *tA = wsp<float2>(ws, p.off_tA), *tB = wsp<float2>(ws, p.off_tB);
+  hipError_t e = TIMED("tucker_images", tucker_images_launch(rows_of(p), tB, x, g, alpha, alpha_dev, gx,
+                                                             gc ? tA : nullptr, st));
+  if (e != hipSuccess || !gc) return e;
+  if ((e = TIMED("tucker_mode1_adj", tucker_mode1_adjoint_launch(rows_of(p), tA, tB, st))) != hipSuccess) return e;
+  GemmArgs a[4];
+  tucker_adjoint_args(p, nullptr, tA, tB, gc, a);
+  e = TIMED("gemm_tucker_adjoint_chain", gemm_launch(a[2], p.precision, wsp<void>(ws, p.off_gemm), st));
+  if (e != hipSuccess) return e;
+  return core_adjoint(p, tA, gc, alpha, alpha_dev, ws, st);
 }
 
 hipError_t run_basis_adjoint(const Plan& p, const float2* S, float2* c, float alpha, const float* alpha_dev,
@@ -1043,6 +1069,7 @@ hipError_t run_basis_adjoint(const Plan& p, const float2* S, float2* c, float al
     g.alpha_dev = alpha_dev;
     return TIMED("gemm_dense_adjoint", gemm_launch(g, p.precision, gws, st));
   }
+  if (p.tucker_rows && aligned16(S)) return tucker_finish(p, nullptr, S, alpha, alpha_dev, nullptr, c, ws, st);
   GemmArgs g[4];
   tucker_adjoint_args(p, S, wsp<float2>(ws, p.off_tA), wsp<float2>(ws, p.off_tB), c, g);
   for (int i = 0; i < 3; ++i) {
@@ -1264,16 +1291,34 @@ static hipError_t adjoint_maps(const Plan& p, const float2* S, const float2* x, 
   return TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, x, p.N, p.J, alpha, scale_dev, gx, want_h ? 1 : 0, st));
 }
 
-// gx and gc from g = F_s^H y in the K region and, unless stream_gx, the maps in the S region.
-// Dense basis: the streaming products form what they need of g themselves, the image
-// gradient (stream_gx) from maps that stay in registers, the coefficients' from
-// h = conj(x) (.) g.
+// Whether the image gradient is taken from maps that stay in registers, so that no map has to
+// be in memory for it: a Tucker basis always (also where maps are at hand: they would be read
+// again), a dense one where there are none.
+static bool maps_in_registers(const Plan& p, bool maps_ready) {
+  return p.basis_kind == MAXWELL_BASIS_DENSE ? p.stream_apply && !maps_ready : p.tucker_rows;
+}
+
+// gx and gc from g = F_s^H y in the K region and the maps in the S region, if they are there
+// (maps_ready, or formed by the caller unless maps_in_registers).  The streaming products form
+// what they need of g themselves, the coefficients' gradient from h = conj(x) (.) g.
 static hipError_t adjoint_finish(const Plan& p, const float2* x, const float2* c, float alpha, const float* scale_dev,
-                                 float2* gx, float2* gc, void* ws, hipStream_t st, bool stream_gx) {
+                                 float2* gx, float2* gc, void* ws, hipStream_t st, bool maps_ready) {
   float2* S = wsp<float2>(ws, p.off_S);
   float2* Kb = wsp<float2>(ws, p.off_K);
   const bool stream_gc = gc && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_adj;
   hipError_t e;
+  if (p.tucker_rows) {
+    if (gx && !maps_ready) {  // T2
+      float2* tA = wsp<float2>(ws, p.off_tA);
+      GemmArgs a[4];
+      tucker_apply_args(p, c, tA, wsp<float2>(ws, p.off_tB), S, a);
+      if ((e = core_forward(p, c, tA, ws, st)) != hipSuccess) return e;
+      e = TIMED("gemm_tucker_chain", gemm_launch(a[1], p.precision, wsp<void>(ws, p.off_gemm), st));
+      if (e != hipSuccess) return e;
+    }
+    return tucker_finish(p, x, Kb, alpha, scale_dev, gx, gc, ws, st);
+  }
+  const bool stream_gx = gx && maps_in_registers(p, maps_ready);
   if (stream_gx) {
     e = TIMED("dense_gx", stream_gx_launch(p.dense, p.N, p.K, c, p.J, p.precision, Kb, alpha, scale_dev, gx, st));
     if (e != hipSuccess) return e;
@@ -1299,13 +1344,12 @@ hipError_t run_adjoint(const Plan& p, const float2* x, const float2* c, const fl
   if (p.fused) return fused_adjoint(p, x, c, y, alpha, scale_dev, gx, gc, ws, st, maps_ready, transfer);
   float2* S = wsp<float2>(ws, p.off_S);
   const bool ordered = transfer && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer;
-  const bool stream_gx = gx && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_apply && !maps_ready;
   hipError_t e;
-  if (gx && !maps_ready && !stream_gx) {
+  if (gx && !maps_ready && !maps_in_registers(p, maps_ready)) {
     if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
   }
   if ((e = adjoint_transform(p, y, alpha, scale_dev, ws, st, ordered)) != hipSuccess) return e;
-  return adjoint_finish(p, x, c, alpha, scale_dev, gx, gc, ws, st, stream_gx);
+  return adjoint_finish(p, x, c, alpha, scale_dev, gx, gc, ws, st, maps_ready);
 }
 
 hipError_t run_grad(const Plan& p, const float2* x, const float2* c, const float2* y, float2* gx, float2* gc,
@@ -1326,7 +1370,7 @@ hipError_t run_grad(const Plan& p, const float2* x, const float2* c, const float
     if ((e = fft_round_trip(p, S, Kb, x, st, &res)) != hipSuccess) return e;
     const double* rp = res.part;
     if (loss && (e = TIMED("reduce_loss", reduce_loss_launch(rp, p.res_blocks, loss, st))) != hipSuccess) return e;
-    return adjoint_finish(p, x, c, 2.0f, nullptr, gx, gc, ws, st, false);
+    return adjoint_finish(p, x, c, 2.0f, nullptr, gx, gc, ws, st, true);
   }
   if ((e = run_forward_loss(p, x, c, y, r, loss, ws, st, true)) != hipSuccess) return e;
   if (!want) return hipSuccess;
