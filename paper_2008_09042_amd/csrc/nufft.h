@@ -46,6 +46,11 @@ constexpr int SPREAD_SPLIT_DEFAULT = 48;
 constexpr int SPREAD_SPLIT_PM = 4, SPREAD_SPLIT_PH = 16;
 size_t spread_stage_bytes(int J, int64_t M);
 hipError_t degrid_launch(const NufftArgs& a, const float2* grid, float2* y, hipStream_t st);
+// r[s][j] = w (E - y[j][perm[s]]), the weighted residual in the spread's staging layout (J a
+// multiple of the coil group), and degrid_blocks (at most J M) loss partials sum w |E - y|^2.
+int degrid_blocks(const NufftArgs& a);
+hipError_t degrid_residual_launch(const NufftArgs& a, const float2* grid, const float2* y, const float* w, float2* r,
+                                  double* part, hipStream_t st);
 // grid = alpha * (*scale_dev) * spread(y); ys is a staging buffer of spread_stage_bytes(J, M).
 // With `staged`, y is already in the staging layout (sorted samples, coils innermost, J a
 // multiple of the coil group: ys[s][j] = y[j][perm[s]]) and ys is not used.

@@ -1241,15 +1241,20 @@ hipError_t run_forward_loss(const Plan& p, const float2* x, const float2* c, con
     return hipSuccess;
   }
   float2* E = wsp<float2>(ws, p.off_E);
-  if ((e = run_encode(p, x, c, E, ws, st)) != hipSuccess) return e;
   if (transfer && r && p.sampling == MAXWELL_NONCARTESIAN && p.ordered_transfer) {
-    // the transfer layout of the gridding path: the residual in the spread's sample order
-    const int32_t* inv = p.d_sinv;
-    if ((e = TIMED("residual", residual_ordered_launch(E, y, p.d_w, p.M, p.J, inv, r, part, st))) != hipSuccess)
-      return e;
-  } else if ((e = TIMED("residual", residual_launch(E, y, p.d_w, p.M, p.J, r, part, st))) != hipSuccess) {
-    return e;
+    // the transfer layout of the gridding path: the degridding writes the residual in the
+    // spread's sample order, and its loss partials to the E region
+    float2 *S = wsp<float2>(ws, p.off_S), *G = wsp<float2>(ws, p.off_G);
+    const NufftArgs na = nufft_args(p);
+    double* gp = reinterpret_cast<double*>(E);
+    if ((e = run_basis_apply(p, c, S, ws, st)) != hipSuccess) return e;
+    if ((e = fft_grid_window(p, S, x, G, nullptr, -1, st)) != hipSuccess) return e;
+    if ((e = TIMED("nufft_degrid", degrid_residual_launch(na, G, y, p.d_w, r, gp, st))) != hipSuccess) return e;
+    if (loss) return TIMED("reduce_loss", reduce_loss_launch(gp, degrid_blocks(na), loss, st));
+    return hipSuccess;
   }
+  if ((e = run_encode(p, x, c, E, ws, st)) != hipSuccess) return e;
+  if ((e = TIMED("residual", residual_launch(E, y, p.d_w, p.M, p.J, r, part, st))) != hipSuccess) return e;
   if (loss) return TIMED("reduce_loss", reduce_loss_launch(part, residual_blocks((int64_t)p.J * p.M), loss, st));
   return hipSuccess;
 }
