@@ -221,16 +221,16 @@ __global__ __launch_bounds__(NT) void core_fwd_f32f_kernel(CoreArgs a) {
 // Launched with two steps in flight (the three-product accumulators take the registers of
 // the third).
 template <int NB, int RB, int FD = ADJ_FD>
-__global__ __launch_bounds__(NT) void core_adj_f32f_kernel(CoreArgs a, int nch, int kgroups) {
+__global__ __launch_bounds__(NT) void core_adj_f32f_kernel(CoreArgs a, int nsub, int kgroups) {
   const int xcd = blockIdx.x % 8, i = blockIdx.x / 8;
-  const int ky = i % kgroups, ch = 8 * (i / kgroups) + xcd;
+  const int ky = i % kgroups, cs = 8 * (i / kgroups) + xcd;  // part cs % sub of chunk cs / sub
   const int lane = threadIdx.x & 63, grp = lane >> 4, wave = threadIdx.x >> 6;
   const int mbl = a.g.Kp / 16;
   const int mb0 = ky * (4 * RB) + wave * RB;
-  if (ch >= nch || mb0 >= mbl) return;
+  if (cs >= nsub || mb0 >= mbl) return;
+  const int ch = cs / a.sub, steps = RC / 16 / a.sub, sb = cs % a.sub * steps;
   const int64_t rho0 = (int64_t)ch * RC;
-  const int steps_total = (int)(a.g.Rp / 16);
-  constexpr int steps = RC / 16;
+  const int nchp = (int)(a.g.Rp / RC);  // chunks in the copy's order
   int mbm[RB];
 #pragma unroll
   for (int m = 0; m < RB; ++m) mbm[m] = min(mb0 + m, mbl - 1);
@@ -240,10 +240,10 @@ __global__ __launch_bounds__(NT) void core_adj_f32f_kernel(CoreArgs a, int nch, 
   Tile<0>::A av[FD][RB];
   float2 bv[FD][NB][4];
   auto load = [&](int d, int s) {
-    s = min(s, steps - 1);
+    s = sb + min(s, steps - 1);
 #pragma unroll
     // chunk-step-major: fragment (step s of chunk ch, k row block mb) at (s nch + ch) mbl + mb
-    for (int m = 0; m < RB; ++m) av[d][m] = frag_a<0>(a.adj_f32, mbl, s * (steps_total / steps) + ch, mbm[m], lane);
+    for (int m = 0; m < RB; ++m) av[d][m] = frag_a<0>(a.adj_f32, mbl, s * nchp + ch, mbm[m], lane);
     call_operand<NB>(row, rho0 + 16 * s, a.g.R, grp, bv[d]);
   };
   Tile<0>::Acc acc[RB][NB];
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(NT) void core_adj_f32f_kernel(CoreArgs a, int nch, 
   for (int d = 0; d + 1 < FD; ++d)
     if (s0 + d < steps) compute(d);
   const int Jp = 16 * ((a.J + 15) / 16);
-  float2* part = a.part + (int64_t)ch * a.g.Kp * Jp;
+  float2* part = a.part + (int64_t)cs * a.g.Kp * Jp;
 #pragma unroll
   for (int m = 0; m < RB; ++m)
     if (mb0 + m < mbl)
@@ -351,17 +351,16 @@ __global__ __launch_bounds__(NT) void core_fwd_f32_kernel(CoreArgs a) {
 // are k, columns coils.  The k groups of one chunk are placed on one XCD (workgroups are
 // dispatched round-robin over the 8 XCDs), so the chunk's T1b is fetched into one L2.
 template <int NB, int RB, int FD = ADJ_FD>
-__global__ __launch_bounds__(NT) void core_adj_bf16_kernel(CoreArgs a, int nch, int kgroups) {
+__global__ __launch_bounds__(NT) void core_adj_bf16_kernel(CoreArgs a, int nsub, int kgroups) {
   const int xcd = blockIdx.x % 8, i = blockIdx.x / 8;
-  const int ky = i % kgroups, ch = 8 * (i / kgroups) + xcd;
+  const int ky = i % kgroups, cs = 8 * (i / kgroups) + xcd;  // part cs % sub of chunk cs / sub
   const int lane = threadIdx.x & 63, grp = lane >> 4, wave = threadIdx.x >> 6;
   const int mbl = a.g.Kp / 16;
   const int mb0 = ky * (4 * RB) + wave * RB;
-  if (ch >= nch || mb0 >= mbl) return;
+  if (cs >= nsub || mb0 >= mbl) return;
+  const int ch = cs / a.sub, steps = RC / 16 / a.sub, sb = cs % a.sub * steps;
   const int64_t rho0 = (int64_t)ch * RC;
-  const int64_t steps_total = a.g.Rp / 16;
-  constexpr int steps = RC / 16;
-  const int64_t nchp = steps_total / steps;  // chunks in the planes' order (Rp / RC)
+  const int64_t nchp = a.g.Rp / RC;  // chunks in the planes' order
   int64_t oa[RB];
 #pragma unroll
   for (int m = 0; m < RB; ++m) oa[m] = ((int64_t)ch * mbl + min(mb0 + m, mbl - 1)) * 512 + lane * 8;
@@ -371,7 +370,7 @@ __global__ __launch_bounds__(NT) void core_adj_bf16_kernel(CoreArgs a, int nch, 
   u16x8 ah[FD][RB], al[FD][RB];
   float2 bv[FD][NB][4];
   auto load = [&](int d, int s) {
-    s = min(s, steps - 1);
+    s = sb + min(s, steps - 1);
 #pragma unroll
     for (int m = 0; m < RB; ++m) {
       ah[d][m] = ld8(a.adj_hi + oa[m] + (int64_t)s * nchp * mbl * 512);
@@ -409,7 +408,7 @@ __global__ __launch_bounds__(NT) void core_adj_bf16_kernel(CoreArgs a, int nch, 
   for (int d = 0; d + 1 < FD; ++d)
     if (s0 + d < steps) compute(d);
   const int Jp = 16 * ((a.J + 15) / 16);
-  float2* part = a.part + (int64_t)ch * a.g.Kp * Jp;
+  float2* part = a.part + (int64_t)cs * a.g.Kp * Jp;
 #pragma unroll
   for (int m = 0; m < RB; ++m)
     if (mb0 + m < mbl)
@@ -495,7 +494,14 @@ __global__ __launch_bounds__(RED_OUT * RED_SL) void core_adj_reduce_kernel(CoreA
   const int64_t plane = (int64_t)a.g.Kp * Jp;
   float2 acc = make_float2(0.f, 0.f);
   if (e < plane)
-    for (int c = sl; c < nch; c += RED_SL) acc = cadd(acc, a.part[(int64_t)c * plane + e]);
+    for (int c = sl; c < nch; c += 4 * RED_SL) {  // four loads in flight
+      float2 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = a.part[(int64_t)min(c + u * RED_SL, nch - 1) * plane + e];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u * RED_SL < nch) acc = cadd(acc, v[u]);
+    }
   acc_s[sl][o] = acc;
   __syncthreads();
   if (sl == 0 && e < plane) {
@@ -587,40 +593,62 @@ hipError_t core_frag32_launch(const float2* core, const CoreGeom& g, float2* dst
   return hipGetLastError();
 }
 
-hipError_t core_fwd_launch(const CoreArgs& a, int precision, hipStream_t st) {
-  const dim3 block(NT);
+namespace {
+
+// Rows per wave of the forward: where four blocks each leave half the chip without a workgroup,
+// one (R = 11520, K = 120, 12 coils, FP32: 12.4 -> 5.4 us; at R = 64000 four blocks fill
+// it, and share the loads of c).
+template <int NB, int F>
+void core_fwd_rows(const CoreArgs& a, int precision, hipStream_t st) {
   auto grid = [&](int rb) { return dim3((unsigned)((a.g.R + 64 * rb - 1) / (64 * rb))); };
+  const bool one = grid(F).x < 128;
   if (precision == MAXWELL_BF16_SPLIT) {
-    constexpr int F = FWD_RB_FEW, M = FWD_RB_MANY;
+    if (one) hipLaunchKernelGGL((core_fwd_bf16_kernel<NB, 1>), grid(1), dim3(NT), 0, st, a);
+    else hipLaunchKernelGGL((core_fwd_bf16_kernel<NB, F>), grid(F), dim3(NT), 0, st, a);
+  } else {
+    if (one) hipLaunchKernelGGL((core_fwd_f32f_kernel<NB, 1>), grid(1), dim3(NT), 0, st, a);
+    else hipLaunchKernelGGL((core_fwd_f32f_kernel<NB, F>), grid(F), dim3(NT), 0, st, a);
+  }
+}
+
+int core_adj_kgroups(const CoreGeom& g, int J) {
+  const int rb = (J + 15) / 16 <= 2 ? ADJ_RB_FEW : ADJ_RB_MANY;
+  return (g.Kp / 16 + 4 * rb - 1) / (4 * rb);
+}
+
+}  // namespace
+
+int core_adj_sub(const CoreGeom& g, int J, size_t bytes) {
+  const int64_t wgs = (int64_t)core_adj_chunks(g.R) * core_adj_kgroups(g, J);
+  const size_t part = core_adj_part_bytes(g.R, g.K, J);
+  int sub = 1;
+  while (sub < 8 && wgs * sub * 2 <= 256 && part * sub * 2 <= bytes) sub *= 2;
+  return sub;
+}
+
+hipError_t core_fwd_launch(const CoreArgs& a, int precision, hipStream_t st) {
+  if (precision == MAXWELL_BF16_SPLIT || a.fwd_f32) {
     switch ((a.J + 15) / 16) {
-      case 1: hipLaunchKernelGGL((core_fwd_bf16_kernel<1, F>), grid(F), block, 0, st, a); break;
-      case 2: hipLaunchKernelGGL((core_fwd_bf16_kernel<2, F>), grid(F), block, 0, st, a); break;
-      case 3: hipLaunchKernelGGL((core_fwd_bf16_kernel<3, M>), grid(M), block, 0, st, a); break;
-      default: hipLaunchKernelGGL((core_fwd_bf16_kernel<4, M>), grid(M), block, 0, st, a); break;
-    }
-  } else if (a.fwd_f32) {
-    constexpr int F = FWD_RB_FEW, M = FWD_RB_MANY;
-    switch ((a.J + 15) / 16) {
-      case 1: hipLaunchKernelGGL((core_fwd_f32f_kernel<1, F>), grid(F), block, 0, st, a); break;
-      case 2: hipLaunchKernelGGL((core_fwd_f32f_kernel<2, F>), grid(F), block, 0, st, a); break;
-      case 3: hipLaunchKernelGGL((core_fwd_f32f_kernel<3, M>), grid(M), block, 0, st, a); break;
-      default: hipLaunchKernelGGL((core_fwd_f32f_kernel<4, M>), grid(M), block, 0, st, a); break;
+      case 1: core_fwd_rows<1, FWD_RB_FEW>(a, precision, st); break;
+      case 2: core_fwd_rows<2, FWD_RB_FEW>(a, precision, st); break;
+      case 3: core_fwd_rows<3, FWD_RB_MANY>(a, precision, st); break;
+      default: core_fwd_rows<4, FWD_RB_MANY>(a, precision, st); break;
     }
   } else {
-    hipLaunchKernelGGL(core_fwd_f32_kernel, grid(RB), block, 0, st, a);
+    hipLaunchKernelGGL(core_fwd_f32_kernel, dim3((unsigned)((a.g.R + 64 * RB - 1) / (64 * RB))), dim3(NT), 0, st, a);
   }
   return hipGetLastError();
 }
 
 hipError_t core_adj_launch(const CoreArgs& a, int precision, float alpha, const float* scale_dev, hipStream_t st) {
-  const int nch = core_adj_chunks(a.g.R);
+  const bool split = precision == MAXWELL_BF16_SPLIT || a.adj_f32;
+  const int nch = core_adj_chunks(a.g.R) * (split ? a.sub : 1);
   const int nb = (a.J + 15) / 16;
   const dim3 block(NT);
-  auto kgroups = [&](int rb) { return (a.g.Kp / 16 + 4 * rb - 1) / (4 * rb); };
+  const int kg = core_adj_kgroups(a.g, a.J);
+  const dim3 grid((unsigned)(8 * kg * ((nch + 7) / 8)));
+  constexpr int F = ADJ_RB_FEW, M = ADJ_RB_MANY;
   if (precision == MAXWELL_BF16_SPLIT) {
-    const int rb = nb <= 2 ? ADJ_RB_FEW : ADJ_RB_MANY, kg = kgroups(rb);
-    const dim3 grid((unsigned)(8 * kg * ((nch + 7) / 8)));
-    constexpr int F = ADJ_RB_FEW, M = ADJ_RB_MANY;
     switch (nb) {
       case 1: hipLaunchKernelGGL((core_adj_bf16_kernel<1, F>), grid, block, 0, st, a, nch, kg); break;
       case 2: hipLaunchKernelGGL((core_adj_bf16_kernel<2, F>), grid, block, 0, st, a, nch, kg); break;
@@ -628,9 +656,6 @@ hipError_t core_adj_launch(const CoreArgs& a, int precision, float alpha, const 
       default: hipLaunchKernelGGL((core_adj_bf16_kernel<4, M>), grid, block, 0, st, a, nch, kg); break;
     }
   } else if (a.adj_f32) {
-    const int rb = nb <= 2 ? ADJ_RB_FEW : ADJ_RB_MANY, kg = kgroups(rb);
-    const dim3 grid((unsigned)(8 * kg * ((nch + 7) / 8)));
-    constexpr int F = ADJ_RB_FEW, M = ADJ_RB_MANY;
     switch (nb) {
       case 1: hipLaunchKernelGGL((core_adj_f32f_kernel<1, F, 2>), grid, block, 0, st, a, nch, kg); break;
       case 2: hipLaunchKernelGGL((core_adj_f32f_kernel<2, F, 2>), grid, block, 0, st, a, nch, kg); break;
@@ -638,7 +663,8 @@ hipError_t core_adj_launch(const CoreArgs& a, int precision, float alpha, const 
       default: hipLaunchKernelGGL((core_adj_f32f_kernel<4, M, 2>), grid, block, 0, st, a, nch, kg); break;
     }
   } else {
-    hipLaunchKernelGGL(core_adj_f32_kernel, dim3((unsigned)nch, (unsigned)kgroups(RB)), block, 0, st, a);
+    hipLaunchKernelGGL(core_adj_f32_kernel, dim3((unsigned)nch, (unsigned)((a.g.Kp / 16 + 4 * RB - 1) / (4 * RB))),
+                       block, 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

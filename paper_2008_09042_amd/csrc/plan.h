@@ -56,6 +56,7 @@ struct Plan {
   // dedicated core contraction kernels (Tucker basis, J <= 64)
   bool tucker_rows = false;      // general path: the products next to the coil images as streams
   bool core_direct = false;
+  int core_sub = 1;              // parts of a chunk of the core's adjoint (CoreArgs::sub)
   CoreGeom cg{};
   uint16_t* d_core_split = nullptr;  // BF16-split core planes (BF16_SPLIT plans only)
   float2* d_core_f32 = nullptr;      // FP32 core copies in fragment order (FP32 plans only)

@@ -895,6 +895,8 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
   if (p.core_direct) {
     p.off_cpart = off;
     off += al(core_adj_part_bytes(p.cg.R, p.cg.K, p.J));
+    p.core_sub = core_adj_sub(p.cg, p.J, p.fused ? (size_t)p.J * p.n[2] * p.r[0] * p.r[1] * 8
+                                                 : (size_t)p.J * p.n[0] * p.r[1] * p.r[2] * 8);
   }
   if (p.stream_adj) {
     p.off_adjp = off;
@@ -993,6 +995,7 @@ static CoreArgs core_args(const Plan& p, const float2* in, float2* out, void* ws
   a.in = in;
   a.out = out;
   a.part = wsp<float2>(ws, p.off_cpart);
+  a.sub = 1;
   return a;
 }
 
@@ -1007,8 +1010,12 @@ static hipError_t core_forward(const Plan& p, const float2* c, float2* T1, void*
 // gc = alpha (*alpha_dev) core^H T1b  (last product of the adjoint chain)
 static hipError_t core_adjoint(const Plan& p, const float2* T1b, float2* gc, float alpha, const float* alpha_dev,
                                void* ws, hipStream_t st) {
-  if (p.core_direct)
-    return TIMED("core_adj", core_adj_launch(core_args(p, T1b, gc, ws), p.precision, alpha, alpha_dev, st));
+  if (p.core_direct) {
+    CoreArgs a = core_args(p, T1b, gc, ws);
+    // the product before this one has used up its input, whose region can hold the partials
+    if ((a.sub = p.core_sub) > 1) a.part = wsp<float2>(ws, p.fused ? p.off_T3b : p.off_tB);
+    return TIMED("core_adj", core_adj_launch(a, p.precision, alpha, alpha_dev, st));
+  }
   GemmArgs g[4];
   tucker_adjoint_args(p, nullptr, const_cast<float2*>(T1b), nullptr, gc, g);
   g[3].alpha = alpha;
