@@ -91,6 +91,7 @@ struct Plan {
   size_t off_U = 0, off_cg = 0;  // Gauss-Newton / CG: JVP result; r, d, q, FP64 scalars
   size_t off_admm = 0;           // SENSE / ADMM state (general path only)
   size_t off_adjp = 0;           // dense adjoint: row-chunk partials of the streaming kernel
+  int adj_chunks = 0;            // and the most row chunks their region holds (0: no limit)
   int part_blocks = 0;
   int res_blocks = 0;            // Cartesian: workgroups of the pass that forms the residual itself (0: none does)
   bool res_forward = false;      // the forward's last pass does too, not only the gradient's round trip

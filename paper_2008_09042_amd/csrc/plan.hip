@@ -828,9 +828,9 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
         const int cd = tuned_choice("stream_adjoint " + shape.str(), [&]() -> int {
           float gemm_ms = -1.f;
           const int split = gemm_autotune(dense_adjoint_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm_ms);
-          if (stream_adjoint_bytes(p.N, p.K, p.J) > max_ws) return split;
+          if (stream_adjoint_bytes(p.N, p.K, p.J, 0) > max_ws) return split;
           const float sk = time_ms([&]() {
-            return stream_adjoint_launch(p.dense, p.N, p.K, A, nullptr, p.J, p.precision, 1.0f, nullptr, bufW, C, 0);
+            return stream_adjoint_launch(p.dense, p.N, p.K, A, nullptr, p.J, p.precision, 1.0f, nullptr, bufW, 0, C, 0);
           });
           return (sk > 0.f && (gemm_ms <= 0.f || sk < gemm_ms)) ? -1 : split;
         });
@@ -898,10 +898,6 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
     p.core_sub = core_adj_sub(p.cg, p.J, p.fused ? (size_t)p.J * p.n[2] * p.r[0] * p.r[1] * 8
                                                  : (size_t)p.J * p.n[0] * p.r[1] * p.r[2] * 8);
   }
-  if (p.stream_adj) {
-    p.off_adjp = off;
-    off += al(stream_adjoint_bytes(p.N, p.K, p.J));
-  }
   p.off_E = off; off += al(JM);
   p.off_gemm = off; off += al(gemm_ws);
   p.part_blocks = residual_blocks((int64_t)p.J * p.M);
@@ -921,6 +917,25 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
     p.off_admm = off;
     off += (5 + 2 * p.ndim) * NB + 5 * al(JM) + al((size_t)ball_part_doubles(p.J) * sizeof(double)) +
            al(ADMM_SCALARS * sizeof(double));
+  }
+  if (p.stream_adj) {
+    // The dense adjoint's row-chunk partials go where nothing lives while it runs: the maps'
+    // region (the image gradient has read them) or the samples' and the GEMMs', which adjoin.
+    // Where neither holds them they get a region of their own, unless that alone would make the
+    // plan too large for maxwell_grad_static: then there are as many chunks as fit.
+    const size_t need = stream_adjoint_bytes(p.N, p.K, p.J, 0), row = (size_t)p.J * (size_t)p.K * 8;
+    const size_t maps = al(JN), rest = al(JM) + al(gemm_ws), room = std::max(maps, rest);
+    p.off_adjp = maps >= rest ? p.off_S : p.off_E;
+    if (need > room) {
+      if (off > MAXWELL_STATIC_WS_BYTES || off + al(need) <= MAXWELL_STATIC_WS_BYTES) {
+        p.off_adjp = off;
+        off += al(need);
+      } else if (room >= row) {
+        p.adj_chunks = (int)std::min<size_t>(room / row, INT32_MAX);
+      } else {
+        p.stream_adj = false;  // the tiled GEMM, whose region is counted above
+      }
+    }
   }
   p.ws_bytes = off;
   return MAXWELL_OK;
@@ -1069,7 +1084,7 @@ hipError_t run_basis_adjoint(const Plan& p, const float2* S, float2* c, float al
   void* gws = wsp<void>(ws, p.off_gemm);
   if (p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_adj)
     return TIMED("gemm_dense_adjoint", stream_adjoint_launch(p.dense, p.N, p.K, S, nullptr, p.J, p.precision, alpha,
-                                                             alpha_dev, wsp<void>(ws, p.off_adjp), c, st));
+                                                             alpha_dev, wsp<void>(ws, p.off_adjp), p.adj_chunks, c, st));
   if (p.basis_kind == MAXWELL_BASIS_DENSE) {
     GemmArgs g = dense_adjoint_args(p, S, c);
     g.alpha = alpha;
@@ -1341,7 +1356,7 @@ static hipError_t adjoint_finish(const Plan& p, const float2* x, const float2* c
       if (e != hipSuccess) return e;
     }
     return TIMED("gemm_dense_adjoint", stream_adjoint_launch(p.dense, p.N, p.K, Kb, x, p.J, p.precision, alpha,
-                                                             scale_dev, wsp<void>(ws, p.off_adjp), gc, st));
+                                                             scale_dev, wsp<void>(ws, p.off_adjp), p.adj_chunks, gc, st));
   }
   float2* gxc = stream_gx ? nullptr : gx;
   e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, x, p.N, p.J, alpha, scale_dev, gxc, gc ? 1 : 0, st));
@@ -1392,8 +1407,8 @@ hipError_t run_grad(const Plan& p, const float2* x, const float2* c, const float
 // ---- Gauss-Newton step (Sec. II-B, Eq. (6) and Eq. (7))
 
 // J[dx, dc] = E(dx, c) + E(x, dc): E is bilinear, so the Jacobian-vector product of Eq. (7)
-// is two encodes; the second goes through the E region of the workspace.  On the fused path
-// the two meet in the plane, before the transform.
+// is two encodes on the general path; the second goes through the E region of the workspace.
+// On the fused path the two meet in the plane, before the transform.
 hipError_t run_jvp(const Plan& p, const float2* x, const float2* c, const float2* dx, const float2* dc, float2* y,
                    void* ws, hipStream_t st) {
   hipError_t e;

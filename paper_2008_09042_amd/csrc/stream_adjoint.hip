@@ -33,8 +33,9 @@ struct AdjGeom {
 
 // Waves: as many column groups as K needs (a power of two up to 8), the rest split the rows.
 // Row chunks: a workgroup per compute unit over all coil and column groups (two where the
-// tiles are small enough that two share one), at least one step of every row group.
-AdjGeom adj_geom(int64_t N, int64_t K, int J) {
+// tiles are small enough that two share one), at least one step of every row group, and no more
+// than max_chunks (0: no limit).
+AdjGeom adj_geom(int64_t N, int64_t K, int J, int max_chunks) {
   AdjGeom a;
   const int nkb = (int)((K + 15) / 16), njb = (J + 15) / 16;
   a.JB = njb == 1 ? 1 : njb == 2 ? 2 : 4;
@@ -46,6 +47,7 @@ AdjGeom adj_geom(int64_t N, int64_t K, int J) {
   const int64_t step = (int64_t)16 * (NW >> a.kwl);
   int64_t want = (a.JB == 1 ? 512 : 256) / ((int64_t)a.jgs * a.ks);
   if (want < 32) want = 32;
+  if (max_chunks > 0 && want > max_chunks) want = max_chunks;
   a.chunk = (N + want - 1) / want;
   a.chunk = (a.chunk + step - 1) / step * step;
   a.nchunk = (int)((N + a.chunk - 1) / a.chunk);
@@ -263,16 +265,16 @@ hipError_t dispatch(const AdjCall& a, const AdjGeom& q, hipStream_t st) {
 
 }  // namespace
 
-size_t stream_adjoint_bytes(int64_t N, int64_t K, int J) {
+size_t stream_adjoint_bytes(int64_t N, int64_t K, int J, int max_chunks) {
   if (N <= 0 || K <= 0 || J <= 0) return 0;
-  return (size_t)adj_geom(N, K, J).nchunk * (size_t)J * (size_t)K * sizeof(float2);
+  return (size_t)adj_geom(N, K, J, max_chunks).nchunk * (size_t)J * (size_t)K * sizeof(float2);
 }
 
 hipError_t stream_adjoint_launch(const float2* B, int64_t N, int64_t K, const float2* g, const float2* x, int J,
-                                 int precision, float alpha, const float* alpha_dev, void* ws, float2* c,
-                                 hipStream_t st) {
+                                 int precision, float alpha, const float* alpha_dev, void* ws, int max_chunks,
+                                 float2* c, hipStream_t st) {
   if (N <= 0 || K <= 0 || J <= 0) return hipSuccess;
-  const AdjGeom q = adj_geom(N, K, J);
+  const AdjGeom q = adj_geom(N, K, J, max_chunks);
   const AdjCall a{B, N, (int)K, g, x, J, reinterpret_cast<float2*>(ws)};
   auto odd = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; };
   const bool vec = K % 2 == 0 && N % 2 == 0 && !odd(B) && !odd(g) && !odd(x);
