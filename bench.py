@@ -360,8 +360,8 @@ def bench_batch(args, torch):
 
 def bench_gn(args, torch):
     """Gauss-Newton step of the joint solve on the 128^3 Tucker workload: maxwell_cg with
-    cg-iters steps per call, each step one normal-operator application (two encodes for the
-    JVP, one adjoint with B c recomputed, the shift) plus the FP64 inner products.  Prints
+    cg-iters steps per call, each step one normal-operator application (the Jacobian product,
+    one adjoint, the shift) plus the FP64 inner products.  Prints
     one JSON line (coil-images/s = J x normal-operator applications per second)."""
     from paper_2008_09042_amd.encoding import MaxwellPlan
     dev = torch.device("cuda:0")
@@ -547,19 +547,19 @@ def bench_kernels2d(args, torch, names=("cart2d_256_dense200_j32", "radial2d_256
                                      gemm_bytes),
                 "gemm_dense_adjoint": ("mfma", gemm_flops, PEAKS_TFLOPS["bf16" if prec == "bf16_split" else "fp32"],
                                        gemm_bytes),
-                # Cartesian: the mask is applied in the last forward and the first inverse
-                # pass (8 B per element in, 8 B per sample and 4 B of inverse mask per point
-                # out, and the reverse), so the four passes move 48 J N + 16 J M + 8 N bytes
+                # Cartesian: three passes, the middle one there and back along the first axis
+                # around the residual (8 B per element in and out, 8 B per measured sample):
+                # 48 J N + 8 J M + 8 N bytes
                 # gridding (g0 x g1 grid, n0 x n1 window): the first forward pass reads the
                 # window (8 B per image element and coil, and the image) and writes its n0 rows,
                 # the second reads them and writes the grid; the first inverse pass reads the
                 # grid and writes the window's n1 columns, the last reads them and writes the
                 # window: 8 J (2 N + 2 n0 g1 + 2 G + 2 g0 n1) + 8 N bytes in four passes
                 "fft_axis": ("hbm", (16.0 * J * (N + G + 2 * p.dims[0] * p.dims[1] * 2) + 8.0 * N) / 4 if G
-                             else (48.0 * J * N + 16.0 * J * M + 8.0 * N) / 4, None, None),
+                             else (48.0 * J * N + 8.0 * J * M + 8.0 * N) / 3, None, None),
                 "gather": ("hbm", 8.0 * J * M * 2 + 4.0 * M, None, None),
                 "scatter": ("hbm", 8.0 * J * (M + N) + 4.0 * N, None, None),
-                "nufft_degrid": ("hbm", 8.0 * J * (G + M) + M * (8.0 + 48.0), None, None),
+                "nufft_degrid": ("hbm", 8.0 * J * (G + 2 * M) + M * (8.0 + 64.0), None, None),
                 "nufft_spread": ("hbm", 8.0 * J * (G + 2 * M) + M * (64.0 + 8.0) + 4.0 * G, None, None),
                 "adjoint_combine": ("hbm", 8.0 * (3 * J * N + 2 * N), None, None),
                 "residual": ("hbm", 8.0 * J * M * 3 + 4.0 * M, None, None),

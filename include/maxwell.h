@@ -228,7 +228,7 @@ maxwell_status maxwell_grad(maxwell_plan_t plan, const maxwell_complex64* x,
  *
  * maxwell_jvp: the Jacobian-vector product of Eq. (7) at (x, c),
  *     y_j = F_s( (B c_j) (.) dx + x (.) (B dc_j) )       dx: [N], dc: [J][K], y: [J][M]
- *   computed as E(dx, c) + E(x, dc) (E is bilinear).
+ *   that is E(dx, c) + E(x, dc) (E is bilinear).
  * maxwell_normal: the normal operator at (x, c),
  *     (ox, oc) = J^H (w (.) J[dx, dc]) + (lambda_x dx, lambda_c dc)
  *   with the plan's data weights w (1 when the plan has none).  For the objective of
@@ -413,11 +413,11 @@ const char* maxwell_last_error(void);
 const char* maxwell_version(void);
 
 /* Plan-time kernel choices: for a dense basis, plan creation times the streaming kernel
- * (few coils) against the tiled GEMM at each split-K factor for both basis products and
- * keeps the fastest, per (GPU architecture, product, N, K, J, precision).  The choices are
+ * against the tiled GEMM at each split-K factor for both basis products and keeps the
+ * fastest, per (GPU architecture, product, N, K, J, precision).  The choices are
  * kept for the process and in a tuning file, $MAXWELL_TUNE_CACHE if set (empty: none), else
  * $HOME/.cache/maxwell/tune.txt, so a later process reuses them without timing.
- * MAXWELL_GEMM_AUTOTUNE=0 skips the timing (a fixed rule).  maxwell_tune_counts: the
+ * MAXWELL_GEMM_AUTOTUNE=0 skips the timing (the streaming kernels).  maxwell_tune_counts: the
  * choices timed and the choices reused since the process started (either may be NULL).  */
 maxwell_status maxwell_tune_counts(int64_t* measured, int64_t* reused);
 
