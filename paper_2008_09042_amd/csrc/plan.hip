@@ -224,16 +224,16 @@ hipError_t fft_dims(const Plan& p, const float2* src, float2* dst, int dir, cons
 // residual w (P F - y): the forward passes from the last
 // axis to the second, the first axis there and back in one pass, and the inverse passes back.
 // One pass over memory fewer than the transform to the samples and the transform from them,
-// and no samples in between.
+// and no samples in between.  but_last: without the last pass.
 bool round_trip_supported(const Plan& p) {
   return p.sampling == MAXWELL_CARTESIAN && p.ndim >= 2 && p.d_inv && p.M > 0 &&
          (int64_t)p.J * p.N <= 0x7fffffffLL && fft_tr_supported(p.n[0]);
 }
 hipError_t fft_round_trip(const Plan& p, const float2* src, float2* dst, const float2* premul, hipStream_t st,
-                          const ResidualOf* res = nullptr) {
+                          const ResidualOf* res = nullptr, bool but_last = false) {
   const int nd = p.ndim;
   const float2* cur = src;
-  for (int t = 0; t < 2 * nd - 1; ++t) {
+  for (int t = 0; t < 2 * nd - 1 - (but_last ? 1 : 0); ++t) {
     const int d = t < nd ? nd - 1 - t : t - nd + 1;
     FftAxisArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -1543,8 +1543,13 @@ static hipError_t sense_normal_op(const Plan& p, const float2* S, const float2* 
   hipError_t e;
   if (round_trip_supported(p)) {
     float2* Kb = wsp<float2>(ws, p.off_K);
-    if ((e = fft_round_trip(p, S, Kb, x, st)) != hipSuccess) return e;
-    e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, nullptr, p.N, p.J, 1.0f, nullptr, out, 0, st));
+    const int64_t nl = p.n[p.ndim - 1], rows = p.N / nl;
+    const bool combine = fft_combine_supported(nl, rows);
+    if ((e = fft_round_trip(p, S, Kb, x, st, nullptr, combine)) != hipSuccess) return e;
+    if (combine)  // the last pass sums over the coils
+      e = TIMED("fft_combine", fft_combine_launch(Kb, S, nl, rows, p.J, p.d_tw[p.ndim - 1], out, st));
+    else
+      e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, nullptr, p.N, p.J, 1.0f, nullptr, out, 0, st));
   } else {
     float2* u = wsp<float2>(ws, p.off_U);
     if ((e = encode_maps(p, S, x, u, ws, st)) != hipSuccess) return e;
