@@ -23,12 +23,15 @@ from . import _lib as L
 _PRECISIONS = {"fp32": L.MAXWELL_FP32, "bf16_split": L.MAXWELL_BF16_SPLIT}
 
 
+# Addresses go to the library as integers: its argument types are declared, so ctypes converts
+# them, and a call saves an object per argument.  The current stream's handle comes without a
+# Stream object around it.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class MaxwellPlan:
@@ -162,9 +165,8 @@ class MaxwellPlan:
             raise TypeError(f"{name} must be a torch tensor")
         if t.dtype != torch.complex64 or t.device != self.device:
             raise ValueError(f"{name} must be complex64 on {self.device}")
-        shape = tuple(int(v) for v in shape)
-        if tuple(t.shape) != shape and not (t.dim() == 1 and t.numel() == int(np.prod(shape))):
-            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape} (or a flat view)")
+        if t.shape != shape and not (t.dim() == 1 and t.numel() == math.prod(shape)):
+            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)} (or a flat view)")
         return t.contiguous()
 
     def bf16_split(self, x: torch.Tensor, variant: int = 0):
@@ -176,7 +178,7 @@ class MaxwellPlan:
         return torch.empty(shape, dtype=torch.complex64, device=self.device)
 
     def _wsargs(self):
-        return ctypes.c_void_p(self.ws.data_ptr()) if self.ws_bytes else None, self.ws_bytes
+        return self.ws.data_ptr() if self.ws_bytes else None, self.ws_bytes
 
     # ---- the C-ABI calls
     def basis_apply(self, c):
@@ -586,7 +588,7 @@ class MaxwellDataFidelity(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gloss):
         x, c, t = ctx.saved_tensors
-        scale = gloss.detach().to(torch.float32).reshape(1)
+        scale = gloss.detach().to(torch.float32)
         gx, gc = ctx.plan.adjoint_transfer(x, c, t, alpha=2.0, scale=scale, want_gx=ctx.needs_input_grad[0],
                                            want_gc=ctx.needs_input_grad[1])
         return _like(gx, x), _like(gc, c), None, None
