@@ -52,7 +52,8 @@ hipError_t core_fwd_launch(const CoreArgs& a, int precision, hipStream_t st);
 hipError_t core_adj_launch(const CoreArgs& a, int precision, float alpha, const float* scale_dev, hipStream_t st);
 size_t core_adj_part_bytes(int64_t R, int K, int J);  // sub = 1
 // Parts of a chunk for `bytes` of partials: as many as a workgroup per compute unit asks for
-// (23 chunks of R = 11520 on 23 workgroups, K = 120, 12 coils, FP32: 27.9 us; in 184 parts 7.4).
+// (23 chunks of R = 11520 on 23 workgroups, K = 120, 12 coils, FP32: 27.9 us; in 184 parts 7.4;
+// R = 64000, K = 300, 32 coils fills the chip as it is: in two parts 57 -> 68 us, BF16 54 -> 59).
 int core_adj_sub(const CoreGeom& g, int J, size_t bytes);
 
 }  // namespace mx
