@@ -55,6 +55,7 @@ struct Plan {
   const void *U2F = nullptr, *U2CF = nullptr;
   // dedicated core contraction kernels (Tucker basis, J <= 64)
   bool tucker_rows = false;      // general path: the products next to the coil images as streams
+  bool tucker_gx = false;        // and the image gradient with them
   bool core_direct = false;
   int core_sub = 1;              // parts of a chunk of the core's adjoint (CoreArgs::sub)
   CoreGeom cg{};

@@ -732,6 +732,7 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
   }
   p.tucker_rows = p.basis_kind == MAXWELL_BASIS_TUCKER && !p.fused &&
                   tucker_rows_supported(p.n[0], p.n[1], p.n[2], p.r[1], p.r[2], p.precision == MAXWELL_BF16_SPLIT);
+  p.tucker_gx = p.tucker_rows && tucker_images_gx_fits(p.n[0], p.n[1], p.J, p.precision == MAXWELL_BF16_SPLIT);
   if (p.basis_kind == MAXWELL_BASIS_TUCKER && core_supported(p.J)) {
     p.core_direct = true;
     p.cg = core_geom(p.r[0] * p.r[1] * p.r[2], (int)p.K);
@@ -1319,10 +1320,10 @@ static hipError_t adjoint_maps(const Plan& p, const float2* S, const float2* x, 
 }
 
 // Whether the image gradient is taken from maps that stay in registers, so that no map has to
-// be in memory for it: a Tucker basis always (also where maps are at hand: they would be read
-// again), a dense one where there are none.
+// be in memory for it: a Tucker basis where its rows fill the chip (also where maps are at hand:
+// they would be read again), a dense one where there are none.
 static bool maps_in_registers(const Plan& p, bool maps_ready) {
-  return p.basis_kind == MAXWELL_BASIS_DENSE ? p.stream_apply && !maps_ready : p.tucker_rows;
+  return p.basis_kind == MAXWELL_BASIS_DENSE ? p.stream_apply && !maps_ready : p.tucker_gx;
 }
 
 // gx and gc from g = F_s^H y in the K region and the maps in the S region, if they are there
@@ -1335,6 +1336,11 @@ static hipError_t adjoint_finish(const Plan& p, const float2* x, const float2* c
   const bool stream_gc = gc && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_adj;
   hipError_t e;
   if (p.tucker_rows) {
+    if (gx && !p.tucker_gx) {  // from the maps in memory
+      e = TIMED("adjoint_combine", adjoint_combine_launch(S, Kb, nullptr, p.N, p.J, alpha, scale_dev, gx, 0, st));
+      if (e != hipSuccess) return e;
+      return gc ? tucker_finish(p, x, Kb, alpha, scale_dev, nullptr, gc, ws, st) : hipSuccess;
+    }
     if (gx && !maps_ready) {  // T2
       float2* tA = wsp<float2>(ws, p.off_tA);
       GemmArgs a[4];

@@ -13,6 +13,8 @@ struct TuckerRows {
 };
 
 bool tucker_rows_supported(int64_t n0, int64_t n1, int64_t n2, int64_t r1, int64_t r2, int precision);
+// Whether tucker_images_launch is also the way to gx, rather than maps in memory and their combination.
+bool tucker_images_gx_fits(int64_t n0, int64_t n1, int J, int precision);
 // Stacks of coil images are 16-byte aligned.
 // S [J][n0][n1][n2] = T2 [J][n0][r1][r2] x_2 U1 x_3 U2
 hipError_t tucker_maps_launch(const TuckerRows& a, const float2* T2, float2* S, hipStream_t st);

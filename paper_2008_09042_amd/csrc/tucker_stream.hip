@@ -491,6 +491,19 @@ bool tucker_rows_supported(int64_t n0, int64_t n1, int64_t n2, int64_t r1, int64
   return (n1 + 15) / 16 * ((r1 + 15) / 16) * 2048 <= 160 * 1024;  // U1's fragments (mode1_adj)
 }
 
+// With gx a wave goes through all coils of its 16 rows, one wave per SIMD (1024 on the chip).
+// Where the rows leave half of them idle, the maps in memory with their combination, which
+// spread the coils over the chip, are faster from a few coils on (FP32, whose products take
+// longer, from fewer): the gradient in registers -> by maps, BF16-split and FP32, takes 267 -> 119
+// and 351 -> 121 us at 20^3, 128 coils, ranks 8; 207 -> 120 and 338 -> 136 at 36^3, 32 coils, ranks
+// 18; 133 -> 115 and 170 -> 126 at 60^3, 8 coils, ranks 20.  From 512 waves on the adjoint, which
+// would have to form the maps first, is faster or even in registers (90^3, 8 coils, ranks 32:
+// 142 against 172 by maps, 196 against 195; 120 x 100 x 90, 8 coils: 158 against 201, 204 against
+// 229), and so it is at one or two coils everywhere (20^3: 0.91-0.95 of the time by maps).
+bool tucker_images_gx_fits(int64_t n0, int64_t n1, int J, int precision) {
+  return n0 * ((n1 + 15) / 16) >= 512 || J <= (precision == 1 ? 4 : 2);
+}
+
 hipError_t tucker_maps_launch(const TuckerRows& a, const float2* T2, float2* S, hipStream_t st) {
   RowsArgs r = rows_args(a);
   r.T2 = T2;
