@@ -5,7 +5,7 @@
 // (tile rows k, reduction n) is conj(B) read down four rows per lane, two adjacent columns at
 // a time where rows are 16-byte aligned (256 contiguous bytes of a row per 16 lanes; the two
 // columns belong to two tiles); the B operand is h, 32 contiguous bytes per lane.  A
-// workgroup's eight waves are kw groups of 16 AKB columns times 8 / kw groups of rows; a wave
+// workgroup's eight waves are one or two groups of 16 AKB columns times groups of rows; a wave
 // loads the next 16 rows while it multiplies the current ones.  Every load is unconditional
 // (addresses clamped): a guarded load makes every use wait for all loads in flight.  The row
 // groups' tiles are added through LDS in a fixed order, one partial per workgroup, and a
@@ -26,12 +26,17 @@ constexpr int NW = 8, NT = 64 * NW;
 
 struct AdjGeom {
   int JB, AKB, jgs;  // 16-coil blocks and 16-column blocks per wave, coil groups
-  int kwl, ks;       // log2 of the column groups per workgroup, workgroups per row chunk along K
+  int kwl, ks;       // log2 of the column groups per workgroup (0 or 1), workgroups per row chunk along K
   int64_t chunk;     // rows per workgroup
   int nchunk;
 };
 
-// Waves: as many column groups as K needs (a power of two up to 8), the rest split the rows.
+// Waves: two column groups where K has two, and row groups.  A workgroup over all of K (up to
+// eight groups) left its partials, one per row chunk, to be most of the traffic of a short
+// basis, and each wave a step or two: 64 x 64, 17 coils, 300 columns, BF16-split 20.7 -> 12.1 us,
+// FP32 23.1 -> 14.5; 128 x 128, 32 coils, 512 columns 35.4 -> 23.4; 256 x 256, 32 coils, 200
+// columns 32.8 -> 28.4.  One group per workgroup reads h once per 64 columns: better up to
+// 256 x 256 (26.9), worse beyond (512 x 512, 16 coils, 100 columns 44.3 -> 52.3).
 // Row chunks: a workgroup per compute unit over all coil and column groups (two where the
 // tiles are small enough that two share one), at least one step of every row group, and no more
 // than max_chunks (0: no limit).
@@ -42,7 +47,7 @@ AdjGeom adj_geom(int64_t N, int64_t K, int J, int max_chunks) {
   a.jgs = (njb + a.JB - 1) / a.JB;
   a.AKB = a.JB < 4 && nkb > 2 ? 4 : 2;
   const int groups = (nkb + a.AKB - 1) / a.AKB;
-  a.kwl = groups > 4 ? 3 : groups > 2 ? 2 : groups > 1 ? 1 : 0;
+  a.kwl = groups > 1 ? 1 : 0;
   a.ks = (groups + (1 << a.kwl) - 1) >> a.kwl;
   const int64_t step = (int64_t)16 * (NW >> a.kwl);
   int64_t want = (a.JB == 1 ? 512 : 256) / ((int64_t)a.jgs * a.ks);
