@@ -413,8 +413,8 @@ const char* maxwell_last_error(void);
 const char* maxwell_version(void);
 
 /* Plan-time kernel choices: for a dense basis, plan creation times the streaming kernel
- * against the tiled GEMM at each split-K factor for both basis products and keeps the
- * fastest, per (GPU architecture, product, N, K, J, precision).  The choices are
+ * against the tiled GEMM at each split-K factor (and, for the gradients, with the passes that go
+ * with it) and keeps the fastest, per (GPU architecture, use, N, K, J, precision).  The choices are
  * kept for the process and in a tuning file, $MAXWELL_TUNE_CACHE if set (empty: none), else
  * $HOME/.cache/maxwell/tune.txt, so a later process reuses them without timing.
  * MAXWELL_GEMM_AUTOTUNE=0 skips the timing (the streaming kernels).  maxwell_tune_counts: the

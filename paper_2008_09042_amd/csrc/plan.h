@@ -63,7 +63,9 @@ struct Plan {
   float2* d_core_f32 = nullptr;      // FP32 core copies in fragment order (FP32 plans only)
   int G_fwd = 2, G_adj = 8;    // coils per plane workgroup (set at plan creation)
   int split_apply = 0, split_adj = 0;  // dense basis GEMMs: split-K factors tuned at plan creation
-  bool stream_apply = false, stream_adj = false;  // dense basis: streaming kernels chosen at plan creation
+  // dense basis: streaming kernels chosen at plan creation, for the maps, the image gradient without
+  // maps at hand, the adjoint, the coefficients' gradient
+  bool stream_apply = false, stream_gx = false, stream_adj = false, stream_gc = false;
   float gscale = 1.0f;         // prod_d (-1)^(n_d/2) / sqrt(N)
   // non-Cartesian sampling (Kaiser-Bessel NUFFT, 2D)
   int g[2] = {0, 0};             // oversampled grid

@@ -781,21 +781,24 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
       return hip_err(e);
   }
 
-  // dense basis: for each of the two basis products, the streaming kernel or the tiled GEMM at
-  // one split-K factor, picked by timing the candidates on scratch operands of
-  // the plan's shapes; the choices persist in the tuning cache (tune.h), keyed by the GPU
+  // dense basis: the streaming kernel or the tiled GEMM at one split-K factor, picked by timing
+  // what each caller runs on scratch operands of the plan's shapes: the maps; the image gradient
+  // without maps at hand (streamed, or the maps and their combination); the bare adjoint; the
+  // coefficients' gradient (streamed from g, or h = conj(x) (.) g written by the combination and the
+  // adjoint of it).  The choices persist in the tuning cache (tune.h), keyed by the GPU
   // architecture and the shape.  MAXWELL_GEMM_AUTOTUNE=0: the streaming kernels without timing.
   if (p.basis_kind == MAXWELL_BASIS_DENSE && !p.fused && p.J > 0 && p.K > 0 && p.N > 0) {
     const char* env = std::getenv("MAXWELL_GEMM_AUTOTUNE");
     if (env && env[0] == '0') {
-      p.stream_apply = p.stream_adj = true;
+      p.stream_apply = p.stream_gx = p.stream_adj = p.stream_gc = true;
     } else {
       const size_t nbuf = (size_t)p.J * std::max<int64_t>(p.N, p.K) * 8;  // c, S, h and gc all fit
       const size_t max_ws = (size_t)256 << 20;
-      void *bufA = nullptr, *bufC = nullptr, *bufW = nullptr;
+      void *bufA = nullptr, *bufC = nullptr, *bufW = nullptr, *bufX = nullptr;
       bool ok = hipMalloc(&bufA, nbuf) == hipSuccess && hipMalloc(&bufC, nbuf) == hipSuccess &&
-                hipMalloc(&bufW, max_ws) == hipSuccess && hipMemset(bufA, 0, nbuf) == hipSuccess &&
-                hipMemset(bufC, 0, nbuf) == hipSuccess;
+                hipMalloc(&bufW, max_ws) == hipSuccess && hipMalloc(&bufX, p.bytes_x()) == hipSuccess &&
+                hipMemset(bufA, 0, nbuf) == hipSuccess && hipMemset(bufC, 0, nbuf) == hipSuccess &&
+                hipMemset(bufX, 0, p.bytes_x()) == hipSuccess;
       if (ok) {
         const float2* A = reinterpret_cast<const float2*>(bufA);
         float2* C = reinterpret_cast<float2*>(bufC);
@@ -820,32 +823,52 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
         std::ostringstream shape;
         shape << device_arch() << " N=" << p.N << " K=" << p.K << " J=" << p.J << " prec=" << p.precision
               << " odd=" << ((reinterpret_cast<uintptr_t>(p.dense) & 15u) != 0 ? 1 : 0);
-        const int ca = tuned_choice("stream_apply " + shape.str(), [&]() -> int {
-          float gemm_ms = -1.f;
-          const int split = gemm_autotune(dense_apply_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm_ms);
+        float2* X = reinterpret_cast<float2*>(bufX);
+        auto faster = [](float a, float b) { return a > 0.f && (b <= 0.f || a < b); };
+        // a cached choice: the split, and a bit for each of the two uses that streams
+        const int ca = tuned_choice("maps and gx " + shape.str(), [&]() -> int {
+          float gemm = -1.f;
+          const int split = gemm_autotune(dense_apply_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm);
           const float sk = time_ms([&]() { return stream_apply_launch(p.dense, p.N, p.K, A, p.J, p.precision, C, 0); });
-          return (sk > 0.f && (gemm_ms <= 0.f || sk < gemm_ms)) ? -1 : split;
-        });
-        const int cd = tuned_choice("stream_adjoint " + shape.str(), [&]() -> int {
-          float gemm_ms = -1.f;
-          const int split = gemm_autotune(dense_adjoint_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm_ms);
-          if (stream_adjoint_bytes(p.N, p.K, p.J, 0) > max_ws) return split;
-          const float sk = time_ms([&]() {
-            return stream_adjoint_launch(p.dense, p.N, p.K, A, nullptr, p.J, p.precision, 1.0f, nullptr, bufW, 0, C, 0);
+          const float gx = time_ms([&]() {
+            return stream_gx_launch(p.dense, p.N, p.K, A, p.J, p.precision, C, 1.0f, nullptr, X, 0);
           });
-          return (sk > 0.f && (gemm_ms <= 0.f || sk < gemm_ms)) ? -1 : split;
+          const float comb = time_ms([&]() { return adjoint_combine_launch(A, C, nullptr, p.N, p.J, 1.0f, nullptr, X, 0, 0); });
+          const float maps = faster(sk, gemm) ? sk : gemm;
+          return split * 4 + (faster(gx, maps > 0.f && comb > 0.f ? maps + comb : -1.f) ? 2 : 0) + (faster(sk, gemm) ? 1 : 0);
         });
-        p.stream_apply = ca < 0;
-        p.stream_adj = cd < 0;
-        p.split_apply = ca < 0 ? 0 : ca;
-        p.split_adj = cd < 0 ? 0 : cd;
+        const int cd = tuned_choice("adjoint and gc " + shape.str(), [&]() -> int {
+          float gemm = -1.f;
+          const int split = gemm_autotune(dense_adjoint_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm);
+          if (stream_adjoint_bytes(p.N, p.K, p.J, 0) > max_ws) return split * 4;
+          auto adjoint = [&](const float2* x) {
+            return time_ms([&]() {
+              return stream_adjoint_launch(p.dense, p.N, p.K, A, x, p.J, p.precision, 1.0f, nullptr, bufW, 0, C, 0);
+            });
+          };
+          auto combine = [&](int want_h) {
+            return time_ms([&]() { return adjoint_combine_launch(A, C, X, p.N, p.J, 1.0f, nullptr, X, want_h, 0); });
+          };
+          const float sk = adjoint(nullptr), skx = adjoint(X), gx = combine(0), gxh = combine(1);
+          const float bare = faster(sk, gemm) ? sk : gemm;
+          const bool gc = faster(skx + gx, bare > 0.f ? bare + gxh : -1.f);
+          return split * 4 + (skx > 0.f && gx > 0.f && gc ? 2 : 0) + (faster(sk, gemm) ? 1 : 0);
+        });
+        p.stream_apply = ca & 1;
+        p.stream_gx = ca & 2;
+        p.stream_adj = cd & 1;
+        p.stream_gc = cd & 2;
+        // the splits where a GEMM is left to run: the workspace is sized by them
+        p.split_apply = p.stream_apply ? 0 : ca / 4;
+        p.split_adj = p.stream_adj ? 0 : cd / 4;
       } else {
-        p.stream_apply = p.stream_adj = true;
+        p.stream_apply = p.stream_gx = p.stream_adj = p.stream_gc = true;
       }
       (void)hipStreamSynchronize(0);
       if (bufA) (void)hipFree(bufA);
       if (bufC) (void)hipFree(bufC);
       if (bufW) (void)hipFree(bufW);
+      if (bufX) (void)hipFree(bufX);
       (void)hipGetLastError();
     }
   }
@@ -919,7 +942,7 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
     off += (5 + 2 * p.ndim) * NB + 5 * al(JM) + al((size_t)ball_part_doubles(p.J) * sizeof(double)) +
            al(ADMM_SCALARS * sizeof(double));
   }
-  if (p.stream_adj) {
+  if (p.stream_adj || p.stream_gc) {
     // The dense adjoint's row-chunk partials go where nothing lives while it runs: the maps'
     // region (the image gradient has read them) or the samples' and the GEMMs', which adjoin.
     // Where neither holds them they get a region of their own, unless that alone would make the
@@ -934,7 +957,7 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
       } else if (room >= row) {
         p.adj_chunks = (int)std::min<size_t>(room / row, INT32_MAX);
       } else {
-        p.stream_adj = false;  // the tiled GEMM, whose region is counted above
+        p.stream_adj = p.stream_gc = false;  // the tiled GEMM, whose region is counted above
       }
     }
   }
@@ -1323,7 +1346,7 @@ static hipError_t adjoint_maps(const Plan& p, const float2* S, const float2* x, 
 // be in memory for it: a Tucker basis where its rows fill the chip (also where maps are at hand:
 // they would be read again), a dense one where there are none.
 static bool maps_in_registers(const Plan& p, bool maps_ready) {
-  return p.basis_kind == MAXWELL_BASIS_DENSE ? p.stream_apply && !maps_ready : p.tucker_gx;
+  return p.basis_kind == MAXWELL_BASIS_DENSE ? p.stream_gx && !maps_ready : p.tucker_gx;
 }
 
 // gx and gc from g = F_s^H y in the K region and the maps in the S region, if they are there
@@ -1333,7 +1356,7 @@ static hipError_t adjoint_finish(const Plan& p, const float2* x, const float2* c
                                  float2* gx, float2* gc, void* ws, hipStream_t st, bool maps_ready) {
   float2* S = wsp<float2>(ws, p.off_S);
   float2* Kb = wsp<float2>(ws, p.off_K);
-  const bool stream_gc = gc && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_adj;
+  const bool stream_gc = gc && p.basis_kind == MAXWELL_BASIS_DENSE && p.stream_gc;
   hipError_t e;
   if (p.tucker_rows) {
     if (gx && !p.tucker_gx) {  // from the maps in memory

@@ -1,8 +1,8 @@
 // Persistent cache of plan-time kernel choices (host code).
 //
 // A plan picks some kernels per shape by timing the candidates on the device (the dense
-// basis products: the streaming kernel against the tiled GEMM at each split-K factor).  The
-// choices are kept for the process and in a text file keyed by shape and GPU architecture,
+// basis products and the gradients made of them: the streaming kernel against the tiled GEMM at
+// each split-K factor).  The choices are kept for the process and in a text file keyed by shape and GPU architecture,
 // so that a later process on the same kind of GPU reuses them instead of timing again.
 #include <hip/hip_runtime.h>
 
