@@ -224,6 +224,90 @@ __global__ __launch_bounds__(NT) void stream_apply_kernel(const float2* __restri
   }
 }
 
+// The maps of at most 16 columns (one K16 step) and 32 coils over many rows: a workgroup that takes its rows and
+// ends is mostly its start, the fragments of c behind a barrier.  Here a wave goes through row
+// blocks with the rows of four in flight, and c's operands stay in registers.  BF16-split, the kernel
+// above against this one: 1500 x 1500, 2 coils, 4 columns 43.4 -> 32.8 us; 2000 x 2000, 1 coil, 4
+// columns 70.1 -> 49.9 (c's fragments in their own launch: 38.8 and 57.9); 1024 x 1024, 20 coils, 8
+// columns 55.8 -> 36.8.
+constexpr int NARROW_GRID = 512;  // two workgroups per compute unit; 1024: 33.4, 50.2 and 43.0 us
+template <int PREC, int JB, int VEC>
+__global__ __launch_bounds__(NT) void stream_narrow_kernel(const float2* __restrict__ B, int64_t N, int K,
+                                                           const float2* __restrict__ c, int J, float2* __restrict__ S) {
+  constexpr int RB = 2;
+  const int lane = threadIdx.x % 64, g = lane / 16, c16 = lane % 16, k = 4 * g;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), nw = blockDim.x / 64;
+  const int64_t stride = (int64_t)gridDim.x * nw * (16 * RB);
+  int64_t n0 = ((int64_t)blockIdx.x * nw + wave) * (16 * RB);
+  struct Raw { float2 v[RB][4]; };
+  auto fetch = [&](Raw& raw, int64_t first) {  // clamped into B: past the last row, that row again
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int64_t n = first + rb * 16 + c16;
+      const float2* row = B + (n < N ? n : N - 1) * K;
+      if constexpr (VEC == 2) {
+        const float4 a = *reinterpret_cast<const float4*>(row + min(k, K - 2));
+        const float4 b = *reinterpret_cast<const float4*>(row + min(k + 2, K - 2));
+        raw.v[rb][0] = make_float2(a.x, a.y);
+        raw.v[rb][1] = make_float2(a.z, a.w);
+        raw.v[rb][2] = make_float2(b.x, b.y);
+        raw.v[rb][3] = make_float2(b.z, b.w);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) raw.v[rb][t] = row[min(k + t, K - 1)];
+      }
+    }
+  };
+  Raw raw[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) fetch(raw[u], n0 + u * stride);
+  typename Tile<PREC>::A a[JB];
+#pragma unroll
+  for (int jb = 0; jb < JB; ++jb) {
+    const int j = jb * 16 + c16;
+    float2 v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const bool ok = j < J && k + t < K;
+      const float2 w = c[ok ? (int64_t)j * K + k + t : 0];
+      v[t] = ok ? w : make_float2(0.f, 0.f);
+    }
+    a[jb] = Tile<PREC>::make_a(v);
+  }
+  for (;;) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (n0 >= N) return;
+      f32x4 cr[RB][JB], ci[RB][JB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        float2 v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = k + t < K ? raw[u].v[rb][t] : make_float2(0.f, 0.f);
+        const typename Tile<PREC>::B b = Tile<PREC>::make_b(v);
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) {
+          cr[rb][jb] = ci[rb][jb] = z4();
+          Tile<PREC>::mma(cr[rb][jb], ci[rb][jb], a[jb], b);
+        }
+      }
+      fetch(raw[u], n0 + 4 * stride);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const int64_t n = n0 + rb * 16 + c16;
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int j = jb * 16 + 4 * g + r;
+            if (j < J && n < N) S[(int64_t)j * N + n] = make_float2(cr[rb][jb][r], ci[rb][jb][r]);
+          }
+      }
+      n0 += stride;
+    }
+  }
+}
+
 struct ApplyCall {
   const float2* B;
   int64_t N;
@@ -252,6 +336,12 @@ hipError_t launch_few(const ApplyCall& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int PREC, int JB, int VEC>
+hipError_t launch_narrow(const ApplyCall& a, hipStream_t st) {
+  hipLaunchKernelGGL((stream_narrow_kernel<PREC, JB, VEC>), dim3(NARROW_GRID), dim3(NT), 0, st, a.B, a.N, a.K, a.c, a.J, a.S);
+  return hipGetLastError();
+}
+
 template <int PREC, int JB, int RB, int VEC, bool GX>
 hipError_t launch(const ApplyCall& a, hipStream_t st) {
   return a.K <= 64 ? launch_few<PREC, JB, RB, VEC, GX, true>(a, st) : launch_few<PREC, JB, RB, VEC, GX, false>(a, st);
@@ -275,6 +365,15 @@ hipError_t dispatch(ApplyCall a, hipStream_t st) {
   }
   const bool vec = a.K % 2 == 0 && (reinterpret_cast<uintptr_t>(a.B) & 15u) == 0;
   const int jb = a.J <= 16 ? 0 : a.J <= 32 || GX ? 1 : 2;
+  // Few columns, and four blocks of 32 rows for every wave of the narrow kernel: 1000 x 1000, 1 coil, 4
+  // columns 19.9 -> 16.6 us, 512 x 512, 2 coils, 4 columns 6.6 -> 7.6.  Past 32 coils it has no
+  // registers for the rows in flight (1024 x 1024, 40 coils, 16 columns 107 -> 116).
+  if constexpr (!GX) {
+    if (jb < 2 && a.K <= 16 && a.N >= (int64_t)4 * NARROW_GRID * NT / 64 * 32) {
+      if (jb == 0) return vec ? launch_narrow<PREC, 1, 2>(a, st) : launch_narrow<PREC, 1, 1>(a, st);
+      return vec ? launch_narrow<PREC, 2, 2>(a, st) : launch_narrow<PREC, 2, 1>(a, st);
+    }
+  }
   switch (jb * 4 + (wide ? 2 : 0) + (vec ? 1 : 0)) {
     case 0: return launch<PREC, 1, 1, 1, GX>(a, st);
     case 1: return launch<PREC, 1, 1, 2, GX>(a, st);
