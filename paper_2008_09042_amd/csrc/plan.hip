@@ -837,6 +837,8 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
           const float maps = faster(sk, gemm) ? sk : gemm;
           return split * 4 + (faster(gx, maps > 0.f && comb > 0.f ? maps + comb : -1.f) ? 2 : 0) + (faster(sk, gemm) ? 1 : 0);
         });
+        p.stream_apply = ca & 1;
+        p.stream_gx = ca & 2;
         const int cd = tuned_choice("adjoint and gc " + shape.str(), [&]() -> int {
           float gemm = -1.f;
           const int split = gemm_autotune(dense_adjoint_args(p, A, C), p.precision, bufW, max_ws, 0, &gemm);
@@ -846,16 +848,14 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
               return stream_adjoint_launch(p.dense, p.N, p.K, A, x, p.J, p.precision, 1.0f, nullptr, bufW, 0, C, 0);
             });
           };
-          auto combine = [&](int want_h) {
-            return time_ms([&]() { return adjoint_combine_launch(A, C, X, p.N, p.J, 1.0f, nullptr, X, want_h, 0); });
+          auto combine = [&](float2* gx, int want_h) {
+            return time_ms([&]() { return adjoint_combine_launch(A, C, X, p.N, p.J, 1.0f, nullptr, gx, want_h, 0); });
           };
-          const float sk = adjoint(nullptr), skx = adjoint(X), gx = combine(0), gxh = combine(1);
-          const float bare = faster(sk, gemm) ? sk : gemm;
-          const bool gc = faster(skx + gx, bare > 0.f ? bare + gxh : -1.f);
-          return split * 4 + (skx > 0.f && gx > 0.f && gc ? 2 : 0) + (faster(sk, gemm) ? 1 : 0);
+          // h is a pass of its own where gx is streamed, a write more in the combination elsewhere
+          const float gx = p.stream_gx ? 0.f : combine(X, 0), h = combine(p.stream_gx ? nullptr : X, 1) - gx;
+          const float sk = adjoint(nullptr), skx = adjoint(X), bare = faster(sk, gemm) ? sk : gemm;
+          return split * 4 + (faster(skx, bare > 0.f ? bare + h : -1.f) ? 2 : 0) + (faster(sk, gemm) ? 1 : 0);
         });
-        p.stream_apply = ca & 1;
-        p.stream_gx = ca & 2;
         p.stream_adj = cd & 1;
         p.stream_gc = cd & 2;
         // the splits where a GEMM is left to run: the workspace is sized by them
