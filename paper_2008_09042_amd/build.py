@@ -14,8 +14,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libmaxwell.so")
-SOURCES = ["api.hip", "plan.hip", "gemm.hip", "fft_tr16.hip", "fft_tr32.hip", "fft.hip", "elementwise.hip", "nufft.hip", "tucker_fused.hip", "core_contract.hip",
-           "mode3.hip", "solver.hip", "admm.hip", "compress.hip", "stream_apply.hip", "stream_adjoint.hip", "tucker_stream.hip", "fft_combine.hip", "diag.hip", "tune.hip"]
+SOURCES = ["api.hip", "plan.hip", "gemm.hip", "fft_tr16.hip", "fft_tr16_grid.hip", "fft_tr16_multi.hip", "fft_tr32.hip",
+           "fft_tr32_grid.hip", "fft_tr32_multi.hip", "fft.hip", "elementwise.hip", "nufft.hip", "tucker_fused.hip",
+           "core_contract.hip", "mode3.hip", "solver.hip", "admm.hip", "compress.hip", "stream_maps_fp32.hip",
+           "stream_maps_bf16.hip", "stream_gx_fp32.hip", "stream_gx_bf16.hip", "stream_adjoint_fp32.hip",
+           "stream_adjoint_bf16.hip", "tucker_rows_fp32.hip", "tucker_rows_bf16.hip", "fft_combine.hip", "diag.hip",
+           "tune.hip"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed FP32 instructions are disabled for all device code.

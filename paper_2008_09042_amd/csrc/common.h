@@ -141,8 +141,11 @@ void fft_collect(std::vector<FftLaunch>* sink);
 // Launches prepared passes of independent arrays, several per launch.
 hipError_t fft_multi_launch(const std::vector<FftLaunch>& ls, hipStream_t st);
 // The two-radix kernel's launches, radices up to 16 and up to 32.
+constexpr int TR_GRID_FIRST = 4, TR_GRID_LAST = 7;  // the variants of a gridding window
 hipError_t fft_tr16_launch(const FftLaunch& l, hipStream_t st);
 hipError_t fft_tr32_launch(const FftLaunch& l, hipStream_t st);
+hipError_t fft_tr16_grid(const FftLaunch& l, hipStream_t st);
+hipError_t fft_tr32_grid(const FftLaunch& l, hipStream_t st);
 hipError_t fft_tr16_multi(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st);
 hipError_t fft_tr32_multi(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st);
 // out [rows][n] = sum_j conj(S_j) (.) (the inverse centred transform of src_j along its rows), for

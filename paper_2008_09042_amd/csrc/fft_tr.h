@@ -1,6 +1,9 @@
 // Two-radix form of the batched centred DFT along one axis (the operator F of fft.hip, whose
 // data layout, fused sampling and gridding window it shares): the kernel and its launches,
-// instantiated for radices up to 16 (fft_tr16.hip) and up to 32 (fft_tr32.hip).
+// instantiated for radices up to 16 and up to 32, each with the passes of an image (fft_tr16.hip,
+// fft_tr32.hip), of a gridding window (fft_tr16_grid.hip, fft_tr32_grid.hip) and of several slices
+// in one launch (fft_tr16_multi.hip, fft_tr32_multi.hip) in a file of its own: a process loads a
+// file's kernels with the first that it launches.
 #pragma once
 
 #include <cstring>
@@ -363,7 +366,7 @@ __device__ __forceinline__ void tr_pass1(const FftAxisArgs& a, const float2* lds
   }
 }
 
-// BIG: radices up to 32 (about twice the registers), else up to 16.
+// BIG: radices up to 32 (about twice the registers), R0, the larger, above 16; else up to 16.
 template <int SMP, int DIR, bool BIG>
 __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_in, uint32_t nbl) {
   extern __shared__ float2 lds[];
@@ -391,7 +394,7 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
   }
 #define TR_P0(R) case R: tr_pass0<SMP, DIR, R>(a, lds, s, o0, t0); break;
   if constexpr (BIG) {
-    switch (a.tr_r0.d) { TR_SMALL(TR_P0) TR_LARGE(TR_P0) default: break; }
+    switch (a.tr_r0.d) { TR_LARGE(TR_P0) default: break; }
   } else {
     switch (a.tr_r0.d) { TR_SMALL(TR_P0) default: break; }
   }
@@ -411,7 +414,7 @@ __device__ __forceinline__ void fft_tr_body(const FftAxisArgs& a, uint32_t bid_i
     const float scale = SMP == 8 ? 1.f / (float)n : rsqrtf((float)n);
 #define TR_P1(R) case R: tr_pass1<SMP, 1, R>(a, lds, tw, a.tr_r1, s.LL, s.JP, s.RP, o0, t0, scale, acc); break;
     if constexpr (BIG) {
-      switch (a.tr_r0.d) { TR_SMALL(TR_P1) TR_LARGE(TR_P1) default: break; }
+      switch (a.tr_r0.d) { TR_LARGE(TR_P1) default: break; }
     } else {
       switch (a.tr_r0.d) { TR_SMALL(TR_P1) default: break; }
     }
@@ -457,35 +460,33 @@ __global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 || (!BIG && SMP >=
 }  // namespace
 
 // Kernel variants: what the pass reads and writes (its direction follows, except for plain
-// passes)
-#define TR_VARIANTS(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1) F(8, 8, -1) \
-  F(9, 9, -1) F(10, 10, -1)
+// passes), of an image and of a gridding window
+#define TR_IMAGE(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(8, 8, -1) F(9, 9, -1) F(10, 10, -1)
+#define TR_GRID(F) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1)
 // the forward pass with the residual is prepared for radices up to 16 alone
 #define TR_BUILT(SMP) (BIG && SMP == 9 ? 10 : SMP)
 
-template <bool BIG>
+template <bool BIG, bool GRID>
 hipError_t tr_launch_one(const FftLaunch& l, hipStream_t st) {
   const dim3 gr((unsigned)l.blocks), bl((unsigned)l.threads);
-  switch (l.variant) {
 #define TR_LAUNCH(I, SMP, DIR) \
   case I: hipLaunchKernelGGL((fft_tr_kernel<TR_BUILT(SMP), DIR, BIG>), gr, bl, l.lds, st, l.a); break;
-    TR_VARIANTS(TR_LAUNCH)
-#undef TR_LAUNCH
-    default: return hipErrorInvalidValue;
+  if constexpr (GRID) {
+    switch (l.variant) { TR_GRID(TR_LAUNCH) default: return hipErrorInvalidValue; }
+  } else {
+    switch (l.variant) { TR_IMAGE(TR_LAUNCH) default: return hipErrorInvalidValue; }
   }
+#undef TR_LAUNCH
   return hipGetLastError();
 }
 
 template <bool BIG>
 hipError_t tr_launch_many(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st) {
   const dim3 gr((unsigned)m.start[m.n]), bl((unsigned)threads);
-  switch (variant) {
 #define TR_LAUNCH(I, SMP, DIR) \
   case I: hipLaunchKernelGGL((fft_tr_multi_kernel<TR_BUILT(SMP), DIR, BIG>), gr, bl, lds, st, m); break;
-    TR_VARIANTS(TR_LAUNCH)
+  switch (variant) { TR_IMAGE(TR_LAUNCH) TR_GRID(TR_LAUNCH) default: return hipErrorInvalidValue; }
 #undef TR_LAUNCH
-    default: return hipErrorInvalidValue;
-  }
   return hipGetLastError();
 }
 

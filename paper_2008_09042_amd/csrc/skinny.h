@@ -1,4 +1,4 @@
-// Dense basis products as streams of the basis (stream_apply.hip, stream_adjoint.hip).
+// Dense basis products as streams of the basis (stream_apply.h, stream_adjoint.h).
 #pragma once
 
 #include "common.h"

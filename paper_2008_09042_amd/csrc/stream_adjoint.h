@@ -13,12 +13,32 @@
 //
 // 256 x 256, 32 coils, 200 columns (105 MB of basis), BF16-split: 59 + 5 us (tiled GEMM and its
 // split sum) -> 31 + 4 us.
+//
+// Kernels and dispatch, compiled for each precision in a file of its own (stream_adjoint_*.hip).
+#pragma once
+
 #include "mfma_frag.h"
 #include "skinny.h"
 
 #include <algorithm>
 
 namespace mx {
+
+// c [J][K] = s B^H h, or of conj(x) (.) h when x is given; part holds the row chunks' partials.
+struct AdjCall {
+  const float2* B;
+  int64_t N;
+  int K;
+  const float2 *h, *x;
+  int J;
+  float2* part;
+  int max_chunks;
+  float alpha;
+  const float* alpha_dev;
+  float2* c;
+};
+hipError_t stream_adjoint_fp32(const AdjCall& a, hipStream_t st);
+hipError_t stream_adjoint_bf16(const AdjCall& a, hipStream_t st);
 
 namespace {
 
@@ -239,15 +259,6 @@ __global__ __launch_bounds__(RNT) void stream_reduce_kernel(const float2* __rest
   out[e] = cscale(v, sc);
 }
 
-struct AdjCall {
-  const float2* B;
-  int64_t N;
-  int K;
-  const float2 *h, *x;
-  int J;
-  float2* part;
-};
-
 template <int PREC, int JB, int AKB, int VEC, bool X>
 hipError_t launch(const AdjCall& a, const AdjGeom& q, hipStream_t st) {
   const int RW = NW >> q.kwl;
@@ -268,37 +279,25 @@ hipError_t dispatch(const AdjCall& a, const AdjGeom& q, hipStream_t st) {
   }
 }
 
-}  // namespace
-
-size_t stream_adjoint_bytes(int64_t N, int64_t K, int J, int max_chunks) {
-  if (N <= 0 || K <= 0 || J <= 0) return 0;
-  return (size_t)adj_geom(N, K, J, max_chunks).nchunk * (size_t)J * (size_t)K * sizeof(float2);
-}
-
-hipError_t stream_adjoint_launch(const float2* B, int64_t N, int64_t K, const float2* g, const float2* x, int J,
-                                 int precision, float alpha, const float* alpha_dev, void* ws, int max_chunks,
-                                 float2* c, hipStream_t st) {
-  if (N <= 0 || K <= 0 || J <= 0) return hipSuccess;
-  const AdjGeom q = adj_geom(N, K, J, max_chunks);
-  const AdjCall a{B, N, (int)K, g, x, J, reinterpret_cast<float2*>(ws)};
+template <int PREC>
+hipError_t adjoint(const AdjCall& a, hipStream_t st) {
+  const AdjGeom q = adj_geom(a.N, a.K, a.J, a.max_chunks);
   auto odd = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; };
-  const bool vec = K % 2 == 0 && N % 2 == 0 && !odd(B) && !odd(g) && !odd(x);
+  const bool vec = a.K % 2 == 0 && a.N % 2 == 0 && !odd(a.B) && !odd(a.h) && !odd(a.x);
   hipError_t e;
-  switch ((precision == 1 ? 4 : 0) + (vec ? 2 : 0) + (x ? 1 : 0)) {
-    case 0: e = dispatch<0, 1, false>(a, q, st); break;
-    case 1: e = dispatch<0, 1, true>(a, q, st); break;
-    case 2: e = dispatch<0, 2, false>(a, q, st); break;
-    case 3: e = dispatch<0, 2, true>(a, q, st); break;
-    case 4: e = dispatch<1, 1, false>(a, q, st); break;
-    case 5: e = dispatch<1, 1, true>(a, q, st); break;
-    case 6: e = dispatch<1, 2, false>(a, q, st); break;
-    default: e = dispatch<1, 2, true>(a, q, st); break;
+  switch ((vec ? 2 : 0) + (a.x ? 1 : 0)) {
+    case 0: e = dispatch<PREC, 1, false>(a, q, st); break;
+    case 1: e = dispatch<PREC, 1, true>(a, q, st); break;
+    case 2: e = dispatch<PREC, 2, false>(a, q, st); break;
+    default: e = dispatch<PREC, 2, true>(a, q, st); break;
   }
   if (e != hipSuccess) return e;
-  const int64_t JK = (int64_t)J * K;
+  const int64_t JK = (int64_t)a.J * a.K;
   const unsigned rb = (unsigned)((JK + RNT / RG - 1) / (RNT / RG));
-  hipLaunchKernelGGL(stream_reduce_kernel, dim3(rb), dim3(RNT), 0, st, a.part, q.nchunk, JK, alpha, alpha_dev, c);
+  hipLaunchKernelGGL(stream_reduce_kernel, dim3(rb), dim3(RNT), 0, st, a.part, q.nchunk, JK, a.alpha, a.alpha_dev, a.c);
   return hipGetLastError();
 }
+
+}  // namespace
 
 }  // namespace mx

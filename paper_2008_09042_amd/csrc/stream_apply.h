@@ -16,10 +16,34 @@
 //
 // 256 x 256, 32 coils, 200 columns (105 MB of basis), BF16-split: apply 34 + 3 (c fragments in
 // their own launch) -> 25.5 us; rebuilt maps and coil combination 34 + 3 + 11 -> 25.8 us.
+//
+// Kernels and dispatch; the maps and the image gradient of each precision are compiled in a file
+// of their own (stream_maps_*.hip, stream_gx_*.hip), so that a process loads the code that it runs.
+#pragma once
+
 #include "mfma_frag.h"
 #include "skinny.h"
 
 namespace mx {
+
+// One call of either product; S for the maps, g, alpha, alpha_dev and gx for the image gradient.
+struct ApplyCall {
+  const float2* B;
+  int64_t N;
+  int K;
+  const float2* c;
+  int J;
+  float2* S;
+  const float2* g;
+  float alpha;
+  const float* alpha_dev;
+  float2* gx;
+  int nw;  // waves per workgroup
+};
+hipError_t stream_maps_fp32(const ApplyCall& a, hipStream_t st);
+hipError_t stream_maps_bf16(const ApplyCall& a, hipStream_t st);
+hipError_t stream_gx_fp32(const ApplyCall& a, hipStream_t st);
+hipError_t stream_gx_bf16(const ApplyCall& a, hipStream_t st);
 
 namespace {
 
@@ -308,20 +332,6 @@ __global__ __launch_bounds__(NT) void stream_narrow_kernel(const float2* __restr
   }
 }
 
-struct ApplyCall {
-  const float2* B;
-  int64_t N;
-  int K;
-  const float2* c;
-  int J;
-  float2* S;
-  const float2* g;
-  float alpha;
-  const float* alpha_dev;
-  float2* gx;
-  int nw;  // waves per workgroup
-};
-
 template <int PREC, int JB, int RB, int VEC, bool GX, bool FEW>
 hipError_t launch_few(const ApplyCall& a, hipStream_t st) {
   const int steps = (a.K + 15) / 16;
@@ -397,19 +407,5 @@ hipError_t dispatch(ApplyCall a, hipStream_t st) {
 }
 
 }  // namespace
-
-hipError_t stream_apply_launch(const float2* B, int64_t N, int64_t K, const float2* c, int J, int precision, float2* S,
-                               hipStream_t st) {
-  if (N <= 0 || K <= 0 || J <= 0) return hipSuccess;
-  const ApplyCall a{B, N, (int)K, c, J, S, nullptr, 1.f, nullptr, nullptr, 8};
-  return precision == 1 ? dispatch<1, false>(a, st) : dispatch<0, false>(a, st);
-}
-
-hipError_t stream_gx_launch(const float2* B, int64_t N, int64_t K, const float2* c, int J, int precision,
-                            const float2* g, float alpha, const float* alpha_dev, float2* gx, hipStream_t st) {
-  if (N <= 0 || K <= 0 || J <= 0) return hipSuccess;
-  const ApplyCall a{B, N, (int)K, c, J, nullptr, g, alpha, alpha_dev, gx, 8};
-  return precision == 1 ? dispatch<1, true>(a, st) : dispatch<0, true>(a, st);
-}
 
 }  // namespace mx

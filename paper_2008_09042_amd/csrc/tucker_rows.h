@@ -17,10 +17,29 @@
 // gradients 28 + 45 (maps again) + 33 (combination) + 40 + 34 us, here 45 + 10.  The image
 // kernel runs one wave per SIMD (its tiles take most of the registers); with a branch per
 // tile instead of compiled tile counts it took 56 us.
+//
+// Kernels and dispatch, compiled for each precision in a file of its own (tucker_rows_*.hip).
+#pragma once
+
 #include "mfma_frag.h"
 #include "tucker_stream.h"
 
 namespace mx {
+
+struct RowsArgs {
+  int64_t n1, rows16;  // rows16: row blocks of one i0
+  int n0, n2, r1, r2, J, jc;
+  const float2 *T2, *U1, *U2, *x, *g;
+  float alpha;
+  const float* alpha_dev;
+  float2 *S, *gx, *Q3;
+};
+hipError_t tucker_maps_fp32(const RowsArgs& r, hipStream_t st);
+hipError_t tucker_maps_bf16(const RowsArgs& r, hipStream_t st);
+hipError_t tucker_images_fp32(const RowsArgs& r, hipStream_t st);
+hipError_t tucker_images_bf16(const RowsArgs& r, hipStream_t st);
+hipError_t tucker_mode1_fp32(const TuckerRows& a, const float2* Q3, float2* Q2, hipStream_t st);
+hipError_t tucker_mode1_bf16(const TuckerRows& a, const float2* Q3, float2* Q2, hipStream_t st);
 
 namespace {
 
@@ -179,15 +198,6 @@ struct RowTile {
     v[2] = b[0];
     v[3] = b[1];
   }
-};
-
-struct RowsArgs {
-  int64_t n1, rows16;  // rows16: row blocks of one i0
-  int n0, n2, r1, r2, J, jc;
-  const float2 *T2, *U1, *U2, *x, *g;
-  float alpha;
-  const float* alpha_dev;
-  float2 *S, *gx, *Q3;
 };
 
 template <int PREC, int PT>
@@ -406,21 +416,6 @@ __global__ __launch_bounds__(64 * NW, 2) void tucker_mode1_adj_kernel(const floa
           out[(q * 16 + 4 * g + t) * r2 + pb * 16 + c16] = make_float2(cr[q][pb][t], ci[q][pb][t]);
 }
 
-RowsArgs rows_args(const TuckerRows& a) {
-  RowsArgs r{};
-  r.n1 = a.n1;
-  r.rows16 = (a.n1 + 15) / 16;
-  r.n0 = (int)a.n0;
-  r.n2 = (int)a.n2;
-  r.r1 = (int)a.r1;
-  r.r2 = (int)a.r2;
-  r.J = a.J;
-  r.jc = a.J;
-  r.U1 = a.U1;
-  r.U2 = a.U2;
-  return r;
-}
-
 // Coils per workgroup where they need not share one: about 1024 workgroups, four waves per
 // SIMD, before a wave keeps its rows' operands for another coil.
 int64_t row_grid(RowsArgs& r, bool split) {
@@ -471,63 +466,28 @@ hipError_t mode1_adj(const TuckerRows& a, const float2* Q3, float2* Q2, hipStrea
   return hipGetLastError();
 }
 
-#define BY_RANK(CALL)                                              \
-  switch (a.precision * 3 + (int)((a.r2 + 15) / 16) - 1) {         \
-    case 0: { constexpr int PREC = 0, PT = 1; return CALL; }       \
-    case 1: { constexpr int PREC = 0, PT = 2; return CALL; }       \
-    case 2: { constexpr int PREC = 0, PT = 3; return CALL; }       \
-    case 3: { constexpr int PREC = 1, PT = 1; return CALL; }       \
-    case 4: { constexpr int PREC = 1, PT = 2; return CALL; }       \
-    case 5: { constexpr int PREC = 1, PT = 3; return CALL; }       \
-    default: return hipErrorInvalidValue;                          \
+#define BY_RANK(r2, CALL)                       \
+  switch (((r2) + 15) / 16) {                   \
+    case 1: { constexpr int PT = 1; return CALL; } \
+    case 2: { constexpr int PT = 2; return CALL; } \
+    case 3: { constexpr int PT = 3; return CALL; } \
+    default: return hipErrorInvalidValue;       \
   }
 
-}  // namespace
-
-bool tucker_rows_supported(int64_t n0, int64_t n1, int64_t n2, int64_t r1, int64_t r2, int precision) {
-  if (n0 * n1 * n2 >= (int64_t)1 << 29) return false;  // 32-bit offsets into an image
-  if (precision != 0 && precision != 1) return false;
-  if (n2 < 2 || n2 > 128 || n2 % 2 || r1 < 1 || r2 < 1 || r1 > 16 * RANK_TILES || r2 > 16 * RANK_TILES) return false;
-  return (n1 + 15) / 16 * ((r1 + 15) / 16) * 2048 <= 160 * 1024;  // U1's fragments (mode1_adj)
+template <int PREC>
+hipError_t maps_by_rank(const RowsArgs& r, hipStream_t st) {
+  BY_RANK(r.r2, (maps<PREC, PT>(r, st)))
 }
-
-// With gx a wave goes through all coils of its 16 rows, one wave per SIMD (1024 on the chip).
-// Where the rows leave half of them idle, the maps in memory with their combination, which
-// spread the coils over the chip, are faster from a few coils on (FP32, whose products take
-// longer, from fewer): the gradient in registers -> by maps, BF16-split and FP32, takes 267 -> 119
-// and 351 -> 121 us at 20^3, 128 coils, ranks 8; 207 -> 120 and 338 -> 136 at 36^3, 32 coils, ranks
-// 18; 133 -> 115 and 170 -> 126 at 60^3, 8 coils, ranks 20.  From 512 waves on the adjoint, which
-// would have to form the maps first, is faster or even in registers (90^3, 8 coils, ranks 32:
-// 142 against 172 by maps, 196 against 195; 120 x 100 x 90, 8 coils: 158 against 201, 204 against
-// 229), and so it is at one or two coils everywhere (20^3: 0.91-0.95 of the time by maps).
-bool tucker_images_gx_fits(int64_t n0, int64_t n1, int J, int precision) {
-  return n0 * ((n1 + 15) / 16) >= 512 || J <= (precision == 1 ? 4 : 2);
+template <int PREC>
+hipError_t images_by_rank(const RowsArgs& r, hipStream_t st) {
+  BY_RANK(r.r2, (images_any<PREC, PT>(r, st)))
 }
-
-hipError_t tucker_maps_launch(const TuckerRows& a, const float2* T2, float2* S, hipStream_t st) {
-  RowsArgs r = rows_args(a);
-  r.T2 = T2;
-  r.S = S;
-  BY_RANK((maps<PREC, PT>(r, st)))
+template <int PREC>
+hipError_t mode1_by_rank(const TuckerRows& a, const float2* Q3, float2* Q2, hipStream_t st) {
+  BY_RANK(a.r2, (mode1_adj<PREC, PT>(a, Q3, Q2, st)))
 }
-
-hipError_t tucker_images_launch(const TuckerRows& a, const float2* T2, const float2* x, const float2* g, float alpha,
-                                const float* alpha_dev, float2* gx, float2* Q3, hipStream_t st) {
-  RowsArgs r = rows_args(a);
-  r.T2 = T2;
-  r.x = x;
-  r.g = g;
-  r.alpha = alpha;
-  r.alpha_dev = alpha_dev;
-  r.gx = gx;
-  r.Q3 = Q3;
-  BY_RANK((images_any<PREC, PT>(r, st)))
-}
-
-hipError_t tucker_mode1_adjoint_launch(const TuckerRows& a, const float2* Q3, float2* Q2, hipStream_t st) {
-  BY_RANK((mode1_adj<PREC, PT>(a, Q3, Q2, st)))
-}
-
 #undef BY_RANK
+
+}  // namespace
 
 }  // namespace mx

@@ -1,4 +1,4 @@
-// Tucker products of the general 3D path around the coil images (tucker_stream.hip).
+// Tucker products of the general 3D path around the coil images (tucker_rows.h).
 #pragma once
 
 #include "common.h"
