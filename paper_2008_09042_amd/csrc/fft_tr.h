@@ -463,14 +463,21 @@ __global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 || (!BIG && SMP >=
 // passes), of an image and of a gridding window
 #define TR_IMAGE(F) F(0, 0, -1) F(1, 0, 1) F(2, 1, 1) F(3, 2, -1) F(8, 8, -1) F(9, 9, -1) F(10, 10, -1)
 #define TR_GRID(F) F(4, 4, -1) F(5, 5, 1) F(6, 6, -1) F(7, 7, 1)
-// the forward pass with the residual is prepared for radices up to 16 alone
-#define TR_BUILT(SMP) (BIG && SMP == 9 ? 10 : SMP)
+// The forward pass with the residual written out (9) is built for radices up to 16 alone: with
+// larger ones its launch is an error.
+template <bool BIG>
+constexpr bool tr_built(int smp) { return !(BIG && smp == 9); }
 
 template <bool BIG, bool GRID>
 hipError_t tr_launch_one(const FftLaunch& l, hipStream_t st) {
   const dim3 gr((unsigned)l.blocks), bl((unsigned)l.threads);
 #define TR_LAUNCH(I, SMP, DIR) \
-  case I: hipLaunchKernelGGL((fft_tr_kernel<TR_BUILT(SMP), DIR, BIG>), gr, bl, l.lds, st, l.a); break;
+  case I:                                                                                         \
+    if constexpr (tr_built<BIG>(SMP))                                                             \
+      hipLaunchKernelGGL((fft_tr_kernel<SMP, DIR, BIG>), gr, bl, l.lds, st, l.a);                 \
+    else                                                                                          \
+      return hipErrorInvalidValue;                                                                \
+    break;
   if constexpr (GRID) {
     switch (l.variant) { TR_GRID(TR_LAUNCH) default: return hipErrorInvalidValue; }
   } else {
@@ -484,7 +491,12 @@ template <bool BIG>
 hipError_t tr_launch_many(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st) {
   const dim3 gr((unsigned)m.start[m.n]), bl((unsigned)threads);
 #define TR_LAUNCH(I, SMP, DIR) \
-  case I: hipLaunchKernelGGL((fft_tr_multi_kernel<TR_BUILT(SMP), DIR, BIG>), gr, bl, lds, st, m); break;
+  case I:                                                                                         \
+    if constexpr (tr_built<BIG>(SMP))                                                             \
+      hipLaunchKernelGGL((fft_tr_multi_kernel<SMP, DIR, BIG>), gr, bl, lds, st, m);               \
+    else                                                                                          \
+      return hipErrorInvalidValue;                                                                \
+    break;
   switch (variant) { TR_IMAGE(TR_LAUNCH) TR_GRID(TR_LAUNCH) default: return hipErrorInvalidValue; }
 #undef TR_LAUNCH
   return hipGetLastError();
