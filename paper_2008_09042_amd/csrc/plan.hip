@@ -26,6 +26,7 @@
 #include "skinny.h"
 #include "tucker_stream.h"
 #include "plan.h"
+#include "plane_groups.h"
 #include "tune.h"
 
 namespace mx {
@@ -666,34 +667,13 @@ maxwell_status plan_build(Plan& p, const maxwell_plan_desc& d, const maxwell_bas
     p.fused = true;
     p.L = (int64_t)pos.size();
     {
-      // coils per plane workgroup: the time of a launch is about its rounds over the compute
-      // units (one workgroup each: the plane fills the LDS) times the coils of a group, plus
-      // half a coil's worth of set-up per workgroup.  Halving from 16 until every compute
-      // unit had a workgroup took 2 coils in 2 rounds where 3 fit one (64 planes, 12 coils).
-      // The adjoint's groups each write a gx partial: no more of them than the halving rule
-      // gives, and the fewest at equal cost.
       int dev = 0, cus = 256;
       if (hipGetDevice(&dev) == hipSuccess &&
           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
-      auto groups = [&](int G) { return (p.J + G - 1) / G; };
-      int halved = 16;
-      while (halved > 1 && p.n[2] * groups(halved) < cus) halved /= 2;
-      auto pick = [&](int max_groups) {
-        int best = halved;
-        double cost = 0.0;
-        for (int G = std::min(16, p.J); G >= 1; --G) {
-          if (groups(G) > max_groups || groups(G) * (int64_t)G - p.J >= G) continue;
-          const double c = (double)((p.n[2] * groups(G) + cus - 1) / cus) * (G + 0.5);
-          if (cost == 0.0 || c < cost) {
-            cost = c;
-            best = G;
-          }
-        }
-        return best;
-      };
-      p.G_fwd = pick(p.J);
-      p.G_adj = pick(groups(halved));
+      const PlaneGroups g = plane_groups(p.n[2], p.J, cus);
+      p.G_fwd = g.fwd;
+      p.G_adj = g.adj;
     }
     if ((e = hipMalloc(&p.d_pos, pos.size() * sizeof(int32_t))) != hipSuccess) return hip_err(e);
     if ((e = hipMemcpy(p.d_pos, pos.data(), pos.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
