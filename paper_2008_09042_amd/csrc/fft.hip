@@ -26,7 +26,6 @@ namespace {
 
 // ---------------------------------------------------------------- pass by pass in LDS
 constexpr int NT = 256;
-constexpr int TR_NT = 256;          // most threads of a two-radix workgroup
 constexpr int TILE = 4096;          // complex elements per LDS tile at most (before padding):
                                     // with the twiddles, about 40 KB, four workgroups per CU
 constexpr int TW_LDS_MAX = 1024;    // twiddle tables up to this length are staged in LDS
@@ -445,11 +444,8 @@ bool fft_tr_supported(int64_t n) {
 
 void fft_collect(std::vector<FftLaunch>* sink) { g_fft_collect = sink; }
 
-// Lines per workgroup: enough workgroups to spread a small transform over the whole
-// chip (about 1024), at most 64 lines or TILE elements per tile (small tiles keep
-// several workgroups resident per CU), and for strided lines at least 8 adjacent ones
-// (64-byte runs per load) where the tile allows.  With a collector set on the calling
-// thread (fft_collect) the prepared pass is appended to it instead of launched.
+// One pass, prepared and launched; with a collector set on the calling thread (fft_collect) it is
+// appended to it instead.
 hipError_t fft_axis_launch(const FftAxisArgs& args, hipStream_t st) {
   FftLaunch l;
   hipError_t e = fft_axis_prepare(args, l);

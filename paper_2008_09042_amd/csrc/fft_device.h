@@ -232,6 +232,7 @@ __device__ __forceinline__ void tr_twiddle(float2 (&v)[R], const float2* tw, int
   }
 }
 
+constexpr int TR_NT = 256;  // most threads of a two-radix workgroup
 #define TR_SMALL(F) F(2) F(3) F(4) F(5) F(6) F(8) F(9) F(10) F(12) F(15) F(16)
 #define TR_LARGE(F) F(18) F(20) F(24) F(25) F(27) F(30) F(32)
 

@@ -19,7 +19,7 @@ namespace {
 // butterfly straight from memory into registers, transforms them, exchanges them with the
 // other threads of its line through LDS once, transforms R1 of them and stores the outputs
 // straight to memory.  An element crosses LDS once (a store and a load) and the workgroup
-// meets one barrier, where the pass-by-pass form below crosses it once per radix and once
+// meets one barrier, where the pass-by-pass form (fft.hip) crosses it once per radix and once
 // more on the way in and out, with two barriers per radix.
 //
 // The chessboard signs of the centred transform are index shifts here: the plain DFT of the
@@ -37,8 +37,6 @@ namespace {
 // 128 coils (537 MB) 115-133 against 148-192 us (4.0-4.7 TB/s; a copy reaches 5.0), the three
 // of 120 x 100 x 90 and 8 coils (138 MB each) 19-34 against 49-67 us, a gridding pass at
 // 512 x 512 and 16 coils 11-16 against 19-27 us.
-constexpr int TR_NT = 256;
-
 // Where one line of a tile comes from and goes to.  SMP as in fft_axis_body, with the
 // gridding window's passes visiting only the lines that carry work: the pad pass (4) takes
 // its lines from the J wn0 window rows, the crop pass (5) from the wn1 window columns.
@@ -448,7 +446,7 @@ __global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 || (!BIG && SMP >=
   fft_tr_body<SMP, DIR, BIG>(a, blockIdx.x, gridDim.x);
 }
 
-// Several passes (of different slices) in one launch, as fft_axis_multi_kernel below.
+// Several passes (of different slices) in one launch, as fft_axis_multi_kernel (fft.hip).
 template <int SMP, int DIR, bool BIG>
 __global__ __launch_bounds__(TR_NT, (BIG ? 3 : 5) - (SMP == 4 || (!BIG && SMP >= 9) ? 1 : 0)) void fft_tr_multi_kernel(FftMulti m) {
   int i = 0;

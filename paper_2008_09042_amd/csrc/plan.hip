@@ -23,7 +23,7 @@
 #include "nufft.h"
 #include "solver.h"
 #include "admm.h"
-#include "skinny.h"
+#include "dense_stream.h"
 #include "tucker_stream.h"
 #include "plan.h"
 #include "plane_groups.h"

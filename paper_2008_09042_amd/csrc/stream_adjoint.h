@@ -18,7 +18,7 @@
 #pragma once
 
 #include "mfma_frag.h"
-#include "skinny.h"
+#include "dense_stream.h"
 
 #include <algorithm>
 

@@ -22,7 +22,7 @@
 #pragma once
 
 #include "mfma_frag.h"
-#include "skinny.h"
+#include "dense_stream.h"
 
 namespace mx {
 

@@ -97,8 +97,10 @@ struct Share {
 };
 
 // The wave's index in a scalar register with run-time rank blocks (and in the JVP kernel):
-// uniform branches and offsets, no spills (the run-time adjoint had 61, at 96 x 80 78 -> 64 us).
-// The compile-time rank blocks fit as they are and lose 2 % to it (128 x 128: 402 -> 410 us).
+// uniform branches and offsets, and fewer spilled registers (96 x 80 adjoint 78 -> 64 us).  At
+// run-time plane sizes, without -> with it, FP32 adjoint 6 and 23 (both gradients, one) -> none,
+// JVP 10 -> none; BF16-split adjoint 10 and 61 -> none and 20, JVP 93 -> 73.  The compile-time
+// rank blocks fit as they are and lose 2 % to it (128 x 128: 402 -> 410 us).
 template <bool SCALAR>
 __device__ __forceinline__ int wave_index() {
   const int w = threadIdx.x >> 6;
@@ -536,7 +538,6 @@ __global__ __launch_bounds__(PT) void plane_fwd_kernel(PlaneArgs a) {
 // (P and P' whole would take 128 registers).
 template <int PREC, int N0, int N1, int RB>
 __global__ __launch_bounds__(PT) void plane_jvp_kernel(PlaneArgs a) {
-  constexpr bool HALF = false;
   __shared__ float2 lds[LDS_ELEMS];
   const Geo<N0, N1, RB> g(a);
   const int ngrp = (a.J + a.G - 1) / a.G;
@@ -570,11 +571,11 @@ __global__ __launch_bounds__(PT) void plane_jvp_kernel(PlaneArgs a) {
       for (int e = tid; e < n; e += PT) dst[e] = src[e];
       w_store<PREC>(g, lds, tid, w);
       __syncthreads();
-      coil_v<PREC, HALF>(g, lds, lane, u1, v1);
+      coil_v<PREC, false>(g, lds, lane, u1, v1);
       __syncthreads();  // W is consumed
       w_store<PREC>(g, lds, tid, w2);
       __syncthreads();
-      coil_v<PREC, HALF>(g, lds, lane, u1, v2);
+      coil_v<PREC, false>(g, lds, lane, u1, v2);
     }
     float2 m[8][4];
     {
@@ -596,8 +597,8 @@ __global__ __launch_bounds__(PT) void plane_jvp_kernel(PlaneArgs a) {
           for (int s = 0; s < 3; ++s)
             if (s < g.r0b) {
               const typename Tile<PREC>::A u = frag_a<PREC>(lds, g.r0b, rb, s, lane);
-              rank_mma<PREC>(c1, u, v1[s], HALF && s == g.r0b - 1);
-              rank_mma<PREC>(c2, u, v2[s], HALF && s == g.r0b - 1);
+              rank_mma<PREC>(c1, u, v1[s], false);
+              rank_mma<PREC>(c2, u, v2[s], false);
             }
           f32x4 pr, pi, qr, qi;
           Tile<PREC>::finish(c1, pr, pi);
@@ -1180,8 +1181,9 @@ void adj_launch(dim3 grid, dim3 block, const PlaneArgs& a, hipStream_t st) {
     else hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0>), grid, block, 0, st, a);
   } else {
     if constexpr (N0 == 0) {
-      // run-time plane sizes: the map held across the transform spilled 126 registers (128 x 96
-      // planes 412 -> 296 us with the late form, 48 x 128 265 -> 166, 96 x 80 106 -> 78)
+      // run-time plane sizes: the map held across the transform spills 98 registers with both
+      // gradients and 209 with one (128 x 96 planes 412 -> 296 us with the late form, 48 x 128
+      // 265 -> 166, 96 x 80 106 -> 78)
       if (full) hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0, true>), grid, block, 0, st, a);
       else hipLaunchKernelGGL((plane_adj_late_kernel<PREC, N0, N1, 0>), grid, block, 0, st, a);
     } else {
