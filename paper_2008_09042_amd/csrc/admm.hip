@@ -38,14 +38,14 @@ struct Dims {
   int64_t n[3], stride[3], N;
 };
 
-// The pixel of a thread of a (64, 4) workgroup of the three-dimensional grid: the workgroup's
-// position is the index, so no index is divided.
+// The pixel of a thread of a workgroup of the three-dimensional grid: the workgroup's position is
+// the index, so no index is divided.
 __device__ __forceinline__ bool tv_pixel(const Dims& g, int64_t& i, int (&c)[3]) {
-  c[2] = blockIdx.x * 64 + threadIdx.x;
-  c[1] = blockIdx.y * 4 + threadIdx.y;
-  c[0] = blockIdx.z;
+  c[2] = blockIdx.x * blockDim.x + threadIdx.x;
+  c[1] = blockIdx.y * blockDim.y + threadIdx.y;
+  c[0] = blockIdx.z * blockDim.z + threadIdx.z;
   i = c[0] * g.stride[0] + c[1] * g.stride[1] + c[2];
-  return c[2] < g.n[2] && c[1] < g.n[1];
+  return c[2] < g.n[2] && c[1] < g.n[1] && c[0] < g.n[0];
 }
 
 // div P - z inv_lam at pixel i
@@ -411,7 +411,18 @@ hipError_t tv_prox_launch(int nd, const int64_t* n, const TvInput& in, int iters
     } while (k < iters);
     return hipGetLastError();
   }
-  const dim3 gr((unsigned)((g.n[2] + 63) / 64), (unsigned)((g.n[1] + 3) / 4), (unsigned)g.n[0]), bl(64, 4);
+  // A wave along the last axis, the rest of the workgroup's threads along the others: at most 64
+  // pixels of the last axis, and no more of the last two than they hold, rounded up to a power of
+  // two.  Always (64, 4, 1) left a short axis' threads without pixels: 500 x 480 x 2, 20 steps 4814 -> 272 us,
+  // 400 x 400 x 4 3558 -> 422.
+  auto side = [](int64_t n, int most) {
+    int b = 1;
+    while (b < n && b < most) b *= 2;
+    return b;
+  };
+  const int bx = side(g.n[2], 64), by = side(g.n[1], NT / bx), bz = NT / (bx * by);
+  const dim3 bl(bx, by, bz), gr((unsigned)((g.n[2] + bx - 1) / bx), (unsigned)((g.n[1] + by - 1) / by),
+                                (unsigned)((g.n[0] + bz - 1) / bz));
   hipError_t e = zero_split_launch(P, nullptr, (int64_t)nd * g.N, 0, st);
   if (e != hipSuccess) return e;
   for (int k = 0; k < iters; ++k) {
