@@ -116,10 +116,14 @@ __global__ __launch_bounds__(TR_NT, 1) void fft_combine_kernel(FftAxisArgs a, co
 }  // namespace
 
 // Two radices of at most 16, and rows enough for a workgroup on most compute units: with 64 rows
-// the separate passes spread the coils over the chip instead.
+// the separate passes spread the coils over the chip instead.  With many rows they win too: a
+// workgroup here runs at one wave per SIMD and holds few threads where the row is short.  Normal
+// operator, this / separate: 256 rows of 256 at 32 coils 41.2 / 49.8 us, of 16 at 2 coils 15.3 / 17.4;
+// 1024 rows of 90 at 32 coils 64.2 / 56.6, of 128 at 8 coils 39.2 / 39.5; 8192 rows of 128 at 8 coils 172 /
+// 150, of 4 at 2 coils 39.8 / 24.6; 160000 rows of 4 at 2 coils 464 / 70.
 bool fft_combine_supported(int64_t n, int64_t rows) {
   int r0, r1;
-  return rows >= 128 && rows < ((int64_t)1 << 31) && fft_tr_radices(n, r0, r1) && r0 <= 16 && r1 <= 16;
+  return rows >= 128 && rows <= 512 && fft_tr_radices(n, r0, r1) && r0 <= 16 && r1 <= 16;
 }
 
 hipError_t fft_combine_launch(const float2* src, const float2* S, int64_t n, int64_t rows, int J, const float2* twiddle,
