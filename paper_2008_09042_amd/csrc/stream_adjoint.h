@@ -18,9 +18,8 @@
 #pragma once
 
 #include "mfma_frag.h"
+#include "adjoint_geom.h"
 #include "dense_stream.h"
-
-#include <algorithm>
 
 namespace mx {
 
@@ -42,42 +41,7 @@ hipError_t stream_adjoint_bf16(const AdjCall& a, hipStream_t st);
 
 namespace {
 
-constexpr int NW = 8, NT = 64 * NW;
-
-struct AdjGeom {
-  int JB, AKB, jgs;  // 16-coil blocks and 16-column blocks per wave, coil groups
-  int kwl, ks;       // log2 of the column groups per workgroup (0 or 1), workgroups per row chunk along K
-  int64_t chunk;     // rows per workgroup
-  int nchunk;
-};
-
-// Waves: two column groups where K has two, and row groups.  A workgroup over all of K (up to
-// eight groups) left its partials, one per row chunk, to be most of the traffic of a short
-// basis, and each wave a step or two: 64 x 64, 17 coils, 300 columns, BF16-split 20.7 -> 12.1 us,
-// FP32 23.1 -> 14.5; 128 x 128, 32 coils, 512 columns 35.4 -> 23.4; 256 x 256, 32 coils, 200
-// columns 32.8 -> 28.4.  One group per workgroup reads h once per 64 columns: better up to
-// 256 x 256 (26.9), worse beyond (512 x 512, 16 coils, 100 columns 44.3 -> 52.3).
-// Row chunks: a workgroup per compute unit over all coil and column groups (two where the
-// tiles are small enough that two share one), at least one step of every row group, and no more
-// than max_chunks (0: no limit).
-AdjGeom adj_geom(int64_t N, int64_t K, int J, int max_chunks) {
-  AdjGeom a;
-  const int nkb = (int)((K + 15) / 16), njb = (J + 15) / 16;
-  a.JB = njb == 1 ? 1 : njb == 2 ? 2 : 4;
-  a.jgs = (njb + a.JB - 1) / a.JB;
-  a.AKB = a.JB < 4 && nkb > 2 ? 4 : 2;
-  const int groups = (nkb + a.AKB - 1) / a.AKB;
-  a.kwl = groups > 1 ? 1 : 0;
-  a.ks = (groups + (1 << a.kwl) - 1) >> a.kwl;
-  const int64_t step = (int64_t)16 * (NW >> a.kwl);
-  int64_t want = (a.JB == 1 ? 512 : 256) / ((int64_t)a.jgs * a.ks);
-  if (want < 32) want = 32;
-  if (max_chunks > 0 && want > max_chunks) want = max_chunks;
-  a.chunk = (N + want - 1) / want;
-  a.chunk = (a.chunk + step - 1) / step * step;
-  a.nchunk = (int)((N + a.chunk - 1) / a.chunk);
-  return a;
-}
+constexpr int NW = ADJ_WAVES, NT = 64 * NW;
 
 template <int PREC, int JB, int AKB, int VEC, bool X>
 __global__ __launch_bounds__(NT) void stream_adjoint_kernel(const float2* __restrict__ B, int64_t N, int K,
