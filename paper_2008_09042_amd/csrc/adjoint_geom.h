@@ -10,7 +10,7 @@ constexpr int ADJ_WAVES = 8;  // per workgroup
 
 struct AdjGeom {
   int JB, AKB, jgs;  // 16-coil blocks and 16-column blocks per wave, coil groups
-  int kwl, ks;       // log2 of the column groups per workgroup (0 or 1), workgroups per row chunk along K
+  int kwl, ks;       // log2 of the column groups per workgroup (0 to 2), workgroups per row chunk along K
   int64_t chunk;     // rows per workgroup
   int nchunk;
 };
@@ -21,6 +21,10 @@ struct AdjGeom {
 // FP32 23.1 -> 14.5; 128 x 128, 32 coils, 512 columns 35.4 -> 23.4; 256 x 256, 32 coils, 200
 // columns 32.8 -> 28.4.  One group per workgroup reads h once per 64 columns: better up to
 // 256 x 256 (26.9), worse beyond (512 x 512, 16 coils, 100 columns 44.3 -> 52.3).
+// Three or four groups of many rows take one workgroup over all of K: two of them would be
+// uneven, a whole workgroup for a few last columns, and read h twice (two groups -> four,
+// 512 x 512, 3 coils, 130 columns 67.5 -> 52.9 us; 1000 x 800, 16 coils, 130 columns 233 -> 185;
+// but 256 x 256, 32 coils, 200 columns 30.2 -> 34.6).
 // Row chunks: a workgroup per compute unit over all coil and column groups (two where the
 // tiles are small enough that two share one), or as few rounds of that as leave at most a tenth
 // of the last one idle, at least one step of every row group, and no more than max_chunks (0: no
@@ -33,7 +37,7 @@ inline AdjGeom adj_geom(int64_t N, int64_t K, int J, int max_chunks) {
   a.jgs = (njb + a.JB - 1) / a.JB;
   a.AKB = a.JB < 4 && nkb > 2 ? 4 : 2;
   const int groups = (nkb + a.AKB - 1) / a.AKB;
-  a.kwl = groups > 1 ? 1 : 0;
+  a.kwl = (groups == 3 || groups == 4) && N >= 131072 ? 2 : groups > 1 ? 1 : 0;
   a.ks = (groups + (1 << a.kwl) - 1) >> a.kwl;
   const int64_t step = (int64_t)16 * (ADJ_WAVES >> a.kwl);
   const int64_t slots = a.JB == 1 ? 512 : 256, per = (int64_t)a.jgs * a.ks;

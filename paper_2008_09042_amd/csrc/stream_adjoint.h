@@ -5,7 +5,7 @@
 // (tile rows k, reduction n) is conj(B) read down four rows per lane, two adjacent columns at
 // a time where rows are 16-byte aligned (256 contiguous bytes of a row per 16 lanes; the two
 // columns belong to two tiles); the B operand is h, 32 contiguous bytes per lane.  A
-// workgroup's eight waves are one or two groups of 16 AKB columns times groups of rows; a wave
+// workgroup's eight waves are one, two or four groups of 16 AKB columns times groups of rows; a wave
 // loads the next 16 rows while it multiplies the current ones.  Every load is unconditional
 // (addresses clamped): a guarded load makes every use wait for all loads in flight.  The row
 // groups' tiles are added through LDS in a fixed order, one partial per workgroup, and a
