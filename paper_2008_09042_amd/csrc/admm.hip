@@ -420,9 +420,19 @@ hipError_t tv_prox_launch(int nd, const int64_t* n, const TvInput& in, int iters
     while (b < n && b < most) b *= 2;
     return b;
   };
-  const int bx = side(g.n[2], 64), by = side(g.n[1], NT / bx), bz = NT / (bx * by);
-  const dim3 bl(bx, by, bz), gr((unsigned)((g.n[2] + bx - 1) / bx), (unsigned)((g.n[1] + by - 1) / by),
-                                (unsigned)((g.n[0] + bz - 1) / bz));
+  // A small image is bound by latency: a workgroup with a short last axis is halved, down to a wave, while
+  // there are few of them (20 steps at 32 x 30 x 16 134 -> 111 us, 18 x 36 x 10 144 -> 126, 64 x 30 x 24
+  // 138 -> 123; (64, 4, 1) takes 119, 130 and 126).
+  const int bx = side(g.n[2], 64);
+  int by, bz;
+  dim3 gr;
+  for (int threads = NT;; threads /= 2) {
+    by = side(g.n[1], threads / bx);
+    bz = threads / (bx * by);
+    gr = dim3((unsigned)((g.n[2] + bx - 1) / bx), (unsigned)((g.n[1] + by - 1) / by), (unsigned)((g.n[0] + bz - 1) / bz));
+    if (bx == 64 || threads == 64 || (int64_t)gr.x * gr.y * gr.z >= 384) break;
+  }
+  const dim3 bl(bx, by, bz);
   hipError_t e = zero_split_launch(P, nullptr, (int64_t)nd * g.N, 0, st);
   if (e != hipSuccess) return e;
   for (int k = 0; k < iters; ++k) {
