@@ -150,7 +150,7 @@ hipError_t fft_tr16_multi(int variant, int threads, size_t lds, const FftMulti& 
 hipError_t fft_tr32_multi(int variant, int threads, size_t lds, const FftMulti& m, hipStream_t st);
 // out [rows][n] = sum_j conj(S_j) (.) (the inverse centred transform of src_j along its rows), for
 // stacks [J][rows][n] (fft_combine.hip).
-bool fft_combine_supported(int64_t n, int64_t rows);
+bool fft_combine_supported(int64_t n, int64_t rows, int J);
 hipError_t fft_combine_launch(const float2* src, const float2* S, int64_t n, int64_t rows, int J, const float2* twiddle,
                               float2* out, hipStream_t st);
 int fft_factorise(int64_t n, int* radix);  // returns number of passes, 0 if unsupported

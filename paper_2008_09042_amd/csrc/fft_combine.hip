@@ -121,15 +121,17 @@ __global__ __launch_bounds__(TR_NT, 1) void fft_combine_kernel(FftAxisArgs a, co
 // operator, this / separate: 256 rows of 256 at 32 coils 41.2 / 49.8 us, of 16 at 2 coils 15.3 / 17.4;
 // 1024 rows of 90 at 32 coils 64.2 / 56.6, of 128 at 8 coils 39.2 / 39.5; 8192 rows of 128 at 8 coils 172 /
 // 150, of 4 at 2 coils 39.8 / 24.6; 160000 rows of 4 at 2 coils 464 / 70.
-bool fft_combine_supported(int64_t n, int64_t rows) {
+// With few coils the launch that is saved carries the pass a little further: 640 rows of 64 at 4 coils
+// 21.8 / 24.3, 900 of 240 at 8 coils 49.8 / 53.8.
+bool fft_combine_supported(int64_t n, int64_t rows, int J) {
   int r0, r1;
-  return rows >= 128 && rows <= 512 && fft_tr_radices(n, r0, r1) && r0 <= 16 && r1 <= 16;
+  return rows >= 128 && rows <= (J <= 8 ? 960 : 512) && fft_tr_radices(n, r0, r1) && r0 <= 16 && r1 <= 16;
 }
 
 hipError_t fft_combine_launch(const float2* src, const float2* S, int64_t n, int64_t rows, int J, const float2* twiddle,
                               float2* out, hipStream_t st) {
   int r0, r1;
-  if (!fft_combine_supported(n, rows) || !fft_tr_radices(n, r0, r1) || J < 1) return hipErrorInvalidValue;
+  if (!fft_combine_supported(n, rows, J) || !fft_tr_radices(n, r0, r1) || J < 1) return hipErrorInvalidValue;
   FftAxisArgs a;
   std::memset(&a, 0, sizeof(a));
   a.src = src;

@@ -1553,7 +1553,7 @@ static hipError_t sense_normal_op(const Plan& p, const float2* S, const float2* 
   if (round_trip_supported(p)) {
     float2* Kb = wsp<float2>(ws, p.off_K);
     const int64_t nl = p.n[p.ndim - 1], rows = p.N / nl;
-    const bool combine = fft_combine_supported(nl, rows);
+    const bool combine = fft_combine_supported(nl, rows, p.J);
     if ((e = fft_round_trip(p, S, Kb, x, st, nullptr, combine)) != hipSuccess) return e;
     if (combine)  // the last pass sums over the coils
       e = TIMED("fft_combine", fft_combine_launch(Kb, S, nl, rows, p.J, p.d_tw[p.ndim - 1], out, st));

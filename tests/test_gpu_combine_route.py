@@ -1,5 +1,6 @@
 """Where the SENSE normal operator sums over the coils in its last inverse pass: from 128 to 512 rows
-of a last axis of two radices up to 16; with fewer or more the combination stays a pass of its own.
+(960 up to eight coils) of a last axis of two radices up to 16; with fewer or more the combination stays a
+pass of its own.
 Sizes on both sides of the lines, against the oracle at the operator's bar, 1e-5."""
 import numpy as np
 import pytest
@@ -16,8 +17,10 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("dims,J,summed", [((120, 30), 3, False), ((128, 30), 3, True), ((512, 12), 5, True),
-                                           ((540, 12), 5, False), ((24, 24, 4), 2, False), ((16, 32, 4), 2, True),
-                                           ((30, 20, 256), 2, False), ((16, 20, 128), 9, True), ((128, 288), 2, False)])
+                                           ((512, 12), 9, True), ((540, 12), 9, False), ((540, 12), 8, True),
+                                           ((960, 30), 5, True), ((1024, 16), 5, False), ((24, 24, 4), 9, False),
+                                           ((24, 24, 4), 2, True), ((16, 32, 4), 2, True), ((30, 20, 256), 9, False),
+                                           ((30, 20, 64), 2, True), ((16, 20, 128), 9, True), ((128, 288), 2, False)])
 def test_combine_route(dims, J, summed):
     from paper_2008_09042_amd.encoding import MaxwellPlan
     rng = np.random.default_rng([112, J, *dims])
